@@ -261,8 +261,11 @@ int xyl_get_launch(xyl_lattice* h, int32_t* rows_per_strip, int32_t* waves_per_b
 int xyl_autotune(xyl_lattice* h);
 /* Steps per captured HIP graph used by xyl_step (0 or 1 disables graphs). */
 int xyl_set_graph_steps(xyl_lattice* h, int32_t steps);
-/* Steps per pass over the state for plain FP32 stepping (1 or 2; default 2).
- * With 2, runs of 4m steps without measurements advance two steps per pass
+/* Steps per pass over the state for plain stepping (1 or 2; default 2).
+ * With 2, lattices up to 4096 sites wide take several steps per launch on
+ * tiles held in registers and LDS (either precision) where a rule of the sizes
+ * (or xyl_autotune) finds that faster, runs of an even number of steps; else,
+ * in FP32, runs of 4m steps without measurements advance two steps per pass
  * (one workgroup per strip of rows across the whole width, the second step
  * one row behind the first) where Ly >= 4 and Lx is at most 4096, uses at
  * least three quarters of the lanes of its waves (256 sites per wave) and at
@@ -272,7 +275,7 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps);
  * exists.  Other shapes, FP64 and measurement steps use single steps.
  * Results are bitwise identical either way; two steps per pass read and write
  * the state once per two steps.  The library allocates a second velocity
- * buffer (4 Lx Ly bytes) on first use; the state returns to the lattice's own
+ * buffer (the state's size) on first use; the state returns to the lattice's own
  * buffers at the end of every call. */
 int xyl_set_fusion(xyl_lattice* h, int32_t steps_per_pass);
 /* The stepping mode in effect: *steps_per_pass = the value set by
@@ -288,7 +291,8 @@ int xyl_get_fusion(const xyl_lattice* h, int32_t* steps_per_pass, int32_t* rows)
  * tiles mean more of them, and up to eight workgroups per CU; below the
  * row's own waves it splits rows up to 4096 sites wide as well, into at least
  * two tiles); 0 keeps the current value.  A tile width no split fits falls
- * back to whole rows (up to 4096 sites) or the fewest tiles.
+ * back to whole rows (up to 4096 sites) or the fewest tiles.  A lattice whose
+ * shape was set takes the two-step pass in place of several steps per launch.
  * Results do not depend on it.  xyl_autotune sets both.  EINVAL outside the
  * ranges. */
 int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves);

@@ -31,6 +31,7 @@
 #include "xyl_domains.hpp"
 #include "xyl_internal.hpp"
 #include "xyl_obs.hpp"
+#include "xyl_tile.hpp"
 
 namespace xyl {
 
@@ -257,6 +258,7 @@ static std::map<std::tuple<int, int, int>, Launch> g_tuned;
 // pass, chosen by xyl_autotune
 struct Tuned2 {
     int fusion, rows, tile_waves;
+    bool tiles;            // several steps per launch on tiles
 };
 static std::map<std::tuple<int, int, int>, Tuned2> g_tuned2;
 // launch shape of measurements without a step, chosen by xyl_autotune
@@ -324,6 +326,9 @@ struct xyl_lattice {
     int cus = 256;                 // compute units of the device
     int step2_rows_tuned = 0;      // rows per strip of the two-step pass from xyl_autotune (0: the size rule)
     int step2_tw_tuned = 0;        // most waves per column tile (widths above 4096) from xyl_autotune (0: the rule)
+    bool tiles = true;             // several steps per launch on tiles allowed
+    bool tiles_tuned = false;      // xyl_autotune timed them faster: no rule needed
+    std::map<uint64_t, TilePlan> tile_plans;   // by the steps to take (T = 0: none)
     int adj2_rows = 0;             // rows per strip of the two-step reverse pass (0: the rule)
     int adj_fusion = 2;            // reverse steps per pass of the adjoint sweep (1 or 2)
     DevBuf<char> u2;               // second velocity buffer of the two-step passes
@@ -482,14 +487,29 @@ static int step2_tile_waves(const xyl_lattice* h) {
     return h->step2_tw_tuned ? h->step2_tw_tuned : step2_tile_waves(h->Lx);
 }
 
-// Rows per strip of the two-step kernel.  A workgroup spans the row (Lx / 256
-// waves of up to 128 VGPRs, 32 Lx bytes of LDS), so a CU holds
-// per_cu = min(16 / waves, 160 KiB / LDS) of them.  The strip count aims at
-// CUs x max(1, per_cu / 2): every CU busy, two or more workgroups per CU where
-// they fit, and strips as tall as that allows (each strip recomputes two halo
-// rows of the first step), 2 to 16 rows.  Measured best over 512^2 .. 4096^2,
-// 4096 x 1024, 1024 x 4096 and 256 x 8192 (strip counts off a multiple of the
-// CU count leave a partial last round of workgroups).
+// Time per step (us) of whole-row two-step passes with strips of `rows` rows,
+// as a rule for choosing: a pass takes 3 us and, for every round of strips
+// that the CUs hold at once, rows + 2 iterations (two halo rows) of
+// sqrt(1 + (0.6 x)^2) us each, x the waves per SIMD (a row of 256 sites per
+// wave; min(16 / waves, 160 KiB / LDS) workgroups per CU).  Within 15% of the
+// passes measured at 512^2 .. 4096^2, 4096 x 1024, 1024 x 4096, 256 x 8192
+// and 2900^2 (29.2 us per step with 11-row strips, 264 of them on 256 CUs).
+static double step2_us(int Lx, int Ly, int cus, int rows) {
+    const int waves = (Lx + kWaveSites - 1) / kWaveSites;
+    const int fit = std::max(1, std::min(16 / waves, (160 * 1024) / (32 * Lx)));
+    const int strips = (Ly + rows - 1) / rows;
+    int left = (strips + cus - 1) / cus;
+    double us = 3.0;
+    for (; left > 0; left -= fit) {
+        const double x = 0.6 * 0.25 * waves * std::min(left, fit);
+        us += (std::min(rows, Ly) + 2) * std::sqrt(1.0 + x * x);
+    }
+    return 0.5 * us;
+}
+
+// Rows per strip of the two-step kernel: whole rows, the cheapest by the rule
+// above (strip counts just above a multiple of what the CUs hold leave a last
+// round of a few workgroups); column tiles as below.
 static int step2_rows(int Lx, int Ly, int cus, int tile_waves) {
     Step2Tiles t;
     if (step2_tiles(Lx, &t, tile_waves) || step2_tiles(Lx, &t)) {
@@ -518,10 +538,16 @@ static int step2_rows(int Lx, int Ly, int cus, int tile_waves) {
         }
         return best;
     }
-    const int waves = (Lx + kWaveSites - 1) / kWaveSites;
-    const int per_cu = std::max(1, std::min(16 / waves, (160 * 1024) / (32 * Lx)));
-    const int strips = cus * std::max(1, per_cu / 2);
-    return std::max(2, std::min(16, Ly / strips));
+    int best = 2;
+    double best_us = 1e30;
+    for (int rows = 32; rows >= 2; --rows) {
+        const double us = step2_us(Lx, Ly, cus, rows);
+        if (us < 0.98 * best_us) {   // taller strips where two are about equal
+            best_us = us;
+            best = rows;
+        }
+    }
+    return best;
 }
 static int step2_rows(const xyl_lattice* h) {
     return h->step2_rows_tuned ? h->step2_rows_tuned : step2_rows(h->Lx, h->Ly, h->cus, step2_tile_waves(h));
@@ -564,11 +590,76 @@ static hipGraphExec_t capture_steps2(xyl_lattice* h, const Lat<float>& v, int S,
     return ex;
 }
 
+// Time per step (us) of the path that a lattice takes without tiles: two-step
+// passes of whole rows, or single steps.  Single steps were measured at 7.0,
+// 15.1 and 28.2 us for 1028^2, 2052^2 and 3076 x 3000 (FP32) and 8.1, 19.4 and
+// 48.5 us for 512^2, 1024^2 and 2048^2 (FP64).
+static double lattice_untiled_us(const xyl_lattice* h) {
+    if (step2_eligible(h)) return step2_us(h->Lx, h->Ly, h->cus, step2_rows(h));
+    return h->dtype == XYL_F64 ? 6.5 + (double)h->N / 1.0e5 : 3.3 + (double)h->N / 3.7e5;
+}
+
+// Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
+// steps (n even), or NULL where another path is faster by the rules' times.
+// Widths above 4096 and lattices beyond 2^24 sites never gain (their passes
+// are bound by issue already, and tiles recompute more halo).  Plans are kept
+// per run length (64 steps and more share one).
+static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
+    if (!h->tiles || h->fusion != 2 || n < 2 || h->Lx > 16 * kWaveSites || h->N > (size_t(1) << 24)) return nullptr;
+    const uint64_t key = std::min<uint64_t>(n, 64);
+    auto it = h->tile_plans.find(key);
+    if (it == h->tile_plans.end()) {
+        TilePlan p;
+        double us = 0.0;
+        if (!tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
+            (!h->tiles_tuned && us > lattice_untiled_us(h)))
+            p = TilePlan();
+        if (p.T) {
+            // where the second velocity buffer does not fit, the other paths do
+            try {
+                h->u2.reserve(elem_size(h->dtype) * h->N);
+            } catch (const Error& e) {
+                if (e.code != XYL_ENOMEM) throw;
+                (void)hipGetLastError();
+                h->tiles = false;
+                return nullptr;
+            }
+        }
+        it = h->tile_plans.emplace(key, p).first;
+    }
+    return it->second.T ? &it->second : nullptr;
+}
+
+// n steps (n even) through an even number of launches, (A, u) -> (B, u2) ->
+// (A, u), A the buffer holding the angles at step k: the state ends where it
+// started.
+template <typename R>
+static void lattice_tile_steps(xyl_lattice* h, const TilePlan& p, uint64_t n) {
+    const Lat<R> v = h->view<R>();
+    const int parity = (int)((h->k + (uint64_t)h->cur) & 1);
+    R* th[2] = {static_cast<R*>(h->th[parity]), static_cast<R*>(h->th[parity ^ 1])};
+    R* u[2] = {static_cast<R*>(h->u), reinterpret_cast<R*>(h->u2.p)};
+    const uint64_t nl = tile_launches(n, p.T);
+    for (uint64_t i = 0; i < nl; ++i) {
+        const int t = (int)(n / nl + (i < n % nl ? 1 : 0));
+        const int a = (int)(i & 1);
+        launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, t, h->k, h->stream);
+        h->k += (uint64_t)t;
+    }
+    h->counter_valid = false;
+}
+
 // Advances n steps in the given mode.  With part_stride > 0 every step writes
 // its measurement partials to part + (k - part_k0) * part_stride.
 template <typename R>
 static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* part, uint64_t part_k0,
                                uint64_t part_stride) {
+    if (mode == kStore && part_stride == 0) {
+        if (const TilePlan* p = lattice_tile_plan(h, n - n % 2)) {
+            lattice_tile_steps<R>(h, *p, n - n % 2);
+            n %= 2;
+        }
+    }
     if constexpr (sizeof(R) == 4) {
         if (mode == kStore && part_stride == 0 && step2_eligible(h) && n >= 4) {
             h->u2.reserve(sizeof(float) * h->N);
@@ -687,7 +778,7 @@ static void lattice_measure_into(xyl_lattice* h, bool advance, double* obs_dev) 
 // passes; otherwise the measured step advances one step and the rest follow.
 template <typename R>
 static void lattice_sample_and_advance(xyl_lattice* h, uint64_t span, double* obs_dev) {
-    if (span >= 4 && step2_eligible(h)) {
+    if ((span >= 4 && step2_eligible(h)) || lattice_tile_plan(h, span - span % 2)) {
         lattice_measure_into<R>(h, false, obs_dev);
         lattice_steps<R>(h, span);
         return;
@@ -840,6 +931,7 @@ static int create_impl(xyl_lattice** out, int32_t Lx, int32_t Ly, int32_t dtype,
             auto it2 = g_tuned2.find({Lx, Ly, dtype});
             if (it2 != g_tuned2.end()) {
                 h->fusion = it2->second.fusion;
+                h->tiles = h->tiles_tuned = it2->second.tiles;
                 h->step2_rows_tuned = it2->second.rows;
                 h->step2_tw_tuned = it2->second.tile_waves;
             }
@@ -1456,7 +1548,7 @@ int xyl_get_launch(xyl_lattice* h, int32_t* rows, int32_t* wpb) {
 // the best single-step shape and sets *fusion (1 or 2, whichever is faster
 // per step) and *rows2 (rows per strip of the best two-step pass, 0 if none).
 template <typename R>
-static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, Launch* mlaunch) {
+static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, bool* tiles, Launch* mlaunch) {
     // time candidates on scratch copies so the lattice state is untouched;
     // each candidate runs as a captured graph of back-to-back steps, so the
     // host's launch overhead does not mask kernel time on small lattices
@@ -1550,6 +1642,7 @@ static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, L
             }
         }
     }
+    float best_step = best_ms / (float)reps;
     // two steps per pass: the same timing over a multiple of 4 steps, per step
     *fusion = 1;
     *rows2 = 0;
@@ -1629,7 +1722,38 @@ static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, L
                 }
             }
             *tw2 = tw;
-            if (best2 < best_ms / (float)reps) *fusion = 2;
+            if (best2 < best_step) *fusion = 2;
+            best_step = std::min(best_step, best2);
+        }
+    }
+    // several steps per launch on tiles, where a tile fits: 64 steps issued as
+    // the stepping issues them
+    *tiles = false;
+    {
+        TilePlan p;
+        if (h->Lx <= 16 * kWaveSites && tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, 64, &p, nullptr)) {
+            R* th[2] = {v.th[0], v.th[1]};
+            R* u[2] = {v.u, reinterpret_cast<R*>(tmp.p + 3 * bytes)};
+            float t = 1e30f;
+            for (int rep = 0; rep < 4; ++rep) {
+                check_hip(hipEventRecord(e0, h->stream), "hipEventRecord");
+                const uint64_t nl = tile_launches(64, p.T);
+                uint64_t k = 0;
+                for (uint64_t i = 0; i < nl; ++i) {
+                    const int n = (int)(64 / nl + (i < 64 % nl ? 1 : 0)), a = (int)(i & 1);
+                    launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, n, k, h->stream);
+                    k += (uint64_t)n;
+                }
+                check_hip(hipEventRecord(e1, h->stream), "hipEventRecord");
+                check_hip(hipEventSynchronize(e1), "hipEventSynchronize");
+                float ms = 0.f;
+                check_hip(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
+                if (rep) t = std::min(t, ms / 64.f);
+            }
+            if (t < best_step) {
+                *tiles = true;
+                *fusion = 2;
+            }
         }
     }
     (void)hipEventDestroy(e0);
@@ -1644,9 +1768,10 @@ int xyl_autotune(xyl_lattice* h) {
         require_init(h);
         DeviceGuard g(h->device);
         int fusion = 1, rows2 = 0, tw2 = 0;
+        bool tiles = false;
         Launch lm;
-        Launch l = h->dtype == XYL_F64 ? autotune_impl<double>(h, &fusion, &rows2, &tw2, &lm)
-                                       : autotune_impl<float>(h, &fusion, &rows2, &tw2, &lm);
+        Launch l = h->dtype == XYL_F64 ? autotune_impl<double>(h, &fusion, &rows2, &tw2, &tiles, &lm)
+                                       : autotune_impl<float>(h, &fusion, &rows2, &tw2, &tiles, &lm);
         h->launch = l;
         h->mlaunch = lm;
         h->mlaunch_tuned = true;
@@ -1654,12 +1779,16 @@ int xyl_autotune(xyl_lattice* h) {
             h->fusion = fusion;
             h->step2_rows_tuned = rows2;
             h->step2_tw_tuned = tw2;
+        } else if (tiles) {
+            h->fusion = 2;
         }
+        h->tiles = h->tiles_tuned = tiles;
+        h->tile_plans.clear();
         h->touch();
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_tuned[{h->Lx, h->Ly, h->dtype}] = l;
         g_tunedm[{h->Lx, h->Ly, h->dtype}] = lm;
-        if (h->dtype == XYL_F32) g_tuned2[{h->Lx, h->Ly, h->dtype}] = {fusion, rows2, tw2};
+        g_tuned2[{h->Lx, h->Ly, h->dtype}] = {h->fusion, h->step2_rows_tuned, h->step2_tw_tuned, tiles};
     });
 }
 
@@ -1687,6 +1816,7 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves) {
                 "waves per tile must be 0 or in [2, 16]");
         if (rows) h->step2_rows_tuned = rows;
         if (tile_waves) h->step2_tw_tuned = tile_waves;
+        if (rows || tile_waves) h->tiles = false;   // the caller shapes the two-step pass: take it
         h->touch();
     });
 }

@@ -1,0 +1,398 @@
+// Several BBK steps per launch on 2-D tiles, for lattices too small to keep
+// the chip busy with one or two steps per launch.
+//
+// What bounded those: a launch that steps 512^2 sites once or twice takes 5 to
+// 7 us, most of it dispatch, one round trip to memory and the latency of one
+// wave's chain of instructions, whatever the lattice's size.  Here a workgroup
+// loads a region (its tile and a halo of T sites on each side), keeps angles,
+// velocities and own rotors in registers and all rotors in LDS, and takes T
+// steps, each of them valid on a region one site smaller; only the tile is
+// stored.  The halo is recomputed by the neighbouring tiles with the same
+// arithmetic (the shared rotor / site_force / site_update / noise4), so the
+// states equal single steps bit for bit.  An axis that a tile spans whole has
+// no halo: the region is periodic there.
+//
+// One barrier per step (the rotor tables are double-buffered).  The draws of a
+// step do not depend on the state and are computed before the barrier.  Left
+// and right rotors come from the adjacent lanes by DPP, except at a wave's
+// ends and at a periodic region's, upper and lower ones from the table.
+//
+// Sites per lane S: a lane of S = 4 owns a Philox block; with S = 2 (and 1)
+// the 2 (4) lanes of a block each compute it for one of 2 (4) successive steps
+// and exchange the draws, which shortens a step's chain where there is about
+// one wave per SIMD (256^2, FP32, T = 8: 1.03 -> 0.90 us per step; 64^2, FP64:
+// 2.37 -> 1.82 with S = 1) and costs throughput where there are many.  In FP64
+// with S = 2 each lane draws its own Box-Muller pair from a block of its own
+// (the FP64 logarithm, root and sine are what a step waits for; 512^2: 4.4 us
+// per step against 4.9 with the exchange).
+//
+// Measured, us per step before (one or two steps per launch) and with tiles:
+// 64^2 FP64 7.4 -> 1.8; 96^2 FP32 5.3 -> 0.9; 512^2 FP32 3.04 -> 1.30 and FP64
+// 8.1 -> 4.5; 772 x 501 FP32 4.3 -> 1.54; 1024^2 FP32 4.6 -> 2.9; 1448^2 10.8
+// -> 5.4.  With one wave per SIMD a step costs 0.45 to 0.7 us of latency, from
+// about three waves per SIMD on it is bound by VALU issue (0.317 us per wave
+// and SIMD, 190 issue slots), of which the halo takes 20 to 45%; a launch's
+// dispatch, first loads and stores take another 2.75 us.
+#include <cmath>
+#include <mutex>
+#include <set>
+#include <type_traits>
+
+#include "xyl_device.hpp"
+#include "xyl_tile.hpp"
+
+namespace xyl {
+
+template <typename R>
+struct TileIO {
+    const R* th_in;
+    const R* u_in;
+    R* th_out;
+    R* u_out;
+};
+struct TileBox {
+    int x0, y0, w, h;     // the sites a workgroup stores
+};
+
+template <typename R, int S>
+__device__ __forceinline__ void tile_load(const R* p, R* o) {
+    if constexpr (S == 4) {
+        load4(p, o);
+    } else if constexpr (S == 2) {
+        typedef R V2 __attribute__((ext_vector_type(2)));
+        const V2 d = *reinterpret_cast<const V2*>(p);
+        o[0] = d.x;
+        o[1] = d.y;
+    } else {
+        o[0] = *p;
+    }
+}
+template <typename R, int S>
+__device__ __forceinline__ void tile_store(R* p, const R* o) {
+    if constexpr (S == 4) {
+        store4(p, o);
+    } else if constexpr (S == 2) {
+        typedef R V2 __attribute__((ext_vector_type(2)));
+        V2 d;
+        d.x = o[0];
+        d.y = o[1];
+        *reinterpret_cast<V2*>(p) = d;
+    } else {
+        *p = o[0];
+    }
+}
+
+// The value of lane J of the lane's group of P lanes (P = 2 or 4, a Philox
+// block's lanes), by DPP.
+template <int P, int J, typename R>
+__device__ __forceinline__ R group_lane(R x) {
+    constexpr int ctrl = P == 4 ? J * 0x55 : (J | (J << 2) | ((2 + J) << 4) | ((2 + J) << 6));
+    if constexpr (sizeof(R) == 4)
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, false));
+    else
+        return dpp_f64<ctrl>(x);
+}
+
+template <typename R, int M, bool F, int S>
+__device__ __forceinline__ void tile_run(const Lat<R>& v, const TileIO<R>& io, const TileBox& b, int T, uint64_t k,
+                                         R* lds, R* coef) {
+    constexpr bool kPair = sizeof(R) == 8 && S == 2;       // each lane draws its own pair in every step
+    constexpr int P = kPair ? 1 : 4 / S;                   // lanes that share the draws of their block
+    const int Lx = v.Lx, Ly = v.Ly;
+    const bool px = b.w == Lx, py = b.h == Ly;             // the region is periodic along the axis
+    const int hx = px ? 0 : (T + 3) / 4 * 4, hy = py ? 0 : T;
+    const int W = b.w + 2 * hx, H = b.h + 2 * hy;
+    const int Wq = W / S, nq = Wq * H;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const bool in = tid < nq;
+    const int g = in ? tid : nq - P + (tid & (P - 1));
+    const int y = g / Wq, xq = g - y * Wq;
+    int gy = b.y0 - hy + y, gx = b.x0 - hx + S * xq;
+    gy = gy < 0 ? gy + Ly : (gy >= Ly ? gy - Ly : gy);
+    gx = gx < 0 ? gx + Lx : (gx >= Lx ? gx - Lx : gx);
+    const uint32_t off = (uint32_t)gy * (uint32_t)Lx + (uint32_t)gx;
+    const uint32_t q = off >> 2;
+    const int part = tid & (P - 1);                        // the lane's place in its block
+    // table slots of the group and of its neighbours (the region's outer ring
+    // of a non-periodic axis has none: its values are never used)
+    const int i0 = S * g;
+    const int iu = y == 0 ? (py ? i0 + (H - 1) * W : i0) : i0 - W;
+    const int id = y == H - 1 ? (py ? i0 - (H - 1) * W : i0) : i0 + W;
+    const int il = xq == 0 ? (px ? i0 + W - 1 : i0) : i0 - 1;
+    const int ir = xq == Wq - 1 ? (px ? i0 + S - W : i0) : i0 + S;
+    const bool edge_l = lane == 0 || (xq == 0 && px), edge_r = lane == kWave - 1 || (xq == Wq - 1 && px);
+    // steps the group's sites stay valid for: the distance of its innermost
+    // site from the region's edge
+    int dist = T;
+    if (!py) dist = min(dist, min(y, H - 1 - y));
+    if (!px) dist = min(dist, min(S * xq + S - 1, W - 1 - S * xq));
+    if (!in) dist = 0;
+    R th[S], u[S], s[S], c[S];
+    tile_load<R, S>(io.th_in + off, th);
+    tile_load<R, S>(io.u_in + off, u);
+    // the steps' noise amplitudes, while the loads are under way
+    for (int j = tid; j < T; j += (int)blockDim.x) coef[j] = noise_coeff<R, F>(v, k + (uint64_t)j);
+    const int tab = 2 * W * H;
+#pragma unroll
+    for (int e = 0; e < S; ++e) rotor<R, M>(th[e], s[e], c[e]);
+    if (in) {
+        tile_store<R, S>(lds + i0, s);
+        tile_store<R, S>(lds + W * H + i0, c);
+    }
+    __syncthreads();
+    // a block's lanes take the draws of P successive steps, one step each
+    R d[4];
+    auto draw = [&](int t) {
+        const uint64_t kt = k + (uint64_t)(t + part);
+        const R hs = coef[min(t + part, T - 1)];
+        if constexpr (kPair) {
+            const U32x4 r = philox4x32_10(q, v.replica, (uint32_t)kt, (uint32_t)(kt >> 32), v.seed_lo, v.seed_hi);
+            const bool hi = (off & 2) != 0;
+            Prec<R>::box_muller(hi ? r.v[2] : r.v[0], hi ? r.v[3] : r.v[1], d[0], d[1]);
+            return;
+        }
+        if constexpr (sizeof(R) == 4) noise4_kick<R>(q, v.replica, kt, v.seed_lo, v.seed_hi, hs, d, noise_u2<R, F>(v));
+        else noise4<R>(q, v.replica, kt, v.seed_lo, v.seed_hi, d);
+    };
+    auto step = [&](auto sub, int t) {
+        constexpr int J = decltype(sub)::value;
+        const uint64_t kt = k + (uint64_t)t;
+        const bool act = t < dist;
+        if constexpr (J == 0) {
+            if (P > 1 || act) draw(t);
+        }
+        if (t) __syncthreads();
+        const R* St = lds + (t & 1) * tab;
+        const R* Ct = St + W * H;
+        // (the DPP moves run with every lane of the wave enabled)
+        R sL = from_lane_below(s[S - 1]), cL = from_lane_below(c[S - 1]);
+        R sR = from_lane_above(s[0]), cR = from_lane_above(c[0]);
+        R su[S], cu[S], sd[S], cd[S];
+        tile_load<R, S>(St + iu, su);
+        tile_load<R, S>(Ct + iu, cu);
+        tile_load<R, S>(St + id, sd);
+        tile_load<R, S>(Ct + id, cd);
+        if (edge_l) {
+            sL = St[il];
+            cL = Ct[il];
+        }
+        if (edge_r) {
+            sR = St[ir];
+            cR = Ct[ir];
+        }
+        R n[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+            if constexpr (P == 1) {
+                n[e] = d[e];
+            } else {
+                n[e] = group_lane<P, J>(d[e]);
+#pragma unroll
+                for (int l = 1; l < P; ++l) {
+                    const R o = group_lane<P, J>(d[l * S + e]);
+                    n[e] = part == l ? o : n[e];
+                }
+            }
+        }
+        if (act) {
+            const bool fresh = kt == v.fresh_k;
+            const R hs = coef[t];
+#pragma unroll
+            for (int e = 0; e < S; ++e) {
+                const R sxm = e == 0 ? sL : s[e - 1], cxm = e == 0 ? cL : c[e - 1];
+                const R sxp = e == S - 1 ? sR : s[e + 1], cxp = e == S - 1 ? cR : c[e + 1];
+                const R f = site_force<R, M, F>(v, s[e], c[e], sxm, cxm, sxp, cxp, su[e], cu[e], sd[e], cd[e], th[e],
+                                                n[e]);
+                R w;
+                site_update<R, M, F>(v, f, u[e], th[e], n[e], hs, fresh, w, u[e], th[e]);
+            }
+            if (t + 1 < T) {
+                R* Sn = lds + ((t + 1) & 1) * tab;
+#pragma unroll
+                for (int e = 0; e < S; ++e) rotor<R, M>(th[e], s[e], c[e]);
+                tile_store<R, S>(Sn + i0, s);
+                tile_store<R, S>(Sn + W * H + i0, c);
+            }
+        }
+    };
+    for (int t = 0; t < T; t += P) {
+        step(std::integral_constant<int, 0>{}, t);
+        if constexpr (P >= 2) {
+            if (t + 1 < T) step(std::integral_constant<int, 1>{}, t + 1);
+        }
+        if constexpr (P == 4) {
+            if (t + 2 < T) step(std::integral_constant<int, 2>{}, t + 2);
+            if (t + 3 < T) step(std::integral_constant<int, 3>{}, t + 3);
+        }
+    }
+    const bool own = in && y >= hy && y < hy + b.h && S * xq >= hx && S * xq < hx + b.w;
+    if (own) {
+        tile_store<R, S>(io.th_out + off, th);
+        tile_store<R, S>(io.u_out + off, u);
+    }
+}
+
+// Tile t of n equal parts of L (in units of S): [t L/S/n, (t + 1) L/S/n) S.
+__device__ __forceinline__ TileBox tile_box(int tx, int ty, int ntx, int nty, int Lx, int Ly) {
+    constexpr int S = kLaneSites;
+    const int nqx = Lx / S;
+    TileBox b;
+    const int xa = (int)((long)tx * nqx / ntx), xb = (int)((long)(tx + 1) * nqx / ntx);
+    const int ya = (int)((long)ty * Ly / nty), yb = (int)((long)(ty + 1) * Ly / nty);
+    b.x0 = xa * S;
+    b.w = (xb - xa) * S;
+    b.y0 = ya;
+    b.h = yb - ya;
+    return b;
+}
+
+template <typename R, int M, bool F, int S, int NT>
+__global__ __launch_bounds__(NT) void k_tile(Lat<R> v, TileIO<R> io, int ntx, int nty, int T, uint64_t k) {
+    extern __shared__ double2 tile_lds_mem[];
+    __shared__ R coef[kTileMaxSteps];
+    const int b = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    const int ty = b / ntx, tx = b - ty * ntx;
+    tile_run<R, M, F, S>(v, io, tile_box(tx, ty, ntx, nty, v.Lx, v.Ly), T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
+}
+
+// Cost model of one launch of T steps, in us: a fixed part (dispatch, the
+// first loads, the stores), a part per wave of the busiest CU (its prologue),
+// and per step the larger of the latency of one wave's step and the issue
+// time of the busiest CU's resident waves, combined as
+// sqrt(lat^2 + (issue x)^2) with x the waves per SIMD; workgroups beyond what
+// a CU holds at once run in further rounds.  Rows of the region whose last
+// valid step has passed drop out wave by wave, so x counts them about half.
+struct TileCost {
+    int S;
+    double fixed, prologue, lat, issue;
+    int max_waves;            // waves per CU by registers
+};
+
+bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us) {
+    static const TileCost cost32[] = {{4, 2.75, 0.25, 0.60, 0.317, 32}, {2, 2.75, 0.15, 0.45, 0.22, 32}};
+    static const TileCost cost64[] = {{2, 3.0, 0.5, 1.40, 1.05, 16}, {1, 3.0, 0.3, 0.85, 0.65, 12}};
+    if (Lx % kLaneSites != 0 || n < 2) return false;
+    const size_t es = f64 ? 8 : 4;
+    const int quads = Lx / kLaneSites;
+    double best = 1e30;
+    for (const TileCost& c : f64 ? cost64 : cost32) {
+        for (int T = 2; T <= 12; ++T) {
+            const uint64_t nl = tile_launches(n, T);
+            const int t = (int)((n + nl - 1) / nl);      // the longest launch's steps
+            if (t < T && T > 2) continue;                // the same as a smaller T
+            if (t > Lx || t > Ly) continue;
+            int last_w = 0;
+            for (int ntx = 1; ntx <= quads && ntx <= 256; ++ntx) {
+                const int w = tile_max_w(Lx, ntx);
+                if (w == last_w) continue;               // more tiles of the same width
+                last_w = w;
+                const int W = tile_region_w(Lx, w, t);
+                if (W != Lx && (W - w) / 2 > Lx) continue;
+                for (int per = 1; per <= 64; per = per < 4 ? per + 1 : per * 2) {
+                    const int nty = std::min(Ly, std::max(1, per * cus / ntx));
+                    const int h = tile_max_h(Ly, nty), H = tile_region_h(Ly, h, t);
+                    const long lanes = (long)(W / c.S) * H;
+                    if (lanes > kTileMaxThreads) continue;
+                    const size_t lds = 4 * es * (size_t)W * H;
+                    if (lds > (size_t)kTileMaxLds) continue;
+                    const int waves = (int)((lanes + kWave - 1) / kWave);
+                    const int wgs = (ntx * nty + cus - 1) / cus;
+                    const int fit = std::max(1, std::min((int)(160 * 1024 / lds), c.max_waves / waves));
+                    const int rounds = (wgs + fit - 1) / fit;
+                    const double alive = H == Ly ? 1.0 : 0.5 + 0.5 * (double)std::max(0, H - t - 1) / H;
+                    double step = 0.0;
+                    for (int r = 0, left = wgs; r < rounds; ++r, left -= fit) {
+                        const double x = 0.25 * waves * std::min(left, fit) * alive;
+                        step += std::sqrt(c.lat * c.lat + c.issue * c.issue * x * x);
+                    }
+                    const double total = ((double)nl * (c.fixed + c.prologue * 0.25 * waves * wgs) + (double)n * step) / (double)n;
+                    if (total < best) {
+                        best = total;
+                        plan->ntx = ntx;
+                        plan->nty = nty;
+                        plan->T = t;
+                        plan->S = c.S;
+                        plan->threads = waves * kWave;
+                    }
+                }
+            }
+        }
+    }
+    if (us) *us = best;
+    return best < 1e30;
+}
+
+template <typename K>
+static void allow_tile_lds(K* kernel) {
+    static std::mutex mu;
+    static std::set<std::pair<int, const void*>> allowed;
+    int dev = 0;
+    check_hip(hipGetDevice(&dev), "hipGetDevice");
+    std::lock_guard<std::mutex> lk(mu);
+    const auto key = std::make_pair(dev, reinterpret_cast<const void*>(kernel));
+    if (allowed.count(key)) return;
+    check_hip(hipFuncSetAttribute(key.second, hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds),
+              "hipFuncSetAttribute");
+    allowed.insert(key);
+}
+
+template <typename R, int M, bool F, int S, int NT>
+static void launch_tile_nt(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
+                           hipStream_t s) {
+    allow_tile_lds(k_tile<R, M, F, S, NT>);
+    k_tile<R, M, F, S, NT><<<p.ntx * p.nty, p.threads, lds, s>>>(v, io, p.ntx, p.nty, T, k);
+    check_hip(hipGetLastError(), "tile kernel launch");
+}
+
+template <typename R, int M, bool F, int S>
+static void launch_tile_s(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
+                          hipStream_t s) {
+    if (p.threads <= 512) launch_tile_nt<R, M, F, S, 512>(v, io, p, T, lds, k, s);
+    else launch_tile_nt<R, M, F, S, 1024>(v, io, p, T, lds, k, s);
+}
+
+template <typename R, int M, bool F>
+static void launch_tile_m(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
+                          hipStream_t s) {
+    if constexpr (sizeof(R) == 4) {
+        if (p.S == 4) {
+            launch_tile_s<R, M, F, 4>(v, io, p, T, lds, k, s);
+            return;
+        }
+    }
+    if (p.S == 2) launch_tile_s<R, M, F, 2>(v, io, p, T, lds, k, s);
+    else launch_tile_s<R, M, F, 1>(v, io, p, T, lds, k, s);
+}
+
+template <typename R>
+void launch_tile(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, const TilePlan& p, int T,
+                 uint64_t k, hipStream_t s) {
+    const int wmax = tile_max_w(v.Lx, p.ntx), hmax = tile_max_h(v.Ly, p.nty);
+    const int W = tile_region_w(v.Lx, wmax, T), H = tile_region_h(v.Ly, hmax, T);
+    const size_t lds = tile_lds<R>(W, H);
+    if (T < 1 || T > kTileMaxSteps || p.ntx < 1 || p.nty < 1 || p.ntx > v.Lx / 4 || p.nty > v.Ly ||
+        !(p.S == 1 || p.S == 2 || (p.S == 4 && sizeof(R) == 4)) || (W / p.S) * H > p.threads ||
+        p.threads > kTileMaxThreads || p.threads % kWave != 0 || lds > kTileMaxLds ||
+        (W != v.Lx && (W - wmax) / 2 > v.Lx) || (H != v.Ly && T > v.Ly))
+        throw Error(-5, "tile launch: shape not supported");
+    const TileIO<R> io{th_in, u_in, th_out, u_out};
+    if constexpr (sizeof(R) == 4) {
+        if (v.model == kModelSI) {
+            if (v.fact) launch_tile_m<R, kModelSI, true>(v, io, p, T, lds, k, s);
+            else launch_tile_m<R, kModelSI, false>(v, io, p, T, lds, k, s);
+        } else {
+            if (v.fact) launch_tile_m<R, kModelXY, true>(v, io, p, T, lds, k, s);
+            else launch_tile_m<R, kModelXY, false>(v, io, p, T, lds, k, s);
+        }
+    } else {
+        if (v.model == kModelSI) launch_tile_m<R, kModelSI, false>(v, io, p, T, lds, k, s);
+        else launch_tile_m<R, kModelXY, false>(v, io, p, T, lds, k, s);
+    }
+}
+
+template void launch_tile<float>(const Lat<float>&, const float*, const float*, float*, float*, const TilePlan&, int,
+                                 uint64_t, hipStream_t);
+template void launch_tile<double>(const Lat<double>&, const double*, const double*, double*, double*, const TilePlan&,
+                                  int, uint64_t, hipStream_t);
+
+}  // namespace xyl

@@ -1,0 +1,77 @@
+"""Several steps per launch on tiles (lattices below the size rule) against
+single steps: the states must be bitwise identical, at the edges of the tiles'
+shapes, for both precisions and models and both forms of the FP32 kick."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2409_06412_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def run(xyl, spec, dtype, fusion, steps, every=0, state=None):
+    lat = xyl.Lattice(spec.Lx, spec.Ly, dtype=dtype, schedule=spec.schedule, seed=spec.seed, replica=spec.replica,
+                      **spec.params())
+    lat.set_fusion(fusion)
+    if state is None:
+        lat.init_random()
+    else:
+        lat.set_state(*state)
+    samples = []
+    for n in steps:
+        if every:
+            samples.append(lat.step_measured(n, every))
+        else:
+            lat.step(n)
+    out = lat.get_raw_state()
+    lat.close()
+    return out, samples
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("Lx,Ly,model,Jx,steps", [
+    (4, 2, "xy", 1.0, [2, 3, 20]),            # the smallest lattice: one quad per row, two rows
+    (8, 3, "si", -10.0, [5, 12]),             # halos that wrap onto the tile itself
+    (4, 300, "xy", 1.0, [16]),                # one quad wide: whole-width tiles
+    (64, 64, "xy", 0.0, [7, 30]),             # the unfactored FP32 kick
+    (96, 96, "si", -10.0, [20, 1, 2]),        # short runs, each with a plan of its own
+    (36, 20, "xy", -1.0, [41]),               # ferromagnetic rows
+    (772, 501, "xy", 1.0, [26]),              # uneven tiles along both axes
+    (1000, 7, "si", 10.0, [18]),              # few rows
+    (20, 1000, "xy", 1.0, [33]),
+    (512, 512, "xy", 1.0, [100]),
+    (1024, 1024, "si", -10.0, [14]),          # the largest in FP64
+])
+def test_tiles_equal_single_steps(xyl, dtype, Lx, Ly, model, Jx, steps):
+    say("tiles", dtype, Lx, Ly, model, Jx, steps)
+    base = workloads.si_lattice(Lx, Ly, seed=5, replica=3) if model == "si" else \
+        workloads.LatticeSpec(Lx, Ly, schedule=((0, 0.9), (20, 0.2, 2)), seed=5, replica=3)
+    base.Jx = Jx
+    a, _ = run(xyl, base, dtype, 1, steps)
+    b, _ = run(xyl, base, dtype, 2, steps)
+    assert a[2] == b[2] == sum(steps) and a[3] == b[3]
+    np.testing.assert_array_equal(a[0], b[0])
+    np.testing.assert_array_equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_tiles_between_samples_and_from_a_fresh_velocity(xyl, dtype):
+    """Samples at every 1, 7 and 20 steps and a start with velocities at a late
+    step: the same samples and states as single steps, bit for bit."""
+    spec = workloads.LatticeSpec(128, 60, schedule=((0, 0.9), (1 << 33, 0.2)), seed=2, replica=1)
+    rng = np.random.default_rng(4)
+    state = (rng.uniform(-3, 3, (60, 128)).astype(np.float32), rng.normal(0, 1, (60, 128)).astype(np.float32),
+             (1 << 32) - 9)
+    for every in (1, 7, 20):
+        a, sa = run(xyl, spec, dtype, 1, [20, 23], every, state)
+        b, sb = run(xyl, spec, dtype, 2, [20, 23], every, state)
+        np.testing.assert_array_equal(a[0], b[0])
+        np.testing.assert_array_equal(a[1], b[1])
+        for x, y in zip(sa, sb):
+            np.testing.assert_array_equal(x, y)
