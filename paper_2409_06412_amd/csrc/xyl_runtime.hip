@@ -1939,7 +1939,21 @@ struct xyl_ensemble {
     DevBuf<char> reps;              // Lat<R>[n]
     DevBuf<Task> tasks;
     int ntasks = 0;
-    std::vector<int> task_active;   // replica ids the task list was built for
+    // replica ids the tables were built for (every replica that steps), and
+    // those of them that the strip kernels measure (not the LDS path's)
+    std::vector<int> task_active, task_meas;
+    // tasks: [0, ntasks_flat) stepped by two-step classes or tile-table steps,
+    // [ntasks_flat, ntasks) on tiles; [0, ntasks_meas) those of task_meas
+    int ntasks_flat = 0, ntasks_meas = 0;
+    // replicas that take several steps per launch on tiles (xyl_tile.hip)
+    TilePlan tile_shape;            // T = 0: none
+    size_t tile_lds = 0;
+    DevBuf<TileTask> tiles;
+    int ntiles = 0;
+    bool tiles_ok = true;           // false: no memory for the second velocity buffer
+    std::vector<char> tiled;        // per replica: on tiles (one of the LDS path then only measures in LDS)
+    // groups of replicas stepped in parallel: the two-step classes, the tiles
+    size_t groups() const { return s2cls.size() + (ntiles ? 1 : 0); }
     DevBuf<double> part;
     DevBuf<double> phases;                  // measurement phase tables, one per side length
     std::map<int, size_t> phase_off;        // side length -> offset of its table in phases
@@ -2068,19 +2082,230 @@ struct xyl_ensemble {
     int model() const { return desc[0].model; }
 };
 
+static bool replica_factored(const xyl_replica_desc& d) {
+    return kick_factored(Params{d.Jx, d.Jy, d.h, d.gamma, d.dt, d.model, d.p});
+}
+
+// Strips of a two-step class as tall as keep at least two waves per SIMD busy
+// (2 to 32 rows; 32 for the 60 x 2048^2 quench batch: 5.83 -> 5.98e11
+// site-updates/s against 16, 5.86e11 with 64).  Rows of more than 8 waves hold
+// one workgroup per CU and go to 64 (eight 4096^2 replicas: 6.05 -> 6.19e11).
+static int class_rows(const xyl_ensemble* e, int waves, const std::vector<int>& reps, long* strips_o) {
+    for (int rows = waves > 8 ? 64 : 32; rows >= 2; rows /= 2) {
+        long strips = 0;
+        for (int r : reps) strips += (e->desc[r].Ly + rows - 1) / rows;
+        *strips_o = strips;
+        if (strips * waves >= 8L * e->cus || rows == 2) return rows;
+    }
+    return 2;
+}
+
+// How the active replicas step with two steps per pass on: which go on tiles,
+// by the paths' times per step.
+//   * Two-step classes: step2_us's form over the class's strips, times 1.15
+//     (1-wave class of 192^2 and 256^2 replicas, 32 each: 10.3 us per step
+//     measured; 2-wave class of 384^2 and 512^2: 25.5); parallel groups
+//     together 0.9 of their sum.
+//   * Whole in LDS: the largest replica's step on its one CU, 4.5 us for 128^2
+//     (5.6 Si), beside the other replicas on a stream of its own, whose issue
+//     it shares.  128 Si replicas of 32^2 to 144^2: the LDS launches took 5.6
+//     us per step and the 144^2 ones 16 in single tile-table steps; on tiles
+//     all of them take about 3.
+//   * Other widths: single tile-table steps, lattice_untiled_us's form.
+//   * Tiles: TileFits::best.
+// Sets e->tile_shape (T = 0: no tiles) and on_tiles[r], and returns the tiles
+// of each distinct size.  Another split than none is taken only where it gains
+// 5%.
+static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ensemble* e, const std::vector<int>& active,
+                                                                       uint64_t n, std::vector<char>& on_tiles) {
+    std::map<std::pair<int, int>, std::pair<int, int>> out;
+    on_tiles.assign(e->n, 0);
+    e->tile_shape = TilePlan();
+    e->tile_lds = 0;
+    if (e->fusion != 2 || n < 4 || !e->tiles_ok) return out;
+    const bool f64 = e->dtype == XYL_F64;
+    // units that step on tiles or not: 0 the LDS replicas, 1..16 the two-step
+    // classes, 17 the others
+    constexpr int kUnits = 18;
+    std::vector<std::vector<int>> unit(kUnits);
+    std::vector<char> fixed(kUnits, 0);
+    double lds_fixed_sites = 0.0;
+    for (int r : active) {
+        const xyl_replica_desc& d = e->desc[r];
+        const bool fact = f64 || replica_factored(d);
+        const bool fits = fact && d.Lx <= 16 * kWaveSites && (size_t)d.Lx * d.Ly <= (size_t(1) << 24);
+        if (!fits && e->lds[r]) lds_fixed_sites += (double)d.Lx * d.Ly;
+        if (!fits) continue;
+        if (e->lds[r]) unit[0].push_back(r);
+        else if (!f64 && step2_shape(d.Lx, d.Ly)) unit[(d.Lx + kWaveSites - 1) / kWaveSites].push_back(r);
+        else unit[17].push_back(r);
+    }
+    std::vector<int> used;
+    std::vector<double> flat_us(kUnits, 0.0);
+    double lds_sites = lds_fixed_sites, full_us = 0.0;
+    int full = 0;              // classes that fill the chip
+    for (int q = 0; q < kUnits; ++q) {
+        if (unit[q].empty()) continue;
+        if (q == 0) {
+            int nmax = 0;
+            for (int r : unit[0]) {
+                const int N = e->desc[r].Lx * e->desc[r].Ly;
+                lds_sites += N;
+                nmax = std::max(nmax, N);
+            }
+            const int fit = std::max(1, std::min(32 / (e->lds_threads / kWave), 160 * 1024 / (8 * e->lds_max_sites)));
+            int left = (int)((unit[0].size() + e->cus - 1) / e->cus);
+            for (; left > 0; left -= fit) {
+                const double x = 0.3 * (nmax / 1024.0) * std::min(left, fit);
+                flat_us[0] += std::sqrt(1.44 + x * x);
+            }
+        } else if (q <= 16) {
+            long strips = 0;
+            int max_lx = 0;
+            for (int r : unit[q]) max_lx = std::max(max_lx, e->desc[r].Lx);
+            const int rows = class_rows(e, q, unit[q], &strips);
+            const int fit = std::max(1, std::min(16 / q, (160 * 1024) / (32 * max_lx)));
+            double us = 3.0;
+            for (long left = (strips + e->cus - 1) / e->cus; left > 0; left -= fit) {
+                const double x = 0.6 * 0.25 * q * (double)std::min<long>(left, fit);
+                us += (rows + 2) * std::sqrt(1.0 + x * x);
+            }
+            flat_us[q] = 1.15 * 0.5 * us;
+            // tiles reach 4.6e5 sites per us at best: a class that fills the
+            // chip stays as it is
+            double N = 0.0;
+            for (int r : unit[q]) N += (double)e->desc[r].Lx * e->desc[r].Ly;
+            if (N / flat_us[q] > 4.8e5) {
+                full_us += flat_us[q];
+                ++full;
+                continue;
+            }
+        } else {
+            double N = 0.0;
+            for (int r : unit[q]) N += (double)e->desc[r].Lx * e->desc[r].Ly;
+            flat_us[q] = f64 ? 6.5 + N / 1.0e5 : 3.3 + N / 3.7e5;
+        }
+        used.push_back(q);
+    }
+    if (used.empty()) return out;
+    std::vector<TileSize> sizes;
+    std::vector<int> size_of(e->n, -1);
+    for (int q : used)
+        for (int r : unit[q]) {
+            const int Lx = e->desc[r].Lx, Ly = e->desc[r].Ly;
+            size_t i = 0;
+            while (i < sizes.size() && (sizes[i].Lx != Lx || sizes[i].Ly != Ly)) ++i;
+            if (i == sizes.size()) {
+                TileSize z;
+                z.Lx = Lx;
+                z.Ly = Ly;
+                sizes.push_back(z);
+            }
+            size_of[r] = (int)i;
+        }
+    // (more than 6 units never occur in practice; the first ones are split then)
+    const int nu = std::min<int>((int)used.size(), 6);
+    const TileFits fits(sizes, f64, e->cus, n);
+    double best = 1e30;
+    unsigned pick = 0;
+    std::vector<long> pick_count;
+    for (unsigned m = 0; m < (1u << nu); ++m) {
+        std::vector<long> count(sizes.size(), 0);
+        double main_us = full_us, lds_us = 0.0, lds_share = lds_fixed_sites / 6.3e5, single_us = 0.0;
+        int groups = full;
+        for (size_t b = 0; b < used.size(); ++b) {
+            const int q = used[b];
+            if (b < (size_t)nu && (m >> b & 1u)) {
+                for (int r : unit[q]) count[size_of[r]] += 1;
+            } else if (q == 0) {
+                lds_us = flat_us[0];
+                lds_share = lds_sites / 6.3e5;
+            } else if (q <= 16) {
+                main_us += flat_us[q];
+                ++groups;
+            } else {
+                single_us += flat_us[q];
+            }
+        }
+        if (m) {
+            const double t = fits.best(count, nullptr, nullptr, nullptr);
+            if (t >= 1e30) continue;
+            main_us += t;
+            ++groups;
+        }
+        if (groups > 1) main_us *= 0.9;
+        main_us += single_us;
+        const double us = main_us > 0.0 ? std::max(lds_us, main_us + lds_share) : lds_us;
+        if (us < best * (m ? 0.95 : 1.0)) {
+            best = us;
+            pick = m;
+            pick_count = count;
+        }
+    }
+    if (!pick) return out;
+    std::vector<TileSize> tiles;
+    fits.best(pick_count, &e->tile_shape, &tiles, &e->tile_lds);
+    for (int b = 0; b < nu; ++b)
+        if (pick >> b & 1u)
+            for (int r : unit[used[b]]) on_tiles[r] = 1;
+    for (const TileSize& z : tiles)
+        if (z.ntx) out[{z.Lx, z.Ly}] = {z.ntx, z.nty};
+    return out;
+}
+
+// Tables for the steps of `active` replicas (LDS replicas among them), planned
+// for chunks of about n steps.
 template <typename R>
-static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<int>& active) {
+static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<int>& active, uint64_t n) {
+    // a replica may change between the streams
+    if (e->side) check_hip(hipStreamSynchronize(e->side), "hipStreamSynchronize");
     std::vector<Lat<R>> tab(e->n);
     for (int r = 0; r < e->n; ++r) tab[r] = e->view<R>(r, jbase);
     e->reps.reserve(sizeof(Lat<R>) * e->n);
     check_hip(hipMemcpyAsync(e->reps.p, tab.data(), sizeof(Lat<R>) * e->n, hipMemcpyHostToDevice, e->stream), "H2D");
+    auto box = ens_plan_tiles(e, active, n, e->tiled);
+    if (!box.empty()) {
+        // where the second velocity buffer does not fit, the other paths do
+        // (the classes, which need it too, report that)
+        try {
+            e->u2.reserve(sizeof(R) * e->total);
+        } catch (const Error& err) {
+            if (err.code != XYL_ENOMEM) throw;
+            (void)hipGetLastError();
+            e->tiles_ok = false;
+            box = ens_plan_tiles(e, active, n, e->tiled);
+        }
+    }
+    std::vector<TileTask> tt;
     std::vector<Task> tk;
-    for (int r : active) {
+    auto tile_rows = [&](int r) {
         const int nxw = (e->desc[r].Lx + kWaveSites - 1) / kWaveSites;
         const int nstrips = (e->desc[r].Ly + e->launch.rows - 1) / e->launch.rows;
         for (int s = 0; s < nstrips; ++s)
             for (int x = 0; x < nxw; ++x) tk.push_back(Task{r, x, s, 0});
-    }
+    };
+    e->task_meas.clear();
+    for (int r : active)
+        if (!e->lds[r]) {
+            e->task_meas.push_back(r);
+            if (!e->tiled[r]) tile_rows(r);
+        }
+    e->ntasks_flat = (int)tk.size();
+    for (int r : active)
+        if (!e->lds[r] && e->tiled[r]) tile_rows(r);
+    e->ntasks_meas = (int)tk.size();
+    for (int r : active)
+        if (e->lds[r] && e->tiled[r]) tile_rows(r);
+    for (int r : active)
+        if (e->tiled[r]) {
+            const auto& b = box.at({e->desc[r].Lx, e->desc[r].Ly});
+            tile_tasks(r, e->desc[r].Lx, e->desc[r].Ly, b.first, b.second, &tt);
+        }
+    e->ntiles = (int)tt.size();
+    e->tiles.reserve(std::max<size_t>(tt.size(), 1));
+    if (!tt.empty())
+        check_hip(hipMemcpyAsync(e->tiles.p, tt.data(), sizeof(TileTask) * tt.size(), hipMemcpyHostToDevice, e->stream),
+                  "H2D");
     e->ntasks = (int)tk.size();
     e->tasks.reserve(std::max<size_t>(tk.size(), 1));
     if (!tk.empty())
@@ -2091,11 +2316,13 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
     std::vector<std::vector<Task2>> t2(17);
     std::vector<Task> rest;
     e->s2cls.clear();
+    e->ntasks_rest = 0;
     if (e->dtype == XYL_F32 && e->fusion == 2) {
         std::vector<std::vector<int>> byw(17);
         for (int r : active) {
+            if (e->lds[r] || e->tiled[r]) continue;
             const xyl_replica_desc& d = e->desc[r];
-            if (step2_shape(d.Lx, d.Ly) && kick_factored(Params{d.Jx, d.Jy, d.h, d.gamma, d.dt, d.model, d.p}))
+            if (step2_shape(d.Lx, d.Ly) && replica_factored(d))
                 byw[(d.Lx + kWaveSites - 1) / kWaveSites].push_back(r);
             else
                 for (const Task& t : tk)
@@ -2105,20 +2332,8 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
             if (byw[w].empty()) continue;
             xyl_ensemble::Step2Class cl;
             cl.waves = w;
-            // strips as tall as keep at least two waves per SIMD busy (2 to 32
-            // rows; 32 for the 60 x 2048^2 quench batch: 5.83 -> 5.98e11
-            // site-updates/s against 16, 5.86e11 with 64).  Rows of more than
-            // 8 waves hold one workgroup per CU and go to 64 (eight 4096^2
-            // replicas: 6.05 -> 6.19e11)
-            cl.rows = 2;
-            for (int rows = w > 8 ? 64 : 32; rows >= 2; rows /= 2) {
-                long strips = 0;
-                for (int r : byw[w]) strips += (e->desc[r].Ly + rows - 1) / rows;
-                if (strips * w >= 8L * e->cus) {
-                    cl.rows = rows;
-                    break;
-                }
-            }
+            long strips = 0;
+            cl.rows = class_rows(e, w, byw[w], &strips);
             for (int r : byw[w]) {
                 const xyl_replica_desc& d = e->desc[r];
                 cl.partial = cl.partial || d.Lx % kWaveSites != 0;
@@ -2140,11 +2355,11 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
                                      e->stream),
                       "H2D");
     }
-    // the second velocity buffer and the class streams now, not in the first
-    // chunk that steps through the classes
-    if (!e->s2cls.empty()) {
-        e->u2.reserve(sizeof(float) * e->total);
-        e->class_streams(e->s2cls.size());
+    // the second velocity buffer and the group streams now, not in the first
+    // chunk that steps through the groups
+    if (e->groups()) {
+        e->u2.reserve(sizeof(R) * e->total);
+        e->class_streams(e->groups());
     }
     // the host vectors must outlive the copies
     check_hip(hipStreamSynchronize(e->stream), "hipStreamSynchronize");
@@ -2270,8 +2485,10 @@ static void ens_step_per_replica(xyl_ensemble* e, uint64_t nsteps, EnsSamples& s
 // or end of any of them form a chunk; large replicas advance through one
 // tile-table launch per step (after the chunk's first step, runs of 4m steps
 // as batched two-step passes for the FP32 replicas whose width that pass
-// takes), small FP32 replicas through one whole-in-LDS launch per chunk on a
-// second stream.
+// takes, or several steps per launch on tiles where ens_plan_tiles finds that
+// faster), small FP32 replicas through one whole-in-LDS launch per chunk on a
+// second stream, or on tiles too; those are still measured in LDS, so a
+// sample's sums do not depend on the path.
 template <typename R>
 static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) {
     std::vector<FinalizeJobHost> jobs;
@@ -2282,22 +2499,14 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
     }
     uint64_t it = 0;
     while (true) {
-        std::vector<int> active_g, meas_g, only_meas_g, lds_set;
+        std::vector<int> active, meas_g, only_meas_g, lds_set;
         std::vector<char> meas(e->n, 0), act(e->n, 0);
         bool any = false;
         for (int r = 0; r < e->n; ++r) {
             meas[r] = smp.wants(r);
             act[r] = it < nsteps && e->k[r] < e->desc[r].nsteps;
-            if (!meas[r] && !act[r]) continue;
-            any = true;
-            if (e->lds[r]) {
-                lds_set.push_back(r);
-            } else if (act[r]) {
-                active_g.push_back(r);
-                if (meas[r]) meas_g.push_back(r);
-            } else {
-                only_meas_g.push_back(r);
-            }
+            any = any || meas[r] || act[r];
+            if (act[r]) active.push_back(r);
         }
         if (!any) break;
         uint64_t chunk = 0;
@@ -2309,9 +2518,30 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
             chunk = any_active ? std::min(chunk, c) : c;
             any_active = true;
         }
+        if (!active.empty() && (active != e->task_active || e->tables_fusion != e->fusion))
+            ens_upload_table<R>(e, e->j, active, chunk);
+        bool step_g = false;   // replicas that step on the ensemble's stream and its class streams
+        for (int r : active) step_g = step_g || !e->lds[r] || e->tiled[r];
+        for (int r = 0; r < e->n; ++r) {
+            if (!e->lds[r]) {
+                if (meas[r]) (act[r] ? meas_g : only_meas_g).push_back(r);
+            } else if (meas[r] || (act[r] && !e->tiled[r])) {
+                lds_set.push_back(r);
+            }
+        }
         size_t nmeas = 0;
         for (int r = 0; r < e->n; ++r) nmeas += meas[r];
         smp.reserve(nmeas);
+        // replicas on tiles that are measured in LDS: the sample reads the
+        // state the tiles have stepped to, and their next launch that writes
+        // over it waits for the sample
+        hipEvent_t lds_sample = nullptr;
+        bool lds_from_tiles = false;
+        for (int r : lds_set) lds_from_tiles = lds_from_tiles || (meas[r] && !e->tiled.empty() && e->tiled[r]);
+        if (lds_from_tiles) {
+            check_hip(hipEventRecord(e->ev_main, e->stream), "hipEventRecord");
+            check_hip(hipStreamWaitEvent(e->side, e->ev_main, 0), "hipStreamWaitEvent");
+        }
         // small replicas: one launch for the whole chunk
         if (!lds_set.empty()) {
             // replicas with the factored FP32 kick first, then the others: one
@@ -2329,7 +2559,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                     const bool f = kick_factored(Params{d.Jx, d.Jy, d.h, d.gamma, d.dt, d.model, d.p});
                     if (f != (pass == 0)) continue;
                     nfact += f ? 1 : 0;
-                    jh.push_back(LdsJobHost{r, meas[r] ? 1 : 0, act[r] ? (int32_t)chunk : 0, 0,
+                    jh.push_back(LdsJobHost{r, meas[r] ? 1 : 0, act[r] && !e->tiled[r] ? (int32_t)chunk : 0, 0,
                                             meas[r] ? smp.take(r) : nullptr});
                 }
             // (pinned table b's last copy went with that launch, so it is free)
@@ -2354,119 +2584,148 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                                     e->lds_max_sites, e->model(), false, e->j, e->side);
             check_hip(hipEventRecord(e->ev_lds[b], e->side), "hipEventRecord");
             e->ev_lds_used[b] = true;
+            if (lds_from_tiles) lds_sample = e->ev_lds[b];
         }
-        // large replicas
-        if (!active_g.empty()) {
-            if (active_g != e->task_active || e->tables_fusion != e->fusion) ens_upload_table<R>(e, e->j, active_g);
+        // the replicas on the ensemble's stream
+        if (step_g) {
             const Lat<R>* reps = reinterpret_cast<const Lat<R>*>(e->reps.p);
+            const size_t ncls = e->s2cls.size(), groups = e->groups();
+            const R* ub = static_cast<const R*>(e->u);
+            R* u2b = reinterpret_cast<R*>(e->u2.p);
+            // group g (a class, or the tiles last) runs on the ensemble's
+            // stream (g = 0) or on a stream of its own
+            auto stream_of = [&](size_t g, hipStream_t main) { return g == 0 ? main : e->cls_streams[g - 1]; };
+            // launch i of nl of the tiles' n steps from step offset jb
+            auto tile_launch = [&](uint64_t i, uint64_t nl, uint64_t n, const uint64_t* kdev, uint64_t jb,
+                                   hipStream_t st) {
+                const uint64_t q = n / nl, m = n % nl, off = i * q + std::min(i, m);
+                launch_ensemble_tile<R>(reps, e->tiles.p, e->ntiles, e->tile_shape, e->tile_lds, e->model(),
+                                        (int)(q + (i < m ? 1 : 0)), (int)(i & 1), off, ub, u2b, kdev, jb + off, st);
+            };
+            // With groups the sample is a measurement without a step, and the
+            // whole chunk runs in passes and tile launches; otherwise (and in
+            // chunks too short for them) the chunk's first step carries it.
+            const bool passes = groups > 0 && chunk >= 4;
             uint64_t c = 0;
-            bool stepped = false;
-            bool preforked = false;   // the later classes' first pass already issued (below)
+            bool preforked = false;   // the later groups' first launch already issued (below)
             if (!meas_g.empty()) {
-                // FP32 with two-step classes: the sample is a measurement
-                // without a step, and the whole chunk runs in pairs of passes;
-                // otherwise the chunk's first step carries the measurement
-                bool passes = false;
-                if constexpr (std::is_same<R, float>::value) passes = !e->s2cls.empty() && chunk >= 4;
-                stepped = !passes;
-                if constexpr (std::is_same<R, float>::value) {
-                    // several classes issued directly: the classes after the
-                    // first start their first pass beside the measurement (it
-                    // reads the sampled state and writes the other buffers);
-                    // their second pass, which overwrites that state, waits
-                    // for the measurement's end
-                    const size_t ncls = e->s2cls.size();
-                    if (passes && ncls > 1 && e->use_graphs != 2) {
-                        e->class_streams(ncls);
-                        const float* ub = static_cast<const float*>(e->u);
-                        float* u2b = reinterpret_cast<float*>(e->u2.p);
-                        check_hip(hipEventRecord(e->cls_events[0], e->stream), "hipEventRecord");
-                        for (size_t c2 = 1; c2 < ncls; ++c2) {
-                            const auto& cl = e->s2cls[c2];
-                            check_hip(hipStreamWaitEvent(e->cls_streams[c2 - 1], e->cls_events[0], 0),
-                                      "hipStreamWaitEvent");
-                            launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial, cl.max_lx,
-                                                  e->model(), 0, ub, u2b, nullptr, e->j, e->cls_streams[c2 - 1]);
+                // several groups issued directly: the groups after the first
+                // start their first launch beside the measurement (it reads
+                // the sampled state and writes the other buffers); their
+                // second, which overwrites that state, waits for the
+                // measurement's end
+                if (passes && groups > 1 && e->use_graphs != 2) {
+                    check_hip(hipEventRecord(e->cls_events[0], e->stream), "hipEventRecord");
+                    for (size_t g = 1; g < groups; ++g) {
+                        hipStream_t st = stream_of(g, e->stream);
+                        check_hip(hipStreamWaitEvent(st, e->cls_events[0], 0), "hipStreamWaitEvent");
+                        if (g < ncls) {
+                            if constexpr (std::is_same<R, float>::value) {
+                                const auto& cl = e->s2cls[g];
+                                launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial, cl.max_lx,
+                                                      e->model(), 0, ub, u2b, nullptr, e->j, st);
+                            }
+                        } else {
+                            const uint64_t n2 = chunk / 2 * 2;
+                            tile_launch(0, tile_launches(n2, e->tile_shape.T), n2, nullptr, e->j, st);
                         }
-                        preforked = true;
                     }
+                    preforked = true;
                 }
-                launch_ensemble_step<R>(reps, e->tasks.p, e->ntasks, passes ? kMeasure : (kStore | kMeasure),
+                launch_ensemble_step<R>(reps, e->tasks.p, e->ntasks_meas, passes ? kMeasure : (kStore | kMeasure),
                                         e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
-                if (preforked)
-                    check_hip(hipEventRecord(e->cls_events[e->s2cls.size()], e->stream), "hipEventRecord");
+                if (preforked) check_hip(hipEventRecord(e->cls_events[groups], e->stream), "hipEventRecord");
                 for (int r : meas_g)
                     jobs.push_back(FinalizeJobHost{e->part.p + e->poff[r], e->nrp(r),
                                                    (double)e->desc[r].Lx * (double)e->desc[r].Ly, smp.take(r)});
                 flush_finalize(e, smp, jobs);
-                c = stepped ? 1 : 0;
+            }
+            if (!passes) {
+                if (lds_sample) check_hip(hipStreamWaitEvent(e->stream, lds_sample, 0), "hipStreamWaitEvent");
+                lds_sample = nullptr;
+                // (the tiles' replicas measured in LDS take that step here)
+                if (!meas_g.empty()) {
+                    if (e->ntasks > e->ntasks_meas)
+                        launch_ensemble_step<R>(reps, e->tasks.p + e->ntasks_meas, e->ntasks - e->ntasks_meas, kStore,
+                                                e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
+                    c = 1;
+                }
             }
             // steps c0 .. c0 + n - 1 of the chunk, step offsets jb + c (with
             // kdev, jb = 0 and the device counter holds e->j)
             auto issue = [&](uint64_t c0, uint64_t n, const uint64_t* kdev, uint64_t jb, hipStream_t main) {
-                uint64_t cc = c0;
-                if constexpr (std::is_same<R, float>::value) {
-                    const uint64_t n4 = n / 4 * 4;
-                    if (n4 && !e->s2cls.empty()) {
-                        e->u2.reserve(sizeof(float) * e->total);
-                        const float* ub = static_cast<const float*>(e->u);
-                        float* u2b = reinterpret_cast<float*>(e->u2.p);
-                        const size_t ncls = e->s2cls.size();
-                        e->class_streams(ncls);
-                        // with `preforked` (a direct chunk of several classes,
-                        // from its start), the later classes are forked and their
-                        // first pass issued; their second waits for the sample
-                        const bool pre = preforked && cc == 0 && kdev == nullptr;
-                        if (ncls > 1 && !pre) {
-                            check_hip(hipEventRecord(e->cls_events[0], main), "hipEventRecord");
-                            for (size_t c2 = 1; c2 < ncls; ++c2)
-                                check_hip(hipStreamWaitEvent(e->cls_streams[c2 - 1], e->cls_events[0], 0),
-                                          "hipStreamWaitEvent");
-                        }
-                        // pass by pass across the classes: issued class by class, a
-                        // class's first pass would wait for every pass of the
-                        // classes before it to be issued (in a replayed graph,
-                        // dispatched), and the classes would hardly overlap
-                        for (uint64_t i = 0; i < n4; i += 4)
-                            for (int ph = 0; ph < 2; ++ph)
-                                for (size_t c2 = 0; c2 < ncls; ++c2) {
-                                    const auto& cl = e->s2cls[c2];
-                                    hipStream_t st = c2 == 0 ? main : e->cls_streams[c2 - 1];
-                                    if (pre && c2 > 0 && i == 0) {
-                                        if (ph == 0) continue;   // issued before the sample
-                                        check_hip(hipStreamWaitEvent(st, e->cls_events[ncls], 0),
-                                                  "hipStreamWaitEvent");
-                                    }
-                                    launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial,
-                                                          cl.max_lx, e->model(), ph, ub, u2b, kdev,
-                                                          jb + cc + i + 2 * ph, st);
-                                }
-                        for (size_t c2 = 1; c2 < ncls; ++c2) {
-                            check_hip(hipEventRecord(e->cls_events[c2], e->cls_streams[c2 - 1]), "hipEventRecord");
-                            check_hip(hipStreamWaitEvent(main, e->cls_events[c2], 0), "hipStreamWaitEvent");
-                        }
-                        if (e->ntasks_rest)
-                            for (uint64_t i = 0; i < n4; ++i)
-                                launch_ensemble_step<R>(reps, e->tasks_rest.p, e->ntasks_rest, kStore, e->model(),
-                                                        e->launch.rows, e->launch.wpb, kdev, jb + cc + i, main);
-                        cc += n4;
+                // classes: 4m steps; tiles: an even number; the rest of the
+                // chunk in single tile-table steps
+                const uint64_t n4 = passes && ncls ? n / 4 * 4 : 0;
+                const uint64_t n2 = passes && e->ntiles ? n / 2 * 2 : 0;
+                if (n4 || n2) {
+                    // with `preforked` (a direct chunk of several groups, from
+                    // its start), the later groups are forked and their first
+                    // launch issued; their second waits for the sample
+                    const bool pre = preforked && c0 == 0 && kdev == nullptr;
+                    if (groups > 1 && !pre) {
+                        check_hip(hipEventRecord(e->cls_events[0], main), "hipEventRecord");
+                        for (size_t g = 1; g < groups; ++g)
+                            check_hip(hipStreamWaitEvent(stream_of(g, main), e->cls_events[0], 0), "hipStreamWaitEvent");
                     }
+                    // launch by launch across the groups: issued group by
+                    // group, a group's first launch would wait for every
+                    // launch of the groups before it to be issued (in a
+                    // replayed graph, dispatched), and the groups would hardly
+                    // overlap
+                    const uint64_t np = n4 / 2, nl = n2 ? tile_launches(n2, e->tile_shape.T) : 0;
+                    const uint64_t rounds = std::max(np, nl);
+                    uint64_t p = 0, l = 0;
+                    for (uint64_t r = 0; r < rounds; ++r) {
+                        for (; p * rounds < (r + 1) * np && p < np; ++p)
+                            for (size_t g = 0; g < ncls; ++g) {
+                                hipStream_t st = stream_of(g, main);
+                                if (pre && g > 0 && p <= 1) {
+                                    if (p == 0) continue;   // issued before the sample
+                                    check_hip(hipStreamWaitEvent(st, e->cls_events[groups], 0), "hipStreamWaitEvent");
+                                }
+                                if constexpr (std::is_same<R, float>::value) {
+                                    const auto& cl = e->s2cls[g];
+                                    launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial,
+                                                          cl.max_lx, e->model(), (int)(p & 1), ub, u2b, kdev,
+                                                          jb + c0 + 2 * p, st);
+                                }
+                            }
+                        for (; l * rounds < (r + 1) * nl && l < nl; ++l) {
+                            hipStream_t st = stream_of(groups - 1, main);
+                            if (pre && groups > 1 && l <= 1) {
+                                if (l == 0) continue;
+                                check_hip(hipStreamWaitEvent(st, e->cls_events[groups], 0), "hipStreamWaitEvent");
+                            }
+                            if (l == 1 && lds_sample && kdev == nullptr)
+                                check_hip(hipStreamWaitEvent(st, lds_sample, 0), "hipStreamWaitEvent");
+                            tile_launch(l, nl, n2, kdev, jb + c0, st);
+                        }
+                    }
+                    for (size_t g = 1; g < groups; ++g) {
+                        check_hip(hipEventRecord(e->cls_events[g], e->cls_streams[g - 1]), "hipEventRecord");
+                        check_hip(hipStreamWaitEvent(main, e->cls_events[g], 0), "hipStreamWaitEvent");
+                    }
+                    if (n4 && e->ntasks_rest)
+                        for (uint64_t i = 0; i < n4; ++i)
+                            launch_ensemble_step<R>(reps, e->tasks_rest.p, e->ntasks_rest, kStore, e->model(),
+                                                    e->launch.rows, e->launch.wpb, kdev, jb + c0 + i, main);
                 }
-                for (; cc < c0 + n; ++cc)
-                    launch_ensemble_step<R>(reps, e->tasks.p, e->ntasks, kStore, e->model(), e->launch.rows,
-                                            e->launch.wpb, kdev, jb + cc, main);
+                // single steps: tasks [a, b), both sets where both have them left
+                for (uint64_t i = std::min(n4, n2); i < n; ++i) {
+                    const int a = i >= n4 ? 0 : e->ntasks_flat, b = i >= n2 ? e->ntasks : e->ntasks_flat;
+                    if (b > a)
+                        launch_ensemble_step<R>(reps, e->tasks.p + a, b - a, kStore, e->model(), e->launch.rows,
+                                                e->launch.wpb, kdev, jb + c0 + i, main);
+                }
             };
             const uint64_t n = chunk - c;
             // launches the chunk's stepping takes
             uint64_t nl = n;
-            if constexpr (std::is_same<R, float>::value)
-                if (!e->s2cls.empty()) nl = n / 4 * 2 * e->s2cls.size() + n % 4 + (e->ntasks_rest ? n / 4 * 4 : 0);
+            if (passes && ncls) nl = n / 4 * 2 * ncls + n % 4 + (e->ntasks_rest ? n / 4 * 4 : 0);
             xyl_ensemble::ChunkGraph* cg = nullptr;
-            bool graphs = e->use_graphs == 2;
-            if constexpr (std::is_same<R, float>::value)
-                graphs = graphs || (e->use_graphs == 1 && e->s2cls.size() <= 1);
-            else
-                graphs = graphs || e->use_graphs == 1;
+            // (tile launches are few and long enough to be issued directly)
+            const bool graphs = e->use_graphs == 2 || (e->use_graphs == 1 && groups <= 1 && e->ntiles == 0);
             if (graphs && nl >= 8) {
                 if (e->graphs_built_for != e->graph_version) {
                     e->drop_graphs();
@@ -2491,10 +2750,6 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                     if (!e->cap_stream)
                         check_hip(hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking), "hipStreamCreate");
                     e->kc.reserve(1);
-                    if (!e->s2cls.empty()) {
-                        e->u2.reserve(sizeof(float) * e->total);
-                        e->class_streams(e->s2cls.size());
-                    }
                     hipGraph_t gr = nullptr;
                     check_hip(hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal),
                               "hipStreamBeginCapture");
@@ -2512,6 +2767,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                 }
             }
             if (cg && cg->exec) {
+                if (lds_sample) check_hip(hipStreamWaitEvent(e->stream, lds_sample, 0), "hipStreamWaitEvent");
                 launch_set_counter(e->kc.p, e->j, e->stream);
                 check_hip(hipGraphLaunch(cg->exec, e->stream), "hipGraphLaunch");
             } else {
@@ -2522,9 +2778,9 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
         // one batched measurement over the task table when they are the
         // replicas it was built for (the same strips and sums as one launch
         // per replica, which took about 1 ms for the 288-replica ensemble)
-        const bool batched_only = !only_meas_g.empty() && only_meas_g == e->task_active && e->ntasks > 0;
+        const bool batched_only = !only_meas_g.empty() && only_meas_g == e->task_meas && e->ntasks_meas > 0;
         if (batched_only)
-            launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(e->reps.p), e->tasks.p, e->ntasks, kMeasure,
+            launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(e->reps.p), e->tasks.p, e->ntasks_meas, kMeasure,
                                     e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
         for (int r : only_meas_g) {
             if (!batched_only) {
@@ -2642,9 +2898,9 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
         const Launch launch0 = e->launch;
         e->launch = best;
         e->fusion = 2;
-        if (!active.empty()) ens_upload_table<R>(e, e->j, active);
-        if (!active.empty() && !e->s2cls.empty()) {
-            const int steps4 = (steps + 3) / 4 * 4;
+        const int steps4 = (steps + 3) / 4 * 4;
+        if (!active.empty()) ens_upload_table<R>(e, e->j, active, (uint64_t)steps4);
+        if (!active.empty() && e->groups()) {
             const Lat<float>* dreps = reinterpret_cast<const Lat<float>*>(dtab.p);
             const float* ub = reinterpret_cast<const float*>(tmp.p + 2 * bytes);
             float* u2b = reinterpret_cast<float*>(tmp.p + 3 * bytes);
@@ -2697,10 +2953,21 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
                         check_hip(hipEventRecord(e->cls_events[c2], e->cls_streams[c2 - 1]), "hipEventRecord");
                         check_hip(hipStreamWaitEvent(main, e->cls_events[c2], 0), "hipStreamWaitEvent");
                     }
-                if (e->ntasks_rest)
+                if (e->ntiles) {
+                    const uint64_t nl = tile_launches((uint64_t)steps4, e->tile_shape.T);
+                    const uint64_t q = (uint64_t)steps4 / nl, m = (uint64_t)steps4 % nl;
+                    for (uint64_t i = 0, off = 0; i < nl; ++i) {
+                        const uint64_t t = q + (i < m ? 1 : 0);
+                        launch_ensemble_tile<R>(dreps, e->tiles.p, e->ntiles, e->tile_shape, e->tile_lds, e->model(),
+                                                (int)t, (int)(i & 1), off, ub, u2b, kc.p, off, main);
+                        off += t;
+                    }
+                }
+                const Task* single = ncls ? e->tasks_rest.p : e->tasks.p;
+                const int nsingle = ncls ? e->ntasks_rest : e->ntasks_flat;
+                if (nsingle)
                     for (int i = 0; i < steps4; ++i)
-                        launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(dtab.p), e->tasks_rest.p,
-                                                e->ntasks_rest, kStore, e->model(), best.rows, best.wpb, kc.p,
+                        launch_ensemble_step<R>(dreps, single, nsingle, kStore, e->model(), best.rows, best.wpb, kc.p,
                                                 (uint64_t)i, main);
             };
             const bool direct = e->use_graphs == 0 || (ncls > 1 && e->use_graphs == 1);
@@ -2798,6 +3065,7 @@ int xyl_ensemble_create(xyl_ensemble** out, const xyl_replica_desc* desc, int32_
             check_hip(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
         }
         e->lds.assign(n, 0);
+        e->tiled.assign(n, 0);
         for (int r = 0; r < n; ++r) {
             const int N = desc[r].Lx * desc[r].Ly;
             if (dtype == XYL_F32 && N <= kLdsMaxSites) {

@@ -232,8 +232,8 @@ __device__ __forceinline__ void tile_run(const Lat<R>& v, const TileIO<R>& io, c
     }
 }
 
-// Tile t of n equal parts of L (in units of S): [t L/S/n, (t + 1) L/S/n) S.
-__device__ __forceinline__ TileBox tile_box(int tx, int ty, int ntx, int nty, int Lx, int Ly) {
+// Tile (tx, ty) of ntx x nty about equal ones, whole quads wide.
+__host__ __device__ __forceinline__ TileBox tile_box(int tx, int ty, int ntx, int nty, int Lx, int Ly) {
     constexpr int S = kLaneSites;
     const int nqx = Lx / S;
     TileBox b;
@@ -255,6 +255,23 @@ __global__ __launch_bounds__(NT) void k_tile(Lat<R> v, TileIO<R> io, int ntx, in
     tile_run<R, M, F, S>(v, io, tile_box(tx, ty, ntx, nty, v.Lx, v.Ly), T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
 }
 
+template <typename R, int M, bool F, int S, int NT>
+__global__ __launch_bounds__(NT) void k_ensemble_tile(const Lat<R>* __restrict__ reps,
+                                                      const TileTask* __restrict__ tasks, int T, int flip,
+                                                      uint64_t dk, const R* u_base, R* u2_base, const uint64_t* kdev,
+                                                      uint64_t j0) {
+    extern __shared__ double2 tile_lds_mem[];
+    __shared__ R coef[kTileMaxSteps];
+    const TileTask t = tasks[xcd_contiguous_block(blockIdx.x, gridDim.x)];
+    const Lat<R>& v = reps[t.rep];
+    const uint64_t k = v.k_base + j0 + (kdev ? *kdev : 0);
+    const int a = (int)((k - dk + (uint64_t)v.cur) & 1) ^ flip;
+    R* u = v.u;
+    R* u2 = u2_base + (u - u_base);
+    const TileIO<R> io{v.th[a], flip ? u2 : u, v.th[a ^ 1], flip ? u : u2};
+    tile_run<R, M, F, S>(v, io, TileBox{t.x0, t.y0, t.w, t.h}, T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
+}
+
 // Cost model of one launch of T steps, in us: a fixed part (dispatch, the
 // first loads, the stores), a part per wave of the busiest CU (its prologue),
 // and per step the larger of the latency of one wave's step and the issue
@@ -268,14 +285,31 @@ struct TileCost {
     int max_waves;            // waves per CU by registers
 };
 
+static const TileCost kCost32[] = {{4, 2.75, 0.25, 0.60, 0.317, 32}, {2, 2.75, 0.15, 0.45, 0.22, 32}};
+static const TileCost kCost64[] = {{2, 3.0, 0.5, 1.40, 1.05, 16}, {1, 3.0, 0.3, 0.85, 0.65, 12}};
+
+// Time per step (us) of n steps in nl launches of up to t: `wgs` workgroups of
+// `waves` waves and `lds` bytes on the busiest CU, a region's rows alive for
+// the fraction `alive` of the steps.
+static double tile_cost(const TileCost& c, uint64_t n, uint64_t nl, int waves, size_t lds, int wgs, double alive) {
+    const int fit = std::max(1, std::min((int)(160 * 1024 / lds), c.max_waves / waves));
+    double step = 0.0;
+    for (int left = wgs; left > 0; left -= fit) {
+        const double x = 0.25 * waves * std::min(left, fit) * alive;
+        step += std::sqrt(c.lat * c.lat + c.issue * c.issue * x * x);
+    }
+    return ((double)nl * (c.fixed + c.prologue * 0.25 * waves * wgs) + (double)n * step) / (double)n;
+}
+static double tile_alive(int H, int Ly, int t) {
+    return H == Ly ? 1.0 : 0.5 + 0.5 * (double)std::max(0, H - t - 1) / H;
+}
+
 bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us) {
-    static const TileCost cost32[] = {{4, 2.75, 0.25, 0.60, 0.317, 32}, {2, 2.75, 0.15, 0.45, 0.22, 32}};
-    static const TileCost cost64[] = {{2, 3.0, 0.5, 1.40, 1.05, 16}, {1, 3.0, 0.3, 0.85, 0.65, 12}};
     if (Lx % kLaneSites != 0 || n < 2) return false;
     const size_t es = f64 ? 8 : 4;
     const int quads = Lx / kLaneSites;
     double best = 1e30;
-    for (const TileCost& c : f64 ? cost64 : cost32) {
+    for (const TileCost& c : f64 ? kCost64 : kCost32) {
         for (int T = 2; T <= 12; ++T) {
             const uint64_t nl = tile_launches(n, T);
             const int t = (int)((n + nl - 1) / nl);      // the longest launch's steps
@@ -297,15 +331,7 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
                     if (lds > (size_t)kTileMaxLds) continue;
                     const int waves = (int)((lanes + kWave - 1) / kWave);
                     const int wgs = (ntx * nty + cus - 1) / cus;
-                    const int fit = std::max(1, std::min((int)(160 * 1024 / lds), c.max_waves / waves));
-                    const int rounds = (wgs + fit - 1) / fit;
-                    const double alive = H == Ly ? 1.0 : 0.5 + 0.5 * (double)std::max(0, H - t - 1) / H;
-                    double step = 0.0;
-                    for (int r = 0, left = wgs; r < rounds; ++r, left -= fit) {
-                        const double x = 0.25 * waves * std::min(left, fit) * alive;
-                        step += std::sqrt(c.lat * c.lat + c.issue * c.issue * x * x);
-                    }
-                    const double total = ((double)nl * (c.fixed + c.prologue * 0.25 * waves * wgs) + (double)n * step) / (double)n;
+                    const double total = tile_cost(c, n, nl, waves, lds, wgs, tile_alive(H, Ly, t));
                     if (total < best) {
                         best = total;
                         plan->ntx = ntx;
@@ -320,6 +346,112 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
     }
     if (us) *us = best;
     return best < 1e30;
+}
+
+// The fewest tiles of a lattice whose regions fit `lanes` lanes of S sites;
+// false if none fit.
+static bool tile_fit(int Lx, int Ly, int S, int T, int lanes, size_t es, int* ntx_o, int* nty_o, int* H_o,
+                     size_t* lds_o) {
+    if (T > Lx || T > Ly) return false;
+    long best = 0;
+    int last_w = 0;
+    // (a region has at least min(Ly, 2 T + 1) rows: wider tiles cannot fit)
+    const int w_max = std::max(kLaneSites, lanes * S / std::min(Ly, 2 * T + 1));
+    for (int ntx = std::max(1, Lx / w_max); ntx <= Lx / kLaneSites; ++ntx) {
+        const int w = tile_max_w(Lx, ntx);
+        if (w == last_w) continue;
+        last_w = w;
+        if (best && ntx >= best) break;
+        const int W = tile_region_w(Lx, w, T);
+        if (W != Lx && (W - w) / 2 > Lx) continue;
+        const int rows = (int)std::min<long>(lanes / (W / S), (long)(kTileMaxLds / (4 * es * (size_t)W)));
+        const int h = rows >= Ly ? Ly : rows - 2 * T;
+        if (h < 1) continue;
+        const int nty = (Ly + h - 1) / h;
+        if (best && (long)ntx * nty >= best) continue;
+        best = (long)ntx * nty;
+        *ntx_o = ntx;
+        *nty_o = nty;
+        *H_o = tile_region_h(Ly, tile_max_h(Ly, nty), T);
+        *lds_o = 4 * es * (size_t)W * (size_t)*H_o;
+    }
+    return best != 0;
+}
+
+TileFits::TileFits(const std::vector<TileSize>& sizes, bool f64, int cus, uint64_t n)
+    : sizes_(sizes), f64_(f64), cus_(cus), n_(n) {
+    if (n < 2) return;
+    for (int c = 0; c < 2; ++c) {
+        const int S = (f64 ? kCost64 : kCost32)[c].S;
+        for (int T : {2, 4, 6, 8, 10}) {
+            Shape sh;
+            sh.cost = c;
+            sh.nl = tile_launches(n, T);
+            sh.t = (int)((n + sh.nl - 1) / sh.nl);
+            bool seen = false;
+            for (const Shape& o : shapes_) seen = seen || (o.cost == c && o.t == sh.t);
+            if (seen) continue;
+            for (int waves : {4, 6, 8, 10, 12, 14, 15, 16}) {
+                sh.waves = waves;
+                sh.fits.clear();
+                for (const TileSize& z : sizes) {
+                    Fit f{0, 0, 0, 0};
+                    if (!tile_fit(z.Lx, z.Ly, S, sh.t, waves * kWave, f64 ? 8 : 4, &f.ntx, &f.nty, &f.H, &f.lds))
+                        f.ntx = 0;
+                    sh.fits.push_back(f);
+                }
+                shapes_.push_back(sh);
+            }
+        }
+    }
+}
+
+double TileFits::best(const std::vector<long>& count, TilePlan* shape, std::vector<TileSize>* tiles,
+                      size_t* lds_o) const {
+    double best = 1e30;
+    const Shape* pick = nullptr;
+    size_t pick_lds = 0;
+    for (const Shape& sh : shapes_) {
+        long wgs = 0;
+        size_t lds = 0;
+        double alive = 0.0;
+        bool ok = true;
+        for (size_t i = 0; i < sizes_.size(); ++i) {
+            if (count[i] == 0) continue;
+            const Fit& f = sh.fits[i];
+            if (f.ntx == 0) {
+                ok = false;
+                break;
+            }
+            wgs += (long)f.ntx * f.nty * count[i];
+            lds = std::max(lds, f.lds);
+            alive = std::max(alive, tile_alive(f.H, sizes_[i].Ly, sh.t));
+        }
+        if (!ok || wgs == 0 || wgs > (1L << 30)) continue;
+        const double us = tile_cost((f64_ ? kCost64 : kCost32)[sh.cost], n_, sh.nl, sh.waves, lds,
+                                    (int)((wgs + cus_ - 1) / cus_), alive);
+        if (us < best) {
+            best = us;
+            pick = &sh;
+            pick_lds = lds;
+        }
+    }
+    if (!pick) return best;
+    if (shape) {
+        *shape = TilePlan();
+        shape->T = pick->t;
+        shape->S = (f64_ ? kCost64 : kCost32)[pick->cost].S;
+        shape->threads = pick->waves * kWave;
+    }
+    if (tiles) {
+        *tiles = sizes_;
+        for (size_t i = 0; i < sizes_.size(); ++i) {
+            (*tiles)[i].ntx = count[i] ? pick->fits[i].ntx : 0;
+            (*tiles)[i].nty = count[i] ? pick->fits[i].nty : 0;
+        }
+    }
+    if (lds_o) *lds_o = pick_lds;
+    return best;
 }
 
 template <typename K>
@@ -364,6 +496,54 @@ static void launch_tile_m(const Lat<R>& v, const TileIO<R>& io, const TilePlan& 
     else launch_tile_s<R, M, F, 1>(v, io, p, T, lds, k, s);
 }
 
+void tile_tasks(int rep, int Lx, int Ly, int ntx, int nty, std::vector<TileTask>* out) {
+    for (int ty = 0; ty < nty; ++ty)
+        for (int tx = 0; tx < ntx; ++tx) {
+            const TileBox b = tile_box(tx, ty, ntx, nty, Lx, Ly);
+            out->push_back(TileTask{rep, b.x0, b.y0, b.w, b.h, 0});
+        }
+}
+
+template <typename R, int M, bool F, int S, int NT>
+static void launch_ensemble_tile_nt(const Lat<R>* reps, const TileTask* tasks, int ntasks, const TilePlan& p,
+                                    size_t lds, int T, int flip, uint64_t dk, const R* ub, R* u2b,
+                                    const uint64_t* kdev, uint64_t j, hipStream_t s) {
+    allow_tile_lds(k_ensemble_tile<R, M, F, S, NT>);
+    k_ensemble_tile<R, M, F, S, NT>
+        <<<ntasks, p.threads, lds, s>>>(reps, tasks, T, flip, dk, ub, u2b, kdev, j);
+    check_hip(hipGetLastError(), "ensemble tile kernel launch");
+}
+
+template <typename R, int M>
+static void launch_ensemble_tile_m(const Lat<R>* reps, const TileTask* tasks, int ntasks, const TilePlan& p,
+                                   size_t lds, int T, int flip, uint64_t dk, const R* ub, R* u2b,
+                                   const uint64_t* kdev, uint64_t j, hipStream_t s) {
+    constexpr bool F = sizeof(R) == 4;
+    if constexpr (sizeof(R) == 4) {
+        if (p.S == 4) {
+            launch_ensemble_tile_nt<R, M, F, 4, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
+            return;
+        }
+    }
+    if (p.S == 2)
+        launch_ensemble_tile_nt<R, M, F, 2, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
+    else
+        launch_ensemble_tile_nt<R, M, F, 1, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
+}
+
+template <typename R>
+void launch_ensemble_tile(const Lat<R>* reps, const TileTask* tasks, int ntasks, const TilePlan& p, size_t lds,
+                          int model, int T, int flip, uint64_t dk, const R* u_base, R* u2_base, const uint64_t* kdev,
+                          uint64_t j, hipStream_t s) {
+    if (ntasks < 1 || T < 1 || T > p.T || p.T > kTileMaxSteps || p.threads > kTileMaxThreads ||
+        p.threads % kWave != 0 || lds > kTileMaxLds || !(p.S == 1 || p.S == 2 || (p.S == 4 && sizeof(R) == 4)))
+        throw Error(-5, "ensemble tile launch: shape not supported");
+    if (model == kModelSI)
+        launch_ensemble_tile_m<R, kModelSI>(reps, tasks, ntasks, p, lds, T, flip, dk, u_base, u2_base, kdev, j, s);
+    else
+        launch_ensemble_tile_m<R, kModelXY>(reps, tasks, ntasks, p, lds, T, flip, dk, u_base, u2_base, kdev, j, s);
+}
+
 template <typename R>
 void launch_tile(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, const TilePlan& p, int T,
                  uint64_t k, hipStream_t s) {
@@ -394,5 +574,12 @@ template void launch_tile<float>(const Lat<float>&, const float*, const float*, 
                                  uint64_t, hipStream_t);
 template void launch_tile<double>(const Lat<double>&, const double*, const double*, double*, double*, const TilePlan&,
                                   int, uint64_t, hipStream_t);
+
+template void launch_ensemble_tile<float>(const Lat<float>*, const TileTask*, int, const TilePlan&, size_t, int, int,
+                                          int, uint64_t, const float*, float*, const uint64_t*, uint64_t,
+                                          hipStream_t);
+template void launch_ensemble_tile<double>(const Lat<double>*, const TileTask*, int, const TilePlan&, size_t, int,
+                                           int, int, uint64_t, const double*, double*, const uint64_t*, uint64_t,
+                                           hipStream_t);
 
 }  // namespace xyl

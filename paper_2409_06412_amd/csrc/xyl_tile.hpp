@@ -1,5 +1,7 @@
 // Several steps per launch on tiles held in registers and LDS (xyl_tile.hip).
 #pragma once
+#include <vector>
+
 #include "xyl_internal.hpp"
 
 namespace xyl {
@@ -36,6 +38,55 @@ inline size_t tile_lds(int W, int H) { return sizeof(R) * 4 * (size_t)W * (size_
 bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us);
 // Launches (an even number) that n steps take in launches of at most T.
 inline uint64_t tile_launches(uint64_t n, int T) { return 2 * ((n + 2 * (uint64_t)T - 1) / (2 * (uint64_t)T)); }
+
+// The same for lattices of several sizes in one launch: the shape all tiles
+// share (T, S, threads), each size's tiles and the largest region's LDS.
+struct TileSize {
+    int Lx, Ly;
+    int ntx = 0, nty = 0;
+};
+class TileFits {
+  public:
+    // the fewest tiles of each size at every shape considered for n steps
+    TileFits(const std::vector<TileSize>& sizes, bool f64, int cus, uint64_t n);
+    // the cheapest shape for count[i] lattices of size i (0: left out): its
+    // time per step in us (1e30: none fits), the shape, the tiles of each size
+    // and the LDS; the outputs may be NULL
+    double best(const std::vector<long>& count, TilePlan* shape, std::vector<TileSize>* tiles, size_t* lds) const;
+
+  private:
+    struct Fit {
+        int ntx, nty, H;
+        size_t lds;
+    };
+    struct Shape {
+        int cost, t, waves;
+        uint64_t nl;
+        std::vector<Fit> fits;    // by size; ntx = 0: does not fit
+    };
+    std::vector<TileSize> sizes_;
+    std::vector<Shape> shapes_;
+    bool f64_;
+    int cus_;
+    uint64_t n_;
+};
+
+// One workgroup of a batched launch: the sites it stores of replica rep.
+struct TileTask {
+    int32_t rep, x0, y0, w, h, pad;
+};
+// The tasks of one lattice cut into ntx x nty tiles.
+void tile_tasks(int rep, int Lx, int Ly, int ntx, int nty, std::vector<TileTask>* out);
+// T steps of every task's replica from step k = k_base + j (+ *kdev), in the
+// launch after dk steps of a run that began with the angles in th[(k - dk) & 1]
+// and the velocities in u: launch `flip` = 0, 2, .. of the run reads those and
+// writes the other angle buffer and u2, launch 1, 3, .. goes back.  u2 is the
+// replica's velocities' place in a second array: u2_base + (v.u - u_base).
+// FP32 replicas have the factored kick.  lds: the bytes of the largest region.
+template <typename R>
+void launch_ensemble_tile(const Lat<R>* reps, const TileTask* tasks, int ntasks, const TilePlan& shape, size_t lds,
+                          int model, int T, int flip, uint64_t dk, const R* u_base, R* u2_base, const uint64_t* kdev,
+                          uint64_t j, hipStream_t s);
 
 // T steps from step k of the lattice v: angles and velocities read from th_in
 // and u_in, written to th_out and u_out (distinct buffers).

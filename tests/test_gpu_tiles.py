@@ -75,3 +75,44 @@ def test_tiles_between_samples_and_from_a_fresh_velocity(xyl, dtype):
         np.testing.assert_array_equal(a[1], b[1])
         for x, y in zip(sa, sb):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,model,sizes,budgets", [
+    ("f32", "si", [(144, 144), (128, 128), (96, 80), (32, 32)], (10 ** 6, 71)),   # LDS replicas on tiles, some end
+    ("f32", "xy", [(320, 40), (192, 192), (64, 64), (4, 6)], (10 ** 6, 10 ** 6)),  # a class, another width, tiny ones
+    ("f32", "xy", [(1024, 512), (2048, 300), (300, 300)], (10 ** 6, 50)),          # two classes beside tiles
+    ("f64", "xy", [(64, 64), (128, 60), (20, 200)], (10 ** 6, 33)),
+])
+def test_ensemble_tiles_equal_single_steps(xyl, dtype, model, sizes, budgets):
+    """Ensembles whose replicas take several steps per launch on tiles, beside
+    two-step classes, whole-in-LDS replicas and replicas that end: samples and
+    states of one step per launch, bit for bit, over chunks of 25, 3 and 20
+    steps, for every graph mode."""
+    specs = []
+    for i, (Lx, Ly) in enumerate(sizes):
+        for j in range(6):
+            s = workloads.si_lattice(Lx, Ly, T=1.8 + 0.05 * j, seed=j, replica=10 * i + j) if model == "si" else \
+                workloads.LatticeSpec(Lx, Ly, schedule=((0, 0.4 + 0.1 * j), (40, 0.3)), seed=j, replica=10 * i + j)
+            s.nsteps = budgets[j % 2]
+            if model == "xy" and j == 5:
+                s.Jx = 0.0                      # the unfactored kick
+            specs.append(s)
+    say("ensemble tiles", dtype, model, sizes)
+    res = []
+    for fusion, graphs in ((1, 0), (2, 1), (2, 0), (2, 2)):
+        ens = xyl.Ensemble(specs, dtype=dtype)
+        ens.set_fusion(fusion)
+        ens.set_graphs(graphs)
+        out = [ens.step(63, every=25), ens.step(6, every=3), ens.step(80, every=20)]
+        ens.step(21)
+        out.append(ens.step(5, every=1000))
+        res.append((out, [ens.get_state(r) for r in range(len(specs))]))
+        ens.close()
+    for got in res[1:]:
+        for a, b in zip(res[0][0], got[0]):
+            for x, y in zip(a, b):
+                np.testing.assert_array_equal(x, y)
+        for (ta, wa, ka), (tb, wb, kb) in zip(res[0][1], got[1]):
+            assert ka == kb
+            np.testing.assert_array_equal(ta, tb)
+            np.testing.assert_array_equal(wa, wb)
