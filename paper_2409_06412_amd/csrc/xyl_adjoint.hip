@@ -24,8 +24,9 @@
 // so one pass per step reads th, u, lt', lu' and writes lt, lu.
 #include <mutex>
 #include <set>
+#include <type_traits>
 
-#include "xyl_device.hpp"
+#include "xyl_tile_device.hpp"
 
 namespace xyl {
 
@@ -49,13 +50,16 @@ struct AdjStep {
     R kap;        // lF = kap (lu' + dt lt')
     R lu_fac;     // lu = lu_fac (lu' + dt lt')
     R cm;         // direct loss coefficient of step k
-    R hs, ghs, ga, gc;
+    R hs;
+    // the gamma adjoint's factors: dL/dgamma += g (ka X + kn n) with X = A, or
+    // u at the fresh step (g w (-dt/2) + a g A (-(dt/2) c^2) and
+    // (g + lA) n hs / (2 gamma) with w = c A, lA = c a g)
+    R ka, kn;
     bool fresh;
 };
 
 template <typename R>
-__device__ __forceinline__ AdjStep<R> adj_step_coef(const AdjArgs<R>& A, uint64_t k) {
-    const Lat<R>& v = A.v;
+__device__ __forceinline__ AdjStep<R> adj_step_coef(const Lat<R>& v, const double* cm, uint64_t cm_base, uint64_t k) {
     AdjStep<R> K;
     const double hsd = half_sigma(v.sched, v.gamma, v.dtd, k);
     K.hs = (R)hsd;
@@ -63,17 +67,20 @@ __device__ __forceinline__ AdjStep<R> adj_step_coef(const AdjArgs<R>& A, uint64_
     const R ca = v.c * v.a;
     K.kap = K.fresh ? v.hdt : v.hdt * (R(1) + ca);
     K.lu_fac = K.fresh ? v.a : ca;
-    K.cm = (R)A.cm[k - A.cm_base];
-    K.ghs = v.gamma > 0.0 ? (R)(hsd / (2.0 * v.gamma)) : R(0);
-    K.ga = (R)(-0.5 * v.dtd);
-    K.gc = (R)(-0.5 * v.dtd * (double)v.c * (double)v.c);
+    K.cm = (R)cm[k - cm_base];
+    const double ghs = v.gamma > 0.0 ? hsd / (2.0 * v.gamma) : 0.0;
+    const double c = (double)v.c, a = (double)v.a;
+    K.ka = (R)(K.fresh ? -0.5 * v.dtd : -0.5 * v.dtd * (c + c * c * a));
+    K.kn = (R)(K.fresh ? ghs : ghs * (1.0 + c * a));
     return K;
 }
 
 // The reverse step at one site.  In: (s, c) of its angle th^k, (sin, cos, lF)
 // of its x- and y-neighbours (m = -1, p = +1), its own lF, lt', lu', u^k,
 // draw n^k and staggering sign eps.  Out: lt, lu; its parameter adjoints are
-// added to (rx, ry, rh, rg).
+// added to (rx, ry, rh, rg).  Sums of products are fused multiply-adds (73
+// operations a site; 95 with separate products and the gamma terms one by
+// one, which took the 512^2 tile launch 2.31 us per step against 2.0).
 template <typename R>
 __device__ __forceinline__ void adj_site(const Lat<R>& v, const AdjStep<R>& K, R s, R c, R sxm, R cxm, R fxm, R sxp,
                                          R cxp, R fxp, R sym, R cym, R fym, R syp, R cyp, R fyp, R lf, R lt, R lu, R u,
@@ -84,26 +91,21 @@ __device__ __forceinline__ void adj_site(const Lat<R>& v, const AdjStep<R>& K, R
     const R dFh = R(-4) * s * c;
     const R F = Prec<R>::fma(v.Jx, dFx, Prec<R>::fma(v.Jy, dFy, (R)v.hd * dFh));
     // J lF with cos(th_i - th_j) = c c_j + s s_j
-    const R jx = (c * cxp + s * sxp) * (lf - fxp) + (c * cxm + s * sxm) * (lf - fxm);
-    const R jy = (c * cyp + s * syp) * (lf - fyp) + (c * cym + s * sym) * (lf - fym);
-    const R jh = (c * c - s * s) * lf;
+    const R wxp = Prec<R>::fma(c, cxp, s * sxp), wxm = Prec<R>::fma(c, cxm, s * sxm);
+    const R wyp = Prec<R>::fma(c, cyp, s * syp), wym = Prec<R>::fma(c, cym, s * sym);
+    const R jx = Prec<R>::fma(wxp, lf - fxp, wxm * (lf - fxm));
+    const R jy = Prec<R>::fma(wyp, lf - fyp, wym * (lf - fym));
+    const R jh = Prec<R>::fma(c, c, -(s * s)) * lf;
     const R Jl = Prec<R>::fma(v.Jx, jx, Prec<R>::fma(v.Jy, jy, -v.h4 * jh));
     const R g = Prec<R>::fma(v.dt, lt, lu);
-    lto = lt + Jl + K.cm * (-eps * s);
+    lto = Prec<R>::fma(-(K.cm * eps), s, lt + Jl);
     luo = K.lu_fac * g;
     // parameter adjoints
     rx = Prec<R>::fma(lf, dFx, rx);
     ry = Prec<R>::fma(lf, dFy, ry);
     rh = Prec<R>::fma(lf, dFh, rh);
-    const R lw = v.a * g;
-    if (K.fresh) {
-        rg += K.ga * g * u + K.ghs * n * g;
-    } else {
-        const R Av = Prec<R>::fma(K.hs, n, Prec<R>::fma(v.hdt, F, u));
-        const R w = v.c * Av;
-        const R lA = v.c * lw;
-        rg += K.ga * g * w + K.gc * lw * Av + K.ghs * n * (g + lA);
-    }
+    const R Av = Prec<R>::fma(K.hs, n, Prec<R>::fma(v.hdt, F, u));
+    rg = Prec<R>::fma(g, Prec<R>::fma(K.ka, K.fresh ? u : Av, K.kn * n), rg);
 }
 
 template <typename R>
@@ -129,7 +131,7 @@ __device__ __forceinline__ void adj_strip(const AdjArgs<R>& A, int task, int xw,
     const int x = x0 + kLaneSites * lane;
     const int xm = x == 0 ? Lx - 1 : x - 1;
     const int xp = x + 4 == Lx ? 0 : x + 4;
-    const AdjStep<R> K = adj_step_coef(A, k);
+    const AdjStep<R> K = adj_step_coef(v, A.cm, A.cm_base, k);
     const R kap = K.kap;
     const uint32_t qrow = (uint32_t)(Lx >> 2);
 
@@ -321,8 +323,8 @@ __global__ __launch_bounds__(kAdj2MaxLx) void k_adjoint2(Adj2Args<R> A2, const u
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) u0[i] = A.u[at(y0 + i)];
     const uint64_t k = koff + (kdev ? *kdev : 0);
-    const AdjStep<R> KA = adj_step_coef(A, k + 1);
-    const AdjStep<R> KB = adj_step_coef(A, k);
+    const AdjStep<R> KA = adj_step_coef(v, A.cm, A.cm_base, k + 1);
+    const AdjStep<R> KB = adj_step_coef(v, A.cm, A.cm_base, k);
     // a stage's reverse step at row r, its rows r-1, r, r+1 at C - stride,
     // C, C + stride in its ring, the lane's own (lt', lu') and draw n, with
     // coefficients K; returns lt, lu and adds the parameter adjoints of the
@@ -416,6 +418,223 @@ __global__ __launch_bounds__(kAdj2MaxLx) void k_adjoint2(Adj2Args<R> A2, const u
     const size_t wave = (size_t)strip * (blockDim.x / kWave) + (size_t)(x / kWave);
     if ((lane & 15) == 0) A.gacc[wave * 4 + (lane >> 4)] += tot;
 }
+
+// T reverse steps per launch on tiles, k + T - 1 down to k, as the forward's
+// tiles (xyl_tile.hip): a workgroup takes a region of its tile and a halo of T
+// sites, keeps the adjoint (lt, lu) in registers and, per step, puts (sin,
+// cos, lF) of every site into LDS (double-buffered, one barrier per step); the
+// next step's angles and velocities are loaded meanwhile.  The halo is
+// recomputed by the neighbouring tiles with the arithmetic of adj_site, so lt
+// and lu are bitwise those of single reverse steps; the parameter adjoints are
+// summed in FP32 over a lane's sites of one step and in FP64 from there on.
+template <typename R>
+struct AdjTileArgs {
+    Lat<R> v;
+    const R* states;       // the state at step k + j: angles at states + 2 j N, velocities N further
+    const R* lt_in;        // the adjoint at k + T
+    const R* lu_in;
+    R* lt_out;             // at k
+    R* lu_out;
+    const double* cm;      // direct loss coefficient of step k at cm[k - cm_base]
+    uint64_t cm_base;
+    double* gacc;          // parameter adjoints, 4 per tile, accumulated
+    int ntx, nty, T;
+};
+
+template <typename R, int S, int NT>
+__global__ __launch_bounds__(NT) void k_adjoint_tile(AdjTileArgs<R> A, uint64_t k) {
+    extern __shared__ double2 adj_tile_lds[];
+    __shared__ AdjStep<R> coef[kTileMaxSteps];
+    __shared__ double red[NT / kWave][4];
+    R* lds = reinterpret_cast<R*>(adj_tile_lds);
+    constexpr bool kPair = tile_own_pair<R, S>();
+    constexpr int P = tile_share<R, S>();
+    const Lat<R>& v = A.v;
+    const int T = A.T;
+    const int tile = xcd_contiguous_block(blockIdx.x, gridDim.x);
+    const int ty = tile / A.ntx, tx = tile - ty * A.ntx;
+    const TileLane<S> L(v.Lx, v.Ly, tile_box(tx, ty, A.ntx, A.nty, v.Lx, v.Ly), T);
+    const int WH = L.W * L.H, tab = 3 * WH;
+    const size_t N = (size_t)v.Lx * v.Ly;
+    R lt[S], lu[S], th[S], u[S];
+    tile_load<R, S>(A.lt_in + L.off, lt);
+    tile_load<R, S>(A.lu_in + L.off, lu);
+    tile_load<R, S>(A.states + 2 * N * (size_t)(T - 1) + L.off, th);
+    tile_load<R, S>(A.states + 2 * N * (size_t)(T - 1) + N + L.off, u);
+    if ((int)threadIdx.x < T) {
+        coef[threadIdx.x] = adj_step_coef(v, A.cm, A.cm_base, k + (uint64_t)threadIdx.x);
+    }
+    R eps[S];
+#pragma unroll
+    for (int e = 0; e < S; ++e) eps[e] = ((((L.gx + e) * v.stag_x) + (L.gy * v.stag_y)) & 1) ? R(-1) : R(1);
+    double gx = 0.0, gy = 0.0, gh = 0.0, gg = 0.0;
+    R d[4];
+    __syncthreads();
+    // iteration i takes reverse step j = T - 1 - i; the lanes of a block that
+    // share its draws take those of P successive iterations
+    auto draw = [&](int i) {
+        const uint64_t kt = k + (uint64_t)max(0, T - 1 - i - (P > 1 ? L.part : 0));
+        if constexpr (kPair) {
+            const U32x4 r = philox4x32_10(L.q, v.replica, (uint32_t)kt, (uint32_t)(kt >> 32), v.seed_lo, v.seed_hi);
+            const bool hi = (L.off & 2) != 0;
+            Prec<R>::box_muller(hi ? r.v[2] : r.v[0], hi ? r.v[3] : r.v[1], d[0], d[1]);
+        } else {
+            noise4<R>(L.q, v.replica, kt, v.seed_lo, v.seed_hi, d);
+        }
+    };
+    auto step = [&](auto sub, int i) {
+        constexpr int J = decltype(sub)::value;
+        const int j = T - 1 - i;
+        const bool act = i < L.dist;
+        const AdjStep<R> K = coef[j];
+        R s[S], c[S], lf[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+            Prec<R>::sincos(th[e], s[e], c[e]);
+            lf[e] = K.kap * Prec<R>::fma(v.dt, lt[e], lu[e]);
+        }
+        R* St = lds + (i & 1) * tab;
+        R* Ct = St + WH;
+        R* Ft = Ct + WH;
+        if (L.in) {
+            tile_store<R, S>(St + L.i0, s);
+            tile_store<R, S>(Ct + L.i0, c);
+            tile_store<R, S>(Ft + L.i0, lf);
+        }
+        R uc[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) uc[e] = u[e];
+        if (j > 0) {
+            tile_load<R, S>(A.states + 2 * N * (size_t)(j - 1) + L.off, th);
+            tile_load<R, S>(A.states + 2 * N * (size_t)(j - 1) + N + L.off, u);
+        }
+        if constexpr (J == 0) draw(i);
+        __syncthreads();
+        // (the DPP moves run with every lane of the wave enabled)
+        R sL = from_lane_below(s[S - 1]), cL = from_lane_below(c[S - 1]), fL = from_lane_below(lf[S - 1]);
+        R sR = from_lane_above(s[0]), cR = from_lane_above(c[0]), fR = from_lane_above(lf[0]);
+        R n[S];
+        tile_draws<S, P, J>(d, L.part, n);
+        if (act) {
+            R su[S], cu[S], fu[S], sd[S], cd[S], fd[S];
+            tile_load<R, S>(St + L.iu, su);
+            tile_load<R, S>(Ct + L.iu, cu);
+            tile_load<R, S>(Ft + L.iu, fu);
+            tile_load<R, S>(St + L.id, sd);
+            tile_load<R, S>(Ct + L.id, cd);
+            tile_load<R, S>(Ft + L.id, fd);
+            if (L.edge_l) {
+                sL = St[L.il];
+                cL = Ct[L.il];
+                fL = Ft[L.il];
+            }
+            if (L.edge_r) {
+                sR = St[L.ir];
+                cR = Ct[L.ir];
+                fR = Ft[L.ir];
+            }
+            R rx = 0, ry = 0, rh = 0, rg = 0;
+            R lto[S], luo[S];
+#pragma unroll
+            for (int e = 0; e < S; ++e) {
+                const R sxm = e == 0 ? sL : s[e - 1], cxm = e == 0 ? cL : c[e - 1], fxm = e == 0 ? fL : lf[e - 1];
+                const R sxp = e == S - 1 ? sR : s[e + 1], cxp = e == S - 1 ? cR : c[e + 1],
+                        fxp = e == S - 1 ? fR : lf[e + 1];
+                adj_site(v, K, s[e], c[e], sxm, cxm, fxm, sxp, cxp, fxp, su[e], cu[e], fu[e], sd[e], cd[e], fd[e],
+                         lf[e], lt[e], lu[e], uc[e], n[e], eps[e], lto[e], luo[e], rx, ry, rh, rg);
+            }
+#pragma unroll
+            for (int e = 0; e < S; ++e) {
+                lt[e] = lto[e];
+                lu[e] = luo[e];
+            }
+            if (L.own) {
+                gx += (double)rx;
+                gy += (double)ry;
+                gh += (double)rh;
+                gg += (double)rg;
+            }
+        }
+    };
+    for (int i = 0; i < T; i += P) {
+        step(std::integral_constant<int, 0>{}, i);
+        if constexpr (P >= 2) {
+            if (i + 1 < T) step(std::integral_constant<int, 1>{}, i + 1);
+        }
+        if constexpr (P == 4) {
+            if (i + 2 < T) step(std::integral_constant<int, 2>{}, i + 2);
+            if (i + 3 < T) step(std::integral_constant<int, 3>{}, i + 3);
+        }
+    }
+    if (L.own) {
+        tile_store<R, S>(A.lt_out + L.off, lt);
+        tile_store<R, S>(A.lu_out + L.off, lu);
+    }
+    // the tile's totals in a fixed order, one slot per tile
+    const double acc[4] = {gx, gy, gh, gg};
+    const int lane = threadIdx.x & (kWave - 1);
+    const double tot = wave_sum4(acc, lane);
+    if ((lane & 15) == 0) red[threadIdx.x / kWave][lane >> 4] = tot;
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = 0.0;
+        for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += red[w][threadIdx.x];
+        A.gacc[(size_t)tile * 4 + threadIdx.x] += t;
+    }
+}
+
+template <typename R, int S, int NT>
+static void launch_adjoint_tile_nt(const AdjTileArgs<R>& A, const TilePlan& p, size_t lds, uint64_t k, hipStream_t s) {
+    static std::mutex mu;
+    static std::set<int> allowed;
+    int dev = 0;
+    check_hip(hipGetDevice(&dev), "hipGetDevice");
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (!allowed.count(dev)) {
+            check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(k_adjoint_tile<R, S, NT>),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds),
+                      "hipFuncSetAttribute");
+            allowed.insert(dev);
+        }
+    }
+    k_adjoint_tile<R, S, NT><<<p.ntx * p.nty, p.threads, lds, s>>>(A, k);
+    check_hip(hipGetLastError(), "reverse tile kernel launch");
+}
+
+template <typename R>
+void launch_adjoint_tile(const Lat<R>& v, const R* states, const R* lt_in, const R* lu_in, R* lt_out, R* lu_out,
+                         const double* cm, uint64_t cm_base, double* gacc, const TilePlan& p, int T, uint64_t k,
+                         hipStream_t s) {
+    const size_t lds = tile_check(v.Lx, v.Ly, sizeof(R) == 8, p, T, 6);
+    const AdjTileArgs<R> A{v, states, lt_in, lu_in, lt_out, lu_out, cm, cm_base, gacc, p.ntx, p.nty, T};
+    if constexpr (sizeof(R) == 4) {
+        if (p.S == 4) {
+            if (p.threads <= 512) launch_adjoint_tile_nt<R, 4, 512>(A, p, lds, k, s);
+            else launch_adjoint_tile_nt<R, 4, 1024>(A, p, lds, k, s);
+            return;
+        }
+    } else if (p.threads > 512) {
+        throw Error(-5, "reverse tile launch: shape not supported");
+    } else if (p.S == 1) {
+        launch_adjoint_tile_nt<R, 1, 512>(A, p, lds, k, s);
+        return;
+    }
+    if constexpr (sizeof(R) == 4) {
+        if (p.threads > 512) {
+            launch_adjoint_tile_nt<R, 2, 1024>(A, p, lds, k, s);
+            return;
+        }
+    }
+    launch_adjoint_tile_nt<R, 2, 512>(A, p, lds, k, s);
+}
+
+template void launch_adjoint_tile<float>(const Lat<float>&, const float*, const float*, const float*, float*, float*,
+                                         const double*, uint64_t, double*, const TilePlan&, int, uint64_t,
+                                         hipStream_t);
+template void launch_adjoint_tile<double>(const Lat<double>&, const double*, const double*, const double*, double*,
+                                          double*, const double*, uint64_t, double*, const TilePlan&, int, uint64_t,
+                                          hipStream_t);
 
 // Seed of the reverse sweep at the last step N: lt = direct loss term, lu = 0.
 template <typename R>

@@ -313,7 +313,7 @@ struct xyl_lattice {
     int graph_steps = 32;
     // captured step sequences, keyed by what their kernel arguments bake in
     struct GraphEntry {
-        int mode = 0, S = 0;
+        int mode = 0, S = 0, cur = 0;
         double* part = nullptr;
         uint64_t part_k0 = 0, part_stride = 0;
         uint64_t version = 0;
@@ -394,6 +394,10 @@ struct AdjState {
     hipEvent_t ev_rec[2] = {nullptr, nullptr}, ev_rev[2] = {nullptr, nullptr}, ev_start = nullptr;
     hipGraphExec_t rec_graph[2] = {nullptr, nullptr};        // K recompute steps into buffer b
     hipGraphExec_t rev_graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [b][adjoint parity]
+    // tile plans of the recompute and of the reverse steps for segments of
+    // tile_K steps (64 and more share one; rev.T = 0: none fits)
+    uint64_t tile_K = 0;
+    TilePlan rec, rev;
     // what the captured graphs bake in; they are rebuilt when it changes
     std::vector<uint64_t> graph_key;
     void drop_graphs() {
@@ -600,7 +604,7 @@ static double lattice_untiled_us(const xyl_lattice* h) {
 }
 
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
-// steps (n even), or NULL where another path is faster by the rules' times.
+// steps (n >= 2), or NULL where another path is faster by the rules' times.
 // Widths above 4096 and lattices beyond 2^24 sites never gain (their passes
 // are bound by issue already, and tiles recompute more halo).  Plans are kept
 // per run length (64 steps and more share one).
@@ -630,11 +634,13 @@ static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
     return it->second.T ? &it->second : nullptr;
 }
 
-// n steps (n even) through an even number of launches, (A, u) -> (B, u2) ->
-// (A, u), A the buffer holding the angles at step k: the state ends where it
-// started.
+// n steps through an even number of launches, (A, u) -> (B, u2) -> (A, u), A
+// the buffer holding the angles at step k: the state ends where it started
+// (after an odd number of steps the angle buffers so trade parities).  With
+// `order` the launches also leave the partial sums of every step's order
+// parameter there (launch_tile_order).
 template <typename R>
-static void lattice_tile_steps(xyl_lattice* h, const TilePlan& p, uint64_t n) {
+static void lattice_tile_steps(xyl_lattice* h, const TilePlan& p, uint64_t n, double* order = nullptr) {
     const Lat<R> v = h->view<R>();
     const int parity = (int)((h->k + (uint64_t)h->cur) & 1);
     R* th[2] = {static_cast<R*>(h->th[parity]), static_cast<R*>(h->th[parity ^ 1])};
@@ -643,9 +649,15 @@ static void lattice_tile_steps(xyl_lattice* h, const TilePlan& p, uint64_t n) {
     for (uint64_t i = 0; i < nl; ++i) {
         const int t = (int)(n / nl + (i < n % nl ? 1 : 0));
         const int a = (int)(i & 1);
-        launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, t, h->k, h->stream);
+        if (order) {
+            launch_tile_order<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], order, p, t, h->k, h->stream);
+            order += (size_t)t * tile_order_parts(p);
+        } else {
+            launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, t, h->k, h->stream);
+        }
         h->k += (uint64_t)t;
     }
+    h->cur ^= (int)(n & 1);
     h->counter_valid = false;
 }
 
@@ -655,9 +667,9 @@ template <typename R>
 static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* part, uint64_t part_k0,
                                uint64_t part_stride) {
     if (mode == kStore && part_stride == 0) {
-        if (const TilePlan* p = lattice_tile_plan(h, n - n % 2)) {
-            lattice_tile_steps<R>(h, *p, n - n % 2);
-            n %= 2;
+        if (const TilePlan* p = lattice_tile_plan(h, n)) {
+            lattice_tile_steps<R>(h, *p, n);
+            return;
         }
     }
     if constexpr (sizeof(R) == 4) {
@@ -719,7 +731,7 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
         if (S > 1 && n >= (uint64_t)S) {
             xyl_lattice::GraphEntry* ge = nullptr;
             for (auto& g : h->graphs)
-                if (g.mode == mode && g.S == S && g.part == v.part && g.part_k0 == v.part_k0 &&
+                if (g.mode == mode && g.S == S && g.cur == h->cur && g.part == v.part && g.part_k0 == v.part_k0 &&
                     g.part_stride == v.part_stride)
                     ge = &g;
             if (ge && ge->version != h->version) {
@@ -732,6 +744,7 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
                 ge = &h->graphs.back();
                 ge->mode = mode;
                 ge->S = S;
+                ge->cur = h->cur;
                 ge->part = v.part;
                 ge->part_k0 = v.part_k0;
                 ge->part_stride = v.part_stride;
@@ -778,7 +791,7 @@ static void lattice_measure_into(xyl_lattice* h, bool advance, double* obs_dev) 
 // passes; otherwise the measured step advances one step and the rest follow.
 template <typename R>
 static void lattice_sample_and_advance(xyl_lattice* h, uint64_t span, double* obs_dev) {
-    if ((span >= 4 && step2_eligible(h)) || lattice_tile_plan(h, span - span % 2)) {
+    if ((span >= 4 && step2_eligible(h)) || lattice_tile_plan(h, span)) {
         lattice_measure_into<R>(h, false, obs_dev);
         lattice_steps<R>(h, span);
         return;
@@ -3302,7 +3315,8 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
     // the window's measurement partials, one block per step, reduced together
     // at the end (falls back to one reduction per step for huge lattices)
     const uint64_t stride = (uint64_t)h->nrowparts() * kNPart;
-    const bool batched = (double)W * (double)stride * 8.0 <= 1.0e9;
+    const bool tiles = lattice_tile_plan(h, std::min<uint64_t>(K, W)) != nullptr;
+    const bool batched = !tiles && (double)W * (double)stride * 8.0 <= 1.0e9;
     if (batched) a->win.reserve(W * stride);
     for (uint64_t s = 0; s < S; ++s) {
         char* slot = a->ckpt.p + s * 2 * bytes;
@@ -3311,7 +3325,17 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
         const uint64_t kend = a->k0 + std::min<uint64_t>((s + 1) * K, N);
         while (h->k < kend) {
             if (h->k >= kw) {
-                if (batched) {
+                // the loss needs the order parameter only: on tiles each step
+                // sums it beside the stepping
+                // (single steps where a piece of the window is too short)
+                const TilePlan* tp = tiles ? lattice_tile_plan(h, kend - h->k) : nullptr;
+                if (tp) {
+                    const uint64_t n = kend - h->k, i = h->k - kw;
+                    const size_t parts = (size_t)tile_order_parts(*tp);
+                    a->win.reserve(n * parts);
+                    lattice_tile_steps<R>(h, *tp, n, a->win.p);
+                    launch_tile_order_sum(a->win.p, (int)parts, (double)h->N, a->obs.p + 6 * i, (int)n, h->stream);
+                } else if (batched) {
                     lattice_steps_mode<R>(h, kend - h->k, kStore | kMeasure, a->win.p, kw, stride);
                 } else {
                     lattice_measure_into<R>(h, true, a->obs.p + 6 * (h->k - kw));
@@ -3377,7 +3401,21 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
     // two reverse steps per pass where the rows fit one workgroup's LDS rings
     const int rows2 = adjoint2_rows(h);
     const bool fuse = h->adj_fusion == 2 && adjoint2_fits<R>(v, rows2);
-    const int ntasks = adjoint_tasks<R>(v, l.rows, fuse ? rows2 : 0);
+    // several reverse (and recompute) steps per launch on tiles, unless the
+    // caller shaped the two-step pass: 512^2 FP32 takes 2.2 us per reverse
+    // step so, with the recompute beside it, against 4.9
+    bool tiles = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && h->Lx <= 16 * kWaveSites &&
+                 h->N <= (size_t(1) << 24);
+    if (tiles && a->tile_K != std::min<uint64_t>(K, 64)) {
+        a->tile_K = std::min<uint64_t>(K, 64);
+        const bool f64 = h->dtype == XYL_F64;
+        if (!tile_plan(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rec, nullptr) ||
+            !tile_plan_reverse(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rev))
+            a->rev = TilePlan();
+    }
+    const TilePlan &rev = a->rev, &rec = a->rec;
+    tiles = tiles && rev.T > 0;
+    const int ntasks = tiles ? rev.ntx * rev.nty : adjoint_tasks<R>(v, l.rows, fuse ? rows2 : 0);
     a->gacc.reserve((size_t)ntasks * 4);
     check_hip(hipMemsetAsync(a->gacc.p, 0, sizeof(double) * ntasks * 4, h->stream), "hipMemsetAsync");
     a->lam.reserve(4 * bytes);
@@ -3506,9 +3544,28 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         const uint64_t ks = k0 + s * K;
         const uint64_t len = std::min<uint64_t>(K, k0 + N - ks);
         const char* ck = a->ckpt.p + s * 2 * bytes;
+        if (tiles && len >= 2) {
+            // states 1 .. len - 1 (the reverse steps need no more), the
+            // checkpoint itself into slot 0 on the way
+            const uint64_t n = len - 1, nl = (n + rec.T - 1) / rec.T;
+            const R* th_in = reinterpret_cast<const R*>(ck);
+            const R* u_in = reinterpret_cast<const R*>(ck + bytes);
+            uint64_t j = 0;
+            for (uint64_t i = 0; i < nl; ++i) {
+                const int t = (int)(n / nl + (i < n % nl ? 1 : 0));
+                launch_tile_states<R>(v, th_in, u_in, i == 0, slot_th(b, j + 1), rec, t, ks + j, a->side);
+                j += (uint64_t)t;
+                th_in = slot_th(b, j);
+                u_in = slot_u(b, j);
+            }
+            check_hip(hipEventRecord(a->ev_rec[b], a->side), "hipEventRecord");
+            return;
+        }
         check_hip(hipMemcpyAsync(slot_th(b, 0), ck, bytes, hipMemcpyDeviceToDevice, a->side), "D2D");
         check_hip(hipMemcpyAsync(slot_u(b, 0), ck + bytes, bytes, hipMemcpyDeviceToDevice, a->side), "D2D");
-        if (use_graph && len == K) {
+        if (tiles) {
+            // a single step: its state is the checkpoint
+        } else if (use_graph && len == K) {
             if (!a->rec_graph[b])
                 a->rec_graph[b] = capture([&] {
                     recompute_run(b, K, a->kseg.p + 1, 0, h->cap_stream);
@@ -3534,7 +3591,17 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         check_hip(hipStreamWaitEvent(h->stream, a->ev_rec[b], 0), "hipStreamWaitEvent");
         const uint64_t ks = k0 + s * K;
         const uint64_t len = std::min<uint64_t>(K, k0 + N - ks);
-        if (use_graph && len == K) {
+        if (tiles) {
+            const uint64_t nl = (len + rev.T - 1) / rev.T;
+            uint64_t j = len;
+            for (uint64_t i = 0; i < nl; ++i) {
+                const int t = (int)(len / nl + (i < len % nl ? 1 : 0));
+                j -= (uint64_t)t;
+                launch_adjoint_tile<R>(v, slot_th(b, j), lt[li], lu[li], lt[li ^ 1], lu[li ^ 1], a->cm.p, k0,
+                                       a->gacc.p, rev, t, ks + j, h->stream);
+                li ^= 1;
+            }
+        } else if (use_graph && len == K) {
             int end = li;
             if (!a->rev_graph[b][li])
                 a->rev_graph[b][li] = capture([&] { end = reverse_segment(b, K, li, a->kseg.p, 0, h->cap_stream); });

@@ -38,162 +38,110 @@
 #include <set>
 #include <type_traits>
 
-#include "xyl_device.hpp"
-#include "xyl_tile.hpp"
+#include "xyl_tile_device.hpp"
 
 namespace xyl {
 
+// What a tile launch does beyond storing the last state:
+enum : int {
+    kTilePlain = 0,
+    kTileStates = 1,   // stores every state, step j of the run at out + 2 j N (angles, then velocities)
+    kTileOrder = 2     // sums the staggered order parameter's component of every state it steps from (XY)
+};
 template <typename R>
 struct TileIO {
     const R* th_in;
     const R* u_in;
     R* th_out;
     R* u_out;
+    R* states = nullptr;         // kTileStates: where the state after the launch's first step goes
+    int first = 0;               //   1: the state it starts from goes before it
+    double* order = nullptr;     // kTileOrder: [step of the launch][workgroup][wave]
 };
-struct TileBox {
-    int x0, y0, w, h;     // the sites a workgroup stores
-};
 
-template <typename R, int S>
-__device__ __forceinline__ void tile_load(const R* p, R* o) {
-    if constexpr (S == 4) {
-        load4(p, o);
-    } else if constexpr (S == 2) {
-        typedef R V2 __attribute__((ext_vector_type(2)));
-        const V2 d = *reinterpret_cast<const V2*>(p);
-        o[0] = d.x;
-        o[1] = d.y;
-    } else {
-        o[0] = *p;
-    }
-}
-template <typename R, int S>
-__device__ __forceinline__ void tile_store(R* p, const R* o) {
-    if constexpr (S == 4) {
-        store4(p, o);
-    } else if constexpr (S == 2) {
-        typedef R V2 __attribute__((ext_vector_type(2)));
-        V2 d;
-        d.x = o[0];
-        d.y = o[1];
-        *reinterpret_cast<V2*>(p) = d;
-    } else {
-        *p = o[0];
-    }
-}
-
-// The value of lane J of the lane's group of P lanes (P = 2 or 4, a Philox
-// block's lanes), by DPP.
-template <int P, int J, typename R>
-__device__ __forceinline__ R group_lane(R x) {
-    constexpr int ctrl = P == 4 ? J * 0x55 : (J | (J << 2) | ((2 + J) << 4) | ((2 + J) << 6));
-    if constexpr (sizeof(R) == 4)
-        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xF, 0xF, false));
-    else
-        return dpp_f64<ctrl>(x);
-}
-
-template <typename R, int M, bool F, int S>
+template <typename R, int M, bool F, int S, int KIND>
 __device__ __forceinline__ void tile_run(const Lat<R>& v, const TileIO<R>& io, const TileBox& b, int T, uint64_t k,
                                          R* lds, R* coef) {
-    constexpr bool kPair = sizeof(R) == 8 && S == 2;       // each lane draws its own pair in every step
-    constexpr int P = kPair ? 1 : 4 / S;                   // lanes that share the draws of their block
-    const int Lx = v.Lx, Ly = v.Ly;
-    const bool px = b.w == Lx, py = b.h == Ly;             // the region is periodic along the axis
-    const int hx = px ? 0 : (T + 3) / 4 * 4, hy = py ? 0 : T;
-    const int W = b.w + 2 * hx, H = b.h + 2 * hy;
-    const int Wq = W / S, nq = Wq * H;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const bool in = tid < nq;
-    const int g = in ? tid : nq - P + (tid & (P - 1));
-    const int y = g / Wq, xq = g - y * Wq;
-    int gy = b.y0 - hy + y, gx = b.x0 - hx + S * xq;
-    gy = gy < 0 ? gy + Ly : (gy >= Ly ? gy - Ly : gy);
-    gx = gx < 0 ? gx + Lx : (gx >= Lx ? gx - Lx : gx);
-    const uint32_t off = (uint32_t)gy * (uint32_t)Lx + (uint32_t)gx;
-    const uint32_t q = off >> 2;
-    const int part = tid & (P - 1);                        // the lane's place in its block
-    // table slots of the group and of its neighbours (the region's outer ring
-    // of a non-periodic axis has none: its values are never used)
-    const int i0 = S * g;
-    const int iu = y == 0 ? (py ? i0 + (H - 1) * W : i0) : i0 - W;
-    const int id = y == H - 1 ? (py ? i0 - (H - 1) * W : i0) : i0 + W;
-    const int il = xq == 0 ? (px ? i0 + W - 1 : i0) : i0 - 1;
-    const int ir = xq == Wq - 1 ? (px ? i0 + S - W : i0) : i0 + S;
-    const bool edge_l = lane == 0 || (xq == 0 && px), edge_r = lane == kWave - 1 || (xq == Wq - 1 && px);
-    // steps the group's sites stay valid for: the distance of its innermost
-    // site from the region's edge
-    int dist = T;
-    if (!py) dist = min(dist, min(y, H - 1 - y));
-    if (!px) dist = min(dist, min(S * xq + S - 1, W - 1 - S * xq));
-    if (!in) dist = 0;
+    constexpr bool kPair = tile_own_pair<R, S>();
+    constexpr int P = tile_share<R, S>();
+    const TileLane<S> L(v.Lx, v.Ly, b, T);
+    const int WH = L.W * L.H;
+    const size_t N = (size_t)v.Lx * v.Ly;
     R th[S], u[S], s[S], c[S];
-    tile_load<R, S>(io.th_in + off, th);
-    tile_load<R, S>(io.u_in + off, u);
+    tile_load<R, S>(io.th_in + L.off, th);
+    tile_load<R, S>(io.u_in + L.off, u);
     // the steps' noise amplitudes, while the loads are under way
-    for (int j = tid; j < T; j += (int)blockDim.x) coef[j] = noise_coeff<R, F>(v, k + (uint64_t)j);
-    const int tab = 2 * W * H;
+    for (int j = threadIdx.x; j < T; j += (int)blockDim.x) coef[j] = noise_coeff<R, F>(v, k + (uint64_t)j);
+    if constexpr (KIND == kTileStates) {
+        if (io.first && L.own) {
+            tile_store<R, S>(io.states - 2 * N + L.off, th);
+            tile_store<R, S>(io.states - N + L.off, u);
+        }
+    }
+    const int tab = 2 * WH;
 #pragma unroll
     for (int e = 0; e < S; ++e) rotor<R, M>(th[e], s[e], c[e]);
-    if (in) {
-        tile_store<R, S>(lds + i0, s);
-        tile_store<R, S>(lds + W * H + i0, c);
+    if (L.in) {
+        tile_store<R, S>(lds + L.i0, s);
+        tile_store<R, S>(lds + WH + L.i0, c);
     }
     __syncthreads();
-    // a block's lanes take the draws of P successive steps, one step each
     R d[4];
     auto draw = [&](int t) {
-        const uint64_t kt = k + (uint64_t)(t + part);
-        const R hs = coef[min(t + part, T - 1)];
+        const uint64_t kt = k + (uint64_t)(t + (P > 1 ? L.part : 0));
         if constexpr (kPair) {
-            const U32x4 r = philox4x32_10(q, v.replica, (uint32_t)kt, (uint32_t)(kt >> 32), v.seed_lo, v.seed_hi);
-            const bool hi = (off & 2) != 0;
+            const U32x4 r = philox4x32_10(L.q, v.replica, (uint32_t)kt, (uint32_t)(kt >> 32), v.seed_lo, v.seed_hi);
+            const bool hi = (L.off & 2) != 0;
             Prec<R>::box_muller(hi ? r.v[2] : r.v[0], hi ? r.v[3] : r.v[1], d[0], d[1]);
-            return;
+        } else if constexpr (sizeof(R) == 4) {
+            const R hs = coef[min(t + (P > 1 ? L.part : 0), T - 1)];
+            noise4_kick<R>(L.q, v.replica, kt, v.seed_lo, v.seed_hi, hs, d, noise_u2<R, F>(v));
+        } else {
+            noise4<R>(L.q, v.replica, kt, v.seed_lo, v.seed_hi, d);
         }
-        if constexpr (sizeof(R) == 4) noise4_kick<R>(q, v.replica, kt, v.seed_lo, v.seed_hi, hs, d, noise_u2<R, F>(v));
-        else noise4<R>(q, v.replica, kt, v.seed_lo, v.seed_hi, d);
     };
     auto step = [&](auto sub, int t) {
         constexpr int J = decltype(sub)::value;
         const uint64_t kt = k + (uint64_t)t;
-        const bool act = t < dist;
+        const bool act = t < L.dist;
         if constexpr (J == 0) {
             if (P > 1 || act) draw(t);
         }
+        if constexpr (KIND == kTileOrder) {
+            // signs: the group starts at a multiple of S on the lattice
+            double m = 0.0;
+            if (L.own) {
+#pragma unroll
+                for (int e = 0; e < S; ++e) {
+                    const bool neg = ((((L.gx + e) * v.stag_x) + (L.gy * v.stag_y)) & 1) != 0;
+                    m += neg ? -(double)c[e] : (double)c[e];
+                }
+            }
+            m = wave_sum1(m);
+            if ((threadIdx.x & (kWave - 1)) == 0)
+                io.order[((size_t)t * gridDim.x + blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave] = m;
+        }
         if (t) __syncthreads();
         const R* St = lds + (t & 1) * tab;
-        const R* Ct = St + W * H;
+        const R* Ct = St + WH;
         // (the DPP moves run with every lane of the wave enabled)
         R sL = from_lane_below(s[S - 1]), cL = from_lane_below(c[S - 1]);
         R sR = from_lane_above(s[0]), cR = from_lane_above(c[0]);
         R su[S], cu[S], sd[S], cd[S];
-        tile_load<R, S>(St + iu, su);
-        tile_load<R, S>(Ct + iu, cu);
-        tile_load<R, S>(St + id, sd);
-        tile_load<R, S>(Ct + id, cd);
-        if (edge_l) {
-            sL = St[il];
-            cL = Ct[il];
+        tile_load<R, S>(St + L.iu, su);
+        tile_load<R, S>(Ct + L.iu, cu);
+        tile_load<R, S>(St + L.id, sd);
+        tile_load<R, S>(Ct + L.id, cd);
+        if (L.edge_l) {
+            sL = St[L.il];
+            cL = Ct[L.il];
         }
-        if (edge_r) {
-            sR = St[ir];
-            cR = Ct[ir];
+        if (L.edge_r) {
+            sR = St[L.ir];
+            cR = Ct[L.ir];
         }
         R n[S];
-#pragma unroll
-        for (int e = 0; e < S; ++e) {
-            if constexpr (P == 1) {
-                n[e] = d[e];
-            } else {
-                n[e] = group_lane<P, J>(d[e]);
-#pragma unroll
-                for (int l = 1; l < P; ++l) {
-                    const R o = group_lane<P, J>(d[l * S + e]);
-                    n[e] = part == l ? o : n[e];
-                }
-            }
-        }
+        tile_draws<S, P, J>(d, L.part, n);
         if (act) {
             const bool fresh = kt == v.fresh_k;
             const R hs = coef[t];
@@ -206,12 +154,18 @@ __device__ __forceinline__ void tile_run(const Lat<R>& v, const TileIO<R>& io, c
                 R w;
                 site_update<R, M, F>(v, f, u[e], th[e], n[e], hs, fresh, w, u[e], th[e]);
             }
+            if constexpr (KIND == kTileStates) {
+                if (L.own) {
+                    tile_store<R, S>(io.states + 2 * N * (size_t)t + L.off, th);
+                    tile_store<R, S>(io.states + 2 * N * (size_t)t + N + L.off, u);
+                }
+            }
             if (t + 1 < T) {
                 R* Sn = lds + ((t + 1) & 1) * tab;
 #pragma unroll
                 for (int e = 0; e < S; ++e) rotor<R, M>(th[e], s[e], c[e]);
-                tile_store<R, S>(Sn + i0, s);
-                tile_store<R, S>(Sn + W * H + i0, c);
+                tile_store<R, S>(Sn + L.i0, s);
+                tile_store<R, S>(Sn + WH + L.i0, c);
             }
         }
     };
@@ -225,34 +179,22 @@ __device__ __forceinline__ void tile_run(const Lat<R>& v, const TileIO<R>& io, c
             if (t + 3 < T) step(std::integral_constant<int, 3>{}, t + 3);
         }
     }
-    const bool own = in && y >= hy && y < hy + b.h && S * xq >= hx && S * xq < hx + b.w;
-    if (own) {
-        tile_store<R, S>(io.th_out + off, th);
-        tile_store<R, S>(io.u_out + off, u);
+    if constexpr (KIND != kTileStates) {
+        if (L.own) {
+            tile_store<R, S>(io.th_out + L.off, th);
+            tile_store<R, S>(io.u_out + L.off, u);
+        }
     }
 }
 
-// Tile (tx, ty) of ntx x nty about equal ones, whole quads wide.
-__host__ __device__ __forceinline__ TileBox tile_box(int tx, int ty, int ntx, int nty, int Lx, int Ly) {
-    constexpr int S = kLaneSites;
-    const int nqx = Lx / S;
-    TileBox b;
-    const int xa = (int)((long)tx * nqx / ntx), xb = (int)((long)(tx + 1) * nqx / ntx);
-    const int ya = (int)((long)ty * Ly / nty), yb = (int)((long)(ty + 1) * Ly / nty);
-    b.x0 = xa * S;
-    b.w = (xb - xa) * S;
-    b.y0 = ya;
-    b.h = yb - ya;
-    return b;
-}
-
-template <typename R, int M, bool F, int S, int NT>
+template <typename R, int M, bool F, int S, int KIND, int NT>
 __global__ __launch_bounds__(NT) void k_tile(Lat<R> v, TileIO<R> io, int ntx, int nty, int T, uint64_t k) {
     extern __shared__ double2 tile_lds_mem[];
     __shared__ R coef[kTileMaxSteps];
     const int b = xcd_contiguous_block(blockIdx.x, gridDim.x);
     const int ty = b / ntx, tx = b - ty * ntx;
-    tile_run<R, M, F, S>(v, io, tile_box(tx, ty, ntx, nty, v.Lx, v.Ly), T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
+    tile_run<R, M, F, S, KIND>(v, io, tile_box(tx, ty, ntx, nty, v.Lx, v.Ly), T, k, reinterpret_cast<R*>(tile_lds_mem),
+                               coef);
 }
 
 template <typename R, int M, bool F, int S, int NT>
@@ -269,7 +211,7 @@ __global__ __launch_bounds__(NT) void k_ensemble_tile(const Lat<R>* __restrict__
     R* u = v.u;
     R* u2 = u2_base + (u - u_base);
     const TileIO<R> io{v.th[a], flip ? u2 : u, v.th[a ^ 1], flip ? u : u2};
-    tile_run<R, M, F, S>(v, io, TileBox{t.x0, t.y0, t.w, t.h}, T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
+    tile_run<R, M, F, S, kTilePlain>(v, io, TileBox{t.x0, t.y0, t.w, t.h}, T, k, reinterpret_cast<R*>(tile_lds_mem), coef);
 }
 
 // Cost model of one launch of T steps, in us: a fixed part (dispatch, the
@@ -304,16 +246,19 @@ static double tile_alive(int H, int Ly, int t) {
     return H == Ly ? 1.0 : 0.5 + 0.5 * (double)std::max(0, H - t - 1) / H;
 }
 
-bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us) {
-    if (Lx % kLaneSites != 0 || n < 2) return false;
+// The cheapest plan for n steps with `tables` LDS numbers per site, in an even
+// number of launches or (pairs = false) in any.
+static bool tile_search(const TileCost* costs, int tables, bool pairs, int max_lanes, int Lx, int Ly, bool f64, int cus, uint64_t n,
+                        TilePlan* plan, double* us) {
     const size_t es = f64 ? 8 : 4;
     const int quads = Lx / kLaneSites;
     double best = 1e30;
-    for (const TileCost& c : f64 ? kCost64 : kCost32) {
-        for (int T = 2; T <= 12; ++T) {
-            const uint64_t nl = tile_launches(n, T);
+    for (int i = 0; i < 2; ++i) {
+        const TileCost& c = costs[i];
+        for (int T = pairs ? 2 : 1; T <= 12; ++T) {
+            const uint64_t nl = pairs ? tile_launches(n, T) : (n + T - 1) / T;
             const int t = (int)((n + nl - 1) / nl);      // the longest launch's steps
-            if (t < T && T > 2) continue;                // the same as a smaller T
+            if (t < T && T > 2) continue;                // as a smaller T
             if (t > Lx || t > Ly) continue;
             int last_w = 0;
             for (int ntx = 1; ntx <= quads && ntx <= 256; ++ntx) {
@@ -322,12 +267,12 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
                 last_w = w;
                 const int W = tile_region_w(Lx, w, t);
                 if (W != Lx && (W - w) / 2 > Lx) continue;
-                for (int per = 1; per <= 64; per = per < 4 ? per + 1 : per * 2) {
+                for (int per = 1; per <= 64; per += std::max(1, per / 6)) {
                     const int nty = std::min(Ly, std::max(1, per * cus / ntx));
                     const int h = tile_max_h(Ly, nty), H = tile_region_h(Ly, h, t);
                     const long lanes = (long)(W / c.S) * H;
-                    if (lanes > kTileMaxThreads) continue;
-                    const size_t lds = 4 * es * (size_t)W * H;
+                    if (lanes > max_lanes) continue;
+                    const size_t lds = tables * es * (size_t)W * H;
                     if (lds > (size_t)kTileMaxLds) continue;
                     const int waves = (int)((lanes + kWave - 1) / kWave);
                     const int wgs = (ntx * nty + cus - 1) / cus;
@@ -346,6 +291,19 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
     }
     if (us) *us = best;
     return best < 1e30;
+}
+
+bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us) {
+    if (Lx % kLaneSites != 0 || n < 2) return false;
+    return tile_search(f64 ? kCost64 : kCost32, 4, true, kTileMaxThreads, Lx, Ly, f64, cus, n, plan, us);
+}
+
+bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan) {
+    // (FP64 regions of more than 512 lanes would spill)
+    static const TileCost rev32[] = {{4, 4.0, 0.35, 0.80, 0.62, 16}, {2, 4.0, 0.2, 0.50, 0.36, 16}};
+    static const TileCost rev64[] = {{2, 4.0, 0.5, 1.60, 1.40, 8}, {1, 4.0, 0.3, 1.00, 1.00, 12}};
+    if (Lx % kLaneSites != 0 || n < 1) return false;
+    return tile_search(f64 ? rev64 : rev32, 6, false, f64 ? 512 : kTileMaxThreads, Lx, Ly, f64, cus, n, plan, nullptr);
 }
 
 // The fewest tiles of a lattice whose regions fit `lanes` lanes of S sites;
@@ -468,33 +426,39 @@ static void allow_tile_lds(K* kernel) {
     allowed.insert(key);
 }
 
-template <typename R, int M, bool F, int S, int NT>
+template <typename R, int M, bool F, int S, int KIND, int NT>
 static void launch_tile_nt(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
                            hipStream_t s) {
-    allow_tile_lds(k_tile<R, M, F, S, NT>);
-    k_tile<R, M, F, S, NT><<<p.ntx * p.nty, p.threads, lds, s>>>(v, io, p.ntx, p.nty, T, k);
+    allow_tile_lds(k_tile<R, M, F, S, KIND, NT>);
+    k_tile<R, M, F, S, KIND, NT><<<p.ntx * p.nty, p.threads, lds, s>>>(v, io, p.ntx, p.nty, T, k);
     check_hip(hipGetLastError(), "tile kernel launch");
 }
 
-template <typename R, int M, bool F, int S>
+template <typename R, int M, bool F, int S, int KIND>
 static void launch_tile_s(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
                           hipStream_t s) {
-    if (p.threads <= 512) launch_tile_nt<R, M, F, S, 512>(v, io, p, T, lds, k, s);
-    else launch_tile_nt<R, M, F, S, 1024>(v, io, p, T, lds, k, s);
+    if (p.threads <= 512) launch_tile_nt<R, M, F, S, KIND, 512>(v, io, p, T, lds, k, s);
+    else launch_tile_nt<R, M, F, S, KIND, 1024>(v, io, p, T, lds, k, s);
 }
 
-template <typename R, int M, bool F>
+template <typename R, int M, bool F, int KIND>
 static void launch_tile_m(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, size_t lds, uint64_t k,
                           hipStream_t s) {
     if constexpr (sizeof(R) == 4) {
         if (p.S == 4) {
-            launch_tile_s<R, M, F, 4>(v, io, p, T, lds, k, s);
+            launch_tile_s<R, M, F, 4, KIND>(v, io, p, T, lds, k, s);
             return;
         }
     }
-    if (p.S == 2) launch_tile_s<R, M, F, 2>(v, io, p, T, lds, k, s);
-    else launch_tile_s<R, M, F, 1>(v, io, p, T, lds, k, s);
+    if constexpr (sizeof(R) == 4) {
+        launch_tile_s<R, M, F, 2, KIND>(v, io, p, T, lds, k, s);
+    } else {
+        if (p.S == 2) launch_tile_s<R, M, F, 2, KIND>(v, io, p, T, lds, k, s);
+        else launch_tile_s<R, M, F, 1, KIND>(v, io, p, T, lds, k, s);
+    }
 }
+
+static bool sites_per_lane_ok(int S, bool f64) { return S == 2 || S == (f64 ? 1 : 4); }
 
 void tile_tasks(int rep, int Lx, int Ly, int ntx, int nty, std::vector<TileTask>* out) {
     for (int ty = 0; ty < nty; ++ty)
@@ -525,10 +489,13 @@ static void launch_ensemble_tile_m(const Lat<R>* reps, const TileTask* tasks, in
             return;
         }
     }
-    if (p.S == 2)
-        launch_ensemble_tile_nt<R, M, F, 2, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
-    else
-        launch_ensemble_tile_nt<R, M, F, 1, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
+    if constexpr (sizeof(R) == 8) {
+        if (p.S == 1) {
+            launch_ensemble_tile_nt<R, M, F, 1, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
+            return;
+        }
+    }
+    launch_ensemble_tile_nt<R, M, F, 2, 1024>(reps, tasks, ntasks, p, lds, T, flip, dk, ub, u2b, kdev, j, s);
 }
 
 template <typename R>
@@ -536,7 +503,7 @@ void launch_ensemble_tile(const Lat<R>* reps, const TileTask* tasks, int ntasks,
                           int model, int T, int flip, uint64_t dk, const R* u_base, R* u2_base, const uint64_t* kdev,
                           uint64_t j, hipStream_t s) {
     if (ntasks < 1 || T < 1 || T > p.T || p.T > kTileMaxSteps || p.threads > kTileMaxThreads ||
-        p.threads % kWave != 0 || lds > kTileMaxLds || !(p.S == 1 || p.S == 2 || (p.S == 4 && sizeof(R) == 4)))
+        p.threads % kWave != 0 || lds > kTileMaxLds || !sites_per_lane_ok(p.S, sizeof(R) == 8))
         throw Error(-5, "ensemble tile launch: shape not supported");
     if (model == kModelSI)
         launch_ensemble_tile_m<R, kModelSI>(reps, tasks, ntasks, p, lds, T, flip, dk, u_base, u2_base, kdev, j, s);
@@ -544,32 +511,95 @@ void launch_ensemble_tile(const Lat<R>* reps, const TileTask* tasks, int ntasks,
         launch_ensemble_tile_m<R, kModelXY>(reps, tasks, ntasks, p, lds, T, flip, dk, u_base, u2_base, kdev, j, s);
 }
 
+// The LDS of the plan's launches of T steps with `tables` rotor tables; checks
+// what the kernels assume.
+size_t tile_check(int Lx, int Ly, bool f64, const TilePlan& p, int T, int tables) {
+    const int wmax = tile_max_w(Lx, p.ntx), hmax = tile_max_h(Ly, p.nty);
+    const int W = tile_region_w(Lx, wmax, T), H = tile_region_h(Ly, hmax, T);
+    const size_t lds = (f64 ? 8 : 4) * (size_t)tables * (size_t)W * H;
+    if (T < 1 || T > p.T || p.T > kTileMaxSteps || p.ntx < 1 || p.nty < 1 || p.ntx > Lx / kLaneSites || p.nty > Ly ||
+        !sites_per_lane_ok(p.S, f64) || (W / p.S) * H > p.threads || p.threads > kTileMaxThreads ||
+        p.threads % kWave != 0 || lds > kTileMaxLds || (W != Lx && (W - wmax) / 2 > Lx) || (H != Ly && T > Ly))
+        throw Error(-5, "tile launch: shape not supported");
+    return lds;
+}
+
 template <typename R>
 void launch_tile(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, const TilePlan& p, int T,
                  uint64_t k, hipStream_t s) {
-    const int wmax = tile_max_w(v.Lx, p.ntx), hmax = tile_max_h(v.Ly, p.nty);
-    const int W = tile_region_w(v.Lx, wmax, T), H = tile_region_h(v.Ly, hmax, T);
-    const size_t lds = tile_lds<R>(W, H);
-    if (T < 1 || T > kTileMaxSteps || p.ntx < 1 || p.nty < 1 || p.ntx > v.Lx / 4 || p.nty > v.Ly ||
-        !(p.S == 1 || p.S == 2 || (p.S == 4 && sizeof(R) == 4)) || (W / p.S) * H > p.threads ||
-        p.threads > kTileMaxThreads || p.threads % kWave != 0 || lds > kTileMaxLds ||
-        (W != v.Lx && (W - wmax) / 2 > v.Lx) || (H != v.Ly && T > v.Ly))
-        throw Error(-5, "tile launch: shape not supported");
+    const size_t lds = tile_check(v.Lx, v.Ly, sizeof(R) == 8, p, T, 4);
     const TileIO<R> io{th_in, u_in, th_out, u_out};
     if constexpr (sizeof(R) == 4) {
         if (v.model == kModelSI) {
-            if (v.fact) launch_tile_m<R, kModelSI, true>(v, io, p, T, lds, k, s);
-            else launch_tile_m<R, kModelSI, false>(v, io, p, T, lds, k, s);
+            if (v.fact) launch_tile_m<R, kModelSI, true, kTilePlain>(v, io, p, T, lds, k, s);
+            else launch_tile_m<R, kModelSI, false, kTilePlain>(v, io, p, T, lds, k, s);
         } else {
-            if (v.fact) launch_tile_m<R, kModelXY, true>(v, io, p, T, lds, k, s);
-            else launch_tile_m<R, kModelXY, false>(v, io, p, T, lds, k, s);
+            if (v.fact) launch_tile_m<R, kModelXY, true, kTilePlain>(v, io, p, T, lds, k, s);
+            else launch_tile_m<R, kModelXY, false, kTilePlain>(v, io, p, T, lds, k, s);
         }
     } else {
-        if (v.model == kModelSI) launch_tile_m<R, kModelSI, false>(v, io, p, T, lds, k, s);
-        else launch_tile_m<R, kModelXY, false>(v, io, p, T, lds, k, s);
+        if (v.model == kModelSI) launch_tile_m<R, kModelSI, false, kTilePlain>(v, io, p, T, lds, k, s);
+        else launch_tile_m<R, kModelXY, false, kTilePlain>(v, io, p, T, lds, k, s);
     }
 }
 
+template <typename R, int KIND>
+static void launch_tile_xy(const Lat<R>& v, const TileIO<R>& io, const TilePlan& p, int T, uint64_t k, hipStream_t s) {
+    const size_t lds = tile_check(v.Lx, v.Ly, sizeof(R) == 8, p, T, 4);
+    if (v.model != kModelXY) throw Error(-5, "tile launch: XY lattices only");
+    if constexpr (sizeof(R) == 4) {
+        if (v.fact) launch_tile_m<R, kModelXY, true, KIND>(v, io, p, T, lds, k, s);
+        else launch_tile_m<R, kModelXY, false, KIND>(v, io, p, T, lds, k, s);
+    } else {
+        launch_tile_m<R, kModelXY, false, KIND>(v, io, p, T, lds, k, s);
+    }
+}
+
+template <typename R>
+void launch_tile_states(const Lat<R>& v, const R* th_in, const R* u_in, bool first, R* states, const TilePlan& p,
+                        int T, uint64_t k, hipStream_t s) {
+    TileIO<R> io{th_in, u_in, nullptr, nullptr};
+    io.states = states;
+    io.first = first ? 1 : 0;
+    launch_tile_xy<R, kTileStates>(v, io, p, T, k, s);
+}
+
+template <typename R>
+void launch_tile_order(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, double* order,
+                       const TilePlan& p, int T, uint64_t k, hipStream_t s) {
+    TileIO<R> io{th_in, u_in, th_out, u_out};
+    io.order = order;
+    launch_tile_xy<R, kTileOrder>(v, io, p, T, k, s);
+}
+
+// One workgroup per step: the sum of its n partials (strided per thread, then
+// a fixed tree) over N into out[6 step + 2].
+__global__ __launch_bounds__(256) void k_tile_order_sum(const double* __restrict__ order, int n, double N,
+                                                        double* __restrict__ out) {
+    __shared__ double red[4];
+    const double* p = order + (size_t)blockIdx.x * n;
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) acc += p[i];
+    acc = wave_sum1(acc);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) out[6 * (size_t)blockIdx.x + 2] = ((red[0] + red[1]) + (red[2] + red[3])) / N;
+}
+
+void launch_tile_order_sum(const double* order, int n, double N, double* out, int steps, hipStream_t s) {
+    if (steps <= 0) return;
+    k_tile_order_sum<<<steps, 256, 0, s>>>(order, n, N, out);
+    check_hip(hipGetLastError(), "order-parameter sum launch");
+}
+
+template void launch_tile_states<float>(const Lat<float>&, const float*, const float*, bool, float*, const TilePlan&,
+                                        int, uint64_t, hipStream_t);
+template void launch_tile_states<double>(const Lat<double>&, const double*, const double*, bool, double*,
+                                         const TilePlan&, int, uint64_t, hipStream_t);
+template void launch_tile_order<float>(const Lat<float>&, const float*, const float*, float*, float*, double*,
+                                       const TilePlan&, int, uint64_t, hipStream_t);
+template void launch_tile_order<double>(const Lat<double>&, const double*, const double*, double*, double*, double*,
+                                        const TilePlan&, int, uint64_t, hipStream_t);
 template void launch_tile<float>(const Lat<float>&, const float*, const float*, float*, float*, const TilePlan&, int,
                                  uint64_t, hipStream_t);
 template void launch_tile<double>(const Lat<double>&, const double*, const double*, double*, double*, const TilePlan&,

@@ -94,4 +94,33 @@ template <typename R>
 void launch_tile(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, const TilePlan& p, int T,
                  uint64_t k, hipStream_t s);
 
+// The same, storing every state (XY): the one after the launch's step j at
+// states + 2 j N (angles, then velocities), with `first` also the one it
+// starts from, before it.
+template <typename R>
+void launch_tile_states(const Lat<R>& v, const R* th_in, const R* u_in, bool first, R* states, const TilePlan& p,
+                        int T, uint64_t k, hipStream_t s);
+// The same as launch_tile, also summing the staggered order parameter of every
+// state that a step starts from (XY): order[j] has tile_order_parts(p) partial
+// sums of the launch's step j.  launch_tile_order_sum adds those of `steps`
+// steps up: out[6 j + 2] = sum / N.
+inline int tile_order_parts(const TilePlan& p) { return p.ntx * p.nty * (p.threads / kWave); }
+template <typename R>
+void launch_tile_order(const Lat<R>& v, const R* th_in, const R* u_in, R* th_out, R* u_out, double* order,
+                       const TilePlan& p, int T, uint64_t k, hipStream_t s);
+void launch_tile_order_sum(const double* order, int n, double N, double* out, int steps, hipStream_t s);
+
+// Checks a plan against what the kernels assume; the LDS of T steps with
+// `tables` numbers per site.
+size_t tile_check(int Lx, int Ly, bool f64, const TilePlan& p, int T, int tables);
+// Reverse steps k + T - 1 .. k (xyl_adjoint.hip): states as
+// launch_tile_states stores them (step k + j at states + 2 j N), (lt_in,
+// lu_in) the adjoint at k + T, (lt_out, lu_out) at k, gacc 4 per tile.
+template <typename R>
+void launch_adjoint_tile(const Lat<R>& v, const R* states, const R* lt_in, const R* lu_in, R* lt_out, R* lu_out,
+                         const double* cm, uint64_t cm_base, double* gacc, const TilePlan& p, int T, uint64_t k,
+                         hipStream_t s);
+// tile_plan for the reverse steps of the adjoint (any number of launches).
+bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan);
+
 }  // namespace xyl

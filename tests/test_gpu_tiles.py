@@ -116,3 +116,39 @@ def test_ensemble_tiles_equal_single_steps(xyl, dtype, model, sizes, budgets):
             assert ka == kb
             np.testing.assert_array_equal(ta, tb)
             np.testing.assert_array_equal(wa, wb)
+
+
+@pytest.mark.parametrize("dtype,Lx,Ly,K,nsteps,window", [
+    ("f32", 512, 300, 50, 123, 60),     # an odd window tail, a short last segment
+    ("f32", 64, 64, 7, 50, 50),         # the window spans every step
+    ("f32", 4, 5, 3, 10, 1),            # the smallest rows, the last state alone in the window
+    ("f32", 1028, 40, 1, 6, 3),         # segments of one step (no tiles)
+    ("f64", 132, 37, 25, 76, 20),       # a last segment of one step
+    ("f64", 512, 64, 40, 80, 30),
+])
+def test_reverse_tiles_equal_single_reverse_steps(xyl, dtype, Lx, Ly, K, nsteps, window):
+    """Several reverse and recompute steps per launch on tiles against single
+    ones: the state adjoints bit for bit, the parameter gradients up to the
+    order of their sums; and the loss window summed on tiles against the
+    single steps' samples, to FP64 rounding of sums over the sites."""
+    say("reverse tiles", dtype, Lx, Ly, K, nsteps, window)
+    spec = dict(Jx=1.0, Jy=-0.2, h=0.4, gamma=0.8, dt=0.02, schedule=[(0, 1.1), (nsteps, 0.4)], seed=5, replica=3)
+    out = []
+    for fusion, adj in ((1, 1), (2, 1), (2, 2)):
+        lat = xyl.Lattice(Lx, Ly, dtype=dtype, **spec)
+        lat.set_fusion(fusion)
+        lat.set_adjoint_fusion(adj)
+        lat.init_random()
+        lat.step(5)
+        L = lat.adjoint_forward(nsteps, K, window)
+        out.append((L,) + lat.adjoint_backward() + (lat.get_state(),))
+        lat.close()
+    for a in (out[0][4], out[1][4]):
+        np.testing.assert_array_equal(a[0], out[2][4][0])
+        np.testing.assert_array_equal(a[1], out[2][4][1])
+    assert abs(out[0][0] - out[2][0]) <= 1e-12 * max(out[0][0], 1e-4)
+    assert out[1][0] == out[2][0]
+    np.testing.assert_array_equal(out[1][2], out[2][2])
+    np.testing.assert_array_equal(out[1][3], out[2][3])
+    np.testing.assert_allclose(out[2][1], out[1][1], rtol=1e-5 if dtype == "f32" else 1e-12,
+                               atol=1e-9 * np.abs(out[1][1]).max())
