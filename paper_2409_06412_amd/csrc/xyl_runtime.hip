@@ -615,7 +615,9 @@ static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
     if (it == h->tile_plans.end()) {
         TilePlan p;
         double us = 0.0;
-        if (!tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
+        // (tiles reach 4.7e5 sites per us at best)
+        const bool hopeless = !h->tiles_tuned && (double)h->N > 4.8e5 * lattice_untiled_us(h);
+        if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
             (!h->tiles_tuned && us > lattice_untiled_us(h)))
             p = TilePlan();
         if (p.T) {

@@ -261,13 +261,19 @@ static bool tile_search(const TileCost* costs, int tables, bool pairs, int max_l
             if (t < T && T > 2) continue;                // as a smaller T
             if (t > Lx || t > Ly) continue;
             int last_w = 0;
-            for (int ntx = 1; ntx <= quads && ntx <= 256; ++ntx) {
+            for (int ntx = 1; ntx <= quads && ntx <= 256; ntx += std::max(1, ntx / 8)) {
                 const int w = tile_max_w(Lx, ntx);
                 if (w == last_w) continue;               // more tiles of the same width
                 last_w = w;
                 const int W = tile_region_w(Lx, w, t);
                 if (W != Lx && (W - w) / 2 > Lx) continue;
-                for (int per = 1; per <= 64; per += std::max(1, per / 6)) {
+                // the tallest region that fits, hence the fewest tiles; more
+                // than about twice as many only add halo
+                const long rows = std::min<long>((long)max_lanes * c.S / W, (long)(kTileMaxLds / (tables * es * (size_t)W)));
+                const long h_most = rows >= Ly ? Ly : rows - 2 * t;
+                if (h_most < 1) continue;
+                const int per0 = (int)std::max<long>(1, ((Ly + h_most - 1) / h_most) * ntx / cus);
+                for (int per = per0; per <= 2 * per0 + 2; per += std::max(1, per / 6)) {
                     const int nty = std::min(Ly, std::max(1, per * cus / ntx));
                     const int h = tile_max_h(Ly, nty), H = tile_region_h(Ly, h, t);
                     const long lanes = (long)(W / c.S) * H;
