@@ -335,6 +335,7 @@ struct xyl_lattice {
     // device scratch
     DevBuf<uint64_t> kdev;
     DevBuf<double> part;
+    DevBuf<double> samples;       // partial sums of the samples of a call, reduced together
     DevBuf<double> obs;
     PinnedBuf<double> obs_host;   // host landing place of the samples' copy
     DevBuf<double> dscratch;
@@ -439,8 +440,9 @@ static void destroy_graph(xyl_lattice* h) {
 }
 
 template <typename R>
-static void lattice_launch_one(xyl_lattice* h, int mode) {
+static void lattice_launch_one(xyl_lattice* h, int mode, double* part = nullptr) {
     Lat<R> v = h->view<R>();
+    if (part) v.part = part;
     const Launch& l = (mode == kMeasure && h->mlaunch_tuned) ? h->mlaunch : h->launch;
     launch_step<R>(v, mode, l, nullptr, h->k, h->stream);
 }
@@ -776,10 +778,12 @@ static void lattice_steps(xyl_lattice* h, uint64_t n) {
     lattice_steps_mode<R>(h, n, kStore, nullptr, 0, 0);
 }
 
+// Observables of the current step into obs_dev; with `part` only their partial
+// sums there.
 template <typename R>
-static void lattice_measure_into(xyl_lattice* h, bool advance, double* obs_dev) {
-    lattice_launch_one<R>(h, advance ? (kStore | kMeasure) : kMeasure);
-    launch_finalize_obs(h->part.p, h->nrowparts(), (double)h->N, obs_dev, h->stream);
+static void lattice_measure_into(xyl_lattice* h, bool advance, double* obs_dev, double* part = nullptr) {
+    lattice_launch_one<R>(h, advance ? (kStore | kMeasure) : kMeasure, part);
+    if (!part) launch_finalize_obs(h->part.p, h->nrowparts(), (double)h->N, obs_dev, h->stream);
     if (advance) {
         h->k += 1;
         h->counter_valid = false;
@@ -792,13 +796,13 @@ static void lattice_measure_into(xyl_lattice* h, bool advance, double* obs_dev) 
 // a measured step) and every step of the span goes through the two-step
 // passes; otherwise the measured step advances one step and the rest follow.
 template <typename R>
-static void lattice_sample_and_advance(xyl_lattice* h, uint64_t span, double* obs_dev) {
+static void lattice_sample_and_advance(xyl_lattice* h, uint64_t span, double* obs_dev, double* part) {
     if ((span >= 4 && step2_eligible(h)) || lattice_tile_plan(h, span)) {
-        lattice_measure_into<R>(h, false, obs_dev);
+        lattice_measure_into<R>(h, false, obs_dev, part);
         lattice_steps<R>(h, span);
         return;
     }
-    lattice_measure_into<R>(h, true, obs_dev);
+    lattice_measure_into<R>(h, true, obs_dev, part);
     lattice_steps<R>(h, span - 1);
 }
 
@@ -1235,18 +1239,34 @@ int xyl_step_measured(xyl_lattice* h, uint64_t nsteps, uint64_t every, xyl_obs* 
         DeviceGuard g(h->device);
         h->obs.reserve(6 * ns);
         h->obs_host.reserve(6 * ns);
+        // Where one workgroup reduces a sample (a 3.6 us launch each), the
+        // partial sums of up to kSampleBatch samples wait for one launch that
+        // reduces them all, one workgroup each (the same sums).
+        constexpr uint64_t kSampleBatch = 64;
+        const size_t stride = (size_t)h->nrowparts() * kNPart;
+        const uint64_t batch = h->nrowparts() <= kFinalizeSplit && ns > 1 ? std::min<uint64_t>(ns, kSampleBatch) : 0;
+        if (batch) h->samples.reserve(batch * stride);
         for (uint64_t j = 0; j < ns; ++j) {
             double* o = h->obs.p + 6 * j;
+            double* part = batch ? h->samples.p + (j % batch) * stride : nullptr;
+            if (batch && j && j % batch == 0)
+                launch_finalize_many(h->samples.p, h->nrowparts(), stride, (double)h->N, o - 6 * batch, (int)batch,
+                                     h->stream);
             if (j * every == nsteps) {
                 // a sample at the last step: measured without stepping
-                if (h->dtype == XYL_F64) lattice_measure_into<double>(h, false, o);
-                else lattice_measure_into<float>(h, false, o);
+                if (h->dtype == XYL_F64) lattice_measure_into<double>(h, false, o, part);
+                else lattice_measure_into<float>(h, false, o, part);
             } else {
                 // up to the next sample, or to the end (nsteps not a multiple of every)
                 const uint64_t span = std::min<uint64_t>(every, nsteps - j * every);
-                if (h->dtype == XYL_F64) lattice_sample_and_advance<double>(h, span, o);
-                else lattice_sample_and_advance<float>(h, span, o);
+                if (h->dtype == XYL_F64) lattice_sample_and_advance<double>(h, span, o, part);
+                else lattice_sample_and_advance<float>(h, span, o, part);
             }
+        }
+        if (batch) {
+            const uint64_t last = (ns - 1) % batch + 1;
+            launch_finalize_many(h->samples.p, h->nrowparts(), stride, (double)h->N, h->obs.p + 6 * (ns - last),
+                                 (int)last, h->stream);
         }
         check_hip(hipMemcpyAsync(h->obs_host.p, h->obs.p, sizeof(double) * 6 * ns, hipMemcpyDeviceToHost, h->stream),
                   "D2H");
