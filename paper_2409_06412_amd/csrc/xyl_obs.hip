@@ -5,6 +5,7 @@
 #include "xyl_device.hpp"
 #include "xyl_domains.hpp"
 #include "xyl_obs.hpp"
+#include "xyl_sincos.hpp"
 
 namespace xyl {
 
@@ -45,53 +46,46 @@ __global__ __launch_bounds__(256) void k_corr_lines(const R* __restrict__ th, in
     }
 }
 
-// Sum of the per-line rows part[l][0..rmax] over the lines, in two passes of
-// fixed order: chunks of kLineChunk lines are summed in parallel (thread r of
-// chunk c writes its sum into column r of the chunk's first row, which only it
-// touches), then the chunk sums are added in chunk order.
-constexpr int kLineChunk = 64;
-
-__global__ void k_line_sum_chunks(double* __restrict__ part, int nlines, int rmax) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > rmax) return;
-    const int l0 = blockIdx.y * kLineChunk;
-    const int l1 = min(l0 + kLineChunk, nlines);
+// Sum of the rows part[l][0..rmax], l < nrows, over l, divided by N: a
+// workgroup takes 16 columns and its 16 thread rows every 16th row (128-B
+// reads), then a fixed tree adds the 16 partial sums of a column.  One launch
+// of 4 us for 512 rows of 1025 (before: chunk sums and their sum, two of 5).
+__global__ __launch_bounds__(256) void k_row_sum(const double* __restrict__ part, int nrows, int rmax, double N,
+                                                 double* __restrict__ out) {
+    __shared__ double red[16][17];
+    const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int r = blockIdx.x * 16 + c;
     double acc = 0.0;
-    // unrolled so that the loads are in flight together; the sum keeps line order
-#pragma unroll 16
-    for (int l = l0; l < l1; ++l) acc += part[(size_t)l * (rmax + 1) + r];
-    part[(size_t)l0 * (rmax + 1) + r] = acc;
+    if (r <= rmax) {
+#pragma unroll 8
+        for (int l = g; l < nrows; l += 16) acc += part[(size_t)l * (rmax + 1) + r];
+    }
+    red[g][c] = acc;
+    __syncthreads();
+    for (int w = 8; w >= 1; w >>= 1) {
+        if (g < w) red[g][c] += red[g + w][c];
+        __syncthreads();
+    }
+    if (g == 0 && r <= rmax) out[r] = red[0][c] / N;
 }
 
-__global__ void k_corr_sum(const double* __restrict__ part, int nlines, int rmax, double N, double* __restrict__ out) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > rmax) return;
-    double acc = 0.0;
-#pragma unroll 16
-    for (int l = 0; l < nlines; l += kLineChunk) acc += part[(size_t)l * (rmax + 1) + r];
-    out[r] = acc / N;
+static void launch_row_sum(const double* part, int nrows, int rmax, double N, double* out, hipStream_t s) {
+    k_row_sum<<<rmax / 16 + 1, 256, 0, s>>>(part, nrows, rmax, N, out);
+    check_hip(hipGetLastError(), "row sum launch");
 }
 
-static void launch_line_sum(double* part, int nlines, int rmax, double N, double* out, hipStream_t s) {
-    const dim3 g1((rmax + 256) / 256, (nlines + kLineChunk - 1) / kLineChunk);
-    k_line_sum_chunks<<<g1, 256, 0, s>>>(part, nlines, rmax);
-    check_hip(hipGetLastError(), "line sum launch");
-    k_corr_sum<<<(rmax + 256) / 256, 256, 0, s>>>(part, nlines, rmax, N, out);
-    check_hip(hipGetLastError(), "line sum launch");
-}
-
-// C(r) from the structure factor of a power-of-two axis (App. C: C and S are
-// a Fourier pair along the axis): C(r) = (1/L) sum_{k<L} S(k) cos(2 pi k r / L)
-// with S(L - k) = S(k), i.e. (1/L) [S(0) + (-1)^r S(L/2) + 2 sum_{0<k<L/2}
-// S(k) cos(2 pi k r / L)].  One workgroup per r sums in a fixed order (strided
+// C(r) from the structure factor of an axis that goes through the transform
+// (App. C: C and S are a Fourier pair along the axis): C(r) = (1/L) sum_{k<L}
+// S(k) cos(2 pi k r / L) with S(L - k) = S(k), i.e. (1/L) [S(0) + (even L)
+// (-1)^r S(L/2) + 2 sum_{0<k<L/2} S(k) cos(2 pi k r / L)].  One workgroup per r sums in a fixed order (strided
 // partial sums, then a fixed tree); cos from the twiddle table tw.
 __global__ __launch_bounds__(256) void k_corr_from_sf(const double* __restrict__ S, const double2* __restrict__ tw,
                                                       int L, double* __restrict__ out) {
     __shared__ double red[256];
     const int r = blockIdx.x;
-    const int h = L / 2;
+    const int h = (L + 1) / 2;
     double acc = 0.0;
-    for (int k = 1 + (int)threadIdx.x; k < h; k += blockDim.x) acc += S[k] * tw[(k * r) & (L - 1)].x;
+    for (int k = 1 + (int)threadIdx.x; k < h; k += blockDim.x) acc += S[k] * tw[(unsigned)(k * r) % (unsigned)L].x;
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = blockDim.x / 2; w > 0; w >>= 1) {
@@ -99,30 +93,27 @@ __global__ __launch_bounds__(256) void k_corr_from_sf(const double* __restrict__
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const double last = L >= 2 ? ((r & 1) ? -S[h] : S[h]) : 0.0;
+        const double last = L % 2 == 0 ? ((r & 1) ? -S[h] : S[h]) : 0.0;
         out[r] = (S[0] + last + 2.0 * red[0]) / (double)L;
     }
 }
 
 template <typename R>
-void launch_correlation(const R* th, int Lx, int Ly, int sx, int sy, int model, int axis, int rmax, double* part,
-                        double* out, hipStream_t s) {
+void launch_correlation(const R* th, int Lx, int Ly, int sx, int sy, int model, int axis, int rmax, const double* tw,
+                        double* scratch, double* out, hipStream_t s) {
     const int nlines = axis == 0 ? Ly : Lx;
     const int L = axis == 0 ? Lx : Ly;
-    if ((L & (L - 1)) == 0) {
-        const size_t N = (size_t)Lx * Ly;
-        double* z = part;
-        double* spart = part + 2 * (N + (size_t)L);
-        double* S = spart + (size_t)nlines * (L / 2 + 1);
-        launch_structure_factor<R>(th, Lx, Ly, sx, sy, model, axis, L / 2, z, spart, S, s);
-        k_corr_from_sf<<<rmax + 1, 256, 0, s>>>(S, reinterpret_cast<const double2*>(z) + N, L, out);
+    if (sf_smooth(L)) {
+        double* S = scratch + structure_factor_scratch(Lx, Ly, axis, L / 2);
+        launch_structure_factor<R>(th, Lx, Ly, sx, sy, model, axis, L / 2, tw, scratch, S, s);
+        k_corr_from_sf<<<rmax + 1, 256, 0, s>>>(S, reinterpret_cast<const double2*>(tw), L, out);
         check_hip(hipGetLastError(), "correlation kernel launch");
         return;
     }
     const size_t lds = 2 * sizeof(double) * (size_t)L;
-    k_corr_lines<R><<<nlines, 256, lds, s>>>(th, Lx, Ly, sx, sy, model == kModelSI ? 2.0 : 1.0, axis, rmax, part);
+    k_corr_lines<R><<<nlines, 256, lds, s>>>(th, Lx, Ly, sx, sy, model == kModelSI ? 2.0 : 1.0, axis, rmax, scratch);
     check_hip(hipGetLastError(), "correlation kernel launch");
-    launch_line_sum(part, nlines, rmax, (double)Lx * (double)Ly, out, s);
+    launch_row_sum(scratch, nlines, rmax, (double)Lx * (double)Ly, out, s);
 }
 
 // ------------------------------------------------- structure factor
@@ -132,12 +123,10 @@ void launch_correlation(const R* th, int Lx, int Ly, int sx, int sy, int model, 
 // line's two real rotor components are packed as one complex sequence
 // z = eps (cos q th + i sin q th), whose transform Z gives
 // sum_kappa |s~^kappa_k|^2 = (|Z_k|^2 + |Z_{L-k}|^2) / 2.
-// Pass 1 writes z line-major (rows as they are; columns through a 32 x 32
-// LDS transpose), pass 2 transforms one line per workgroup in LDS (Stockham
-// passes of radix 16 for power-of-two L, a direct sum otherwise), pass 3
-// sums the lines in a fixed order (launch_line_sum).  Power-of-two rows skip
-// pass 1: the transform computes their rotors as it reads them.  zbuf holds
-// N + L complex values: the lines, then the twiddle table.
+// Lengths with no prime factor above 7 go through k_sf_lines (below), others
+// through the direct sum k_sf_direct on the rotors z, written line-major first
+// (rows as they are; columns through a 32 x 32 LDS transpose).  Either way the
+// lines' spectra are added by launch_row_sum.
 template <typename R>
 __global__ __launch_bounds__(256) void k_rotor_rows(const R* __restrict__ th, int Lx, int Ly, int sx, int sy,
                                                     double q, double2* __restrict__ z) {
@@ -191,9 +180,12 @@ __global__ void k_sf_twiddles(double2* __restrict__ tw, int L) {
     }
 }
 
-// LDS slot of element i: one 16-B pad after every 16 elements, so that the
-// strided stores of the early passes spread over the banks.
-__device__ __forceinline__ int sf_slot(int i) { return i + (i >> 4); }
+// LDS slot of point i of a line: one 16-B pad after every 16 points, so that
+// the strided stores of the early passes spread over the banks.
+__host__ __device__ __forceinline__ int sf_slot(int i) { return i + (i >> 4); }
+__host__ __device__ __forceinline__ int sf_pitch(int L) { return sf_slot(L) + 1; }
+constexpr int kSfPoints = 4096;    // points of the lines that a workgroup transforms at a time
+constexpr int kSfThreads = 512;
 
 constexpr int bit_reverse_c(int q, int bits) {
     int r = 0;
@@ -202,140 +194,248 @@ constexpr int bit_reverse_c(int q, int bits) {
 }
 constexpr int log2_c(int n) { return n <= 1 ? 0 : 1 + log2_c(n / 2); }
 
-// R-point DFT in registers, natural order in and out: radix-2 decimation in
+// v exp(-2 pi i m / 8), m < 4
+__device__ __forceinline__ double2 turn8(double2 v, int m) {
+    constexpr double h = 0.70710678118654752440;
+    if (m == 1) return make_double2(h * (v.x + v.y), h * (v.y - v.x));
+    if (m == 2) return make_double2(v.y, -v.x);
+    if (m == 3) return make_double2(h * (v.y - v.x), -h * (v.x + v.y));
+    return v;
+}
+
+// R-point DFT in registers, natural order in and out: R = 3, 5, 7 by the
+// definition (w_R^m = tw[m L / R]); 2, 4, 8 by radix-2 decimation in
 // frequency (its result comes out bit-reversed and is read back through the
-// bit reversal).  w_R^m = tw[m L / R].
+// bit reversal).
 template <int R>
 __device__ __forceinline__ void dft_regs(double2 v[R], const double2* __restrict__ tw, int L) {
+    double2 t[R];
+    if constexpr (R == 3 || R == 5 || R == 7) {
+        // V_q and V_{R-q} = A +- i B with A = v_0 + sum_r (v_r + v_{R-r}) Re w^(q r),
+        // B = sum_r (v_r - v_{R-r}) Im w^(q r), r = 1 .. (R-1)/2
+        constexpr int H = (R - 1) / 2;
+        t[0] = v[0];
 #pragma unroll
-    for (int span = R / 2; span >= 1; span >>= 1) {
+        for (int r = 1; r <= H; ++r) {
+            const double2 a = cadd(v[r], v[R - r]), b = csub(v[r], v[R - r]);
+            t[0] = cadd(t[0], a);
+            v[r] = a;
+            v[R - r] = b;
+        }
 #pragma unroll
-        for (int i0 = 0; i0 < R; i0 += 2 * span) {
+        for (int q = 1; q <= H; ++q) {
+            double2 A = v[0], B = make_double2(0.0, 0.0);
 #pragma unroll
-            for (int j = 0; j < span; ++j) {
-                const double2 a = v[i0 + j], b = v[i0 + j + span];
-                v[i0 + j] = cadd(a, b);
-                // w_{2 span}^j = exp(-2 pi i j / (2 span)) = tw[j L / (2 span)]
-                v[i0 + j + span] = j == 0 ? csub(a, b) : cmul(csub(a, b), tw[j * (L / (2 * span))]);
+            for (int r = 1; r <= H; ++r) {
+                const double2 w = tw[(q * r) % R * (L / R)];
+                A.x += v[r].x * w.x;
+                A.y += v[r].y * w.x;
+                B.x += v[R - r].x * w.y;
+                B.y += v[R - r].y * w.y;
+            }
+            t[q] = make_double2(A.x - B.y, A.y + B.x);
+            t[R - q] = make_double2(A.x + B.y, A.y - B.x);
+        }
+    } else {
+#pragma unroll
+        for (int span = R / 2; span >= 1; span >>= 1) {
+#pragma unroll
+            for (int i0 = 0; i0 < R; i0 += 2 * span) {
+#pragma unroll
+                for (int j = 0; j < span; ++j) {
+                    const double2 a = v[i0 + j], b = v[i0 + j + span];
+                    v[i0 + j] = cadd(a, b);
+                    v[i0 + j + span] = turn8(csub(a, b), j * (4 / span));
+                }
             }
         }
-    }
-    double2 t[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) t[q] = v[bit_reverse_c(q, log2_c(R))];
+        for (int q = 0; q < R; ++q) t[q] = v[bit_reverse_c(q, log2_c(R))];
+    }
 #pragma unroll
     for (int q = 0; q < R; ++q) v[q] = t[q];
 }
 
-// One Stockham pass of radix R over a line of L points held in LDS (or, for
-// the first pass, produced by `first`), with Ns the product of the radices of
-// the passes before it: group j (of L / R) takes the points j + r L / R,
-// multiplies point r by w^(r (j mod Ns)) with w = exp(-2 pi i / (Ns R)), takes
-// their R-point DFT and stores output q at (j - j mod Ns) R + j mod Ns + q Ns.
-// After the last pass the line holds its transform in natural order.  Every
-// group of the pass is loaded before any is stored (L / R <= blockDim.x), so
-// the pass runs in place.
-template <int R, typename Src>
-__device__ __forceinline__ void sf_pass(const Src& first, double2* buf, const double2* __restrict__ tw, int L,
-                                        int Ns) {
-    const int G = L / R;
-    const int j = threadIdx.x;
-    const bool act = j < G;
-    double2 v[R];
-    if (act) {
+// t / d for t < 2^20 with inv = 1 / d good to a few ulp: (t + 1/2) / d is half
+// of 1 / d or more away from a whole number, its error below 2^-21 of itself.
+__device__ __forceinline__ int small_div(int t, float inv) { return (int)(((float)t + 0.5f) * inv); }
+
+// One Stockham pass of radix R over nl lines of L points held in LDS, with Ns
+// the product of the radices of the passes before it: group j (of G = L / R)
+// of a line takes the points j + r G, multiplies point r by w^(r (j mod Ns))
+// with w = exp(-2 pi i / (Ns R)), takes their R-point DFT and stores output q
+// at (j - j mod Ns) R + j mod Ns + q Ns.  After the last pass a line holds its
+// transform in natural order.  Every group of the pass is loaded before any is
+// stored, so the pass runs in place; a thread has up to K groups.
+template <int R>
+__device__ __forceinline__ void sf_pass(double2* buf, const double2* __restrict__ tw, int L, int nl, int Ns) {
+    constexpr int K = (kSfPoints / R + kSfThreads - 1) / kSfThreads;
+    const int G = L / R, total = nl * G, pitch = sf_pitch(L);
+    const float inv_G = 1.0f / (float)G, inv_Ns = 1.0f / (float)Ns;
+    double2 v[K][R];
+    int base[K], out[K];
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = Ns == 1 ? first(j + r * G) : buf[sf_slot(j + r * G)];
-        if (Ns > 1) {
-            // w^r for r = 1 .. R-1 from one table load: w^2 = w w, w^3 = w^2 w, ...
-            const double2 w1 = tw[(j & (Ns - 1)) * (L / (Ns * R))];
-            double2 w = w1;
+    for (int g = 0; g < K; ++g) {
+        const int t = (int)threadIdx.x + g * kSfThreads;
+        if (t < total) {
+            const int line = small_div(t, inv_G), j = t - line * G, k = j - small_div(j, inv_Ns) * Ns;
+            out[g] = (j - k) * R + k;
+            double2* b = buf + line * pitch;
+            base[g] = line * pitch;
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                v[r] = cmul(v[r], w);
-                w = cmul(w, w1);
+            for (int r = 0; r < R; ++r) v[g][r] = b[sf_slot(j + r * G)];
+            if (Ns > 1) {
+                // w^r for r = 1 .. R-1 from one table load: w^2 = w w, ...
+                const double2 w1 = tw[k * (L / (Ns * R))];
+                double2 w = w1;
+#pragma unroll
+                for (int r = 1; r < R; ++r) {
+                    v[g][r] = cmul(v[g][r], w);
+                    if (r + 1 < R) w = cmul(w, w1);
+                }
+            }
+            dft_regs<R>(v[g], tw, L);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < K; ++g) {
+        const int t = (int)threadIdx.x + g * kSfThreads;
+        if (t < total) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) buf[base[g] + sf_slot(out[g] + q * Ns)] = v[g][q];
+        }
+    }
+    __syncthreads();
+}
+
+// The spectra of lines of L points (at most 4096, no prime factor above 7),
+// straight from the angles: a workgroup takes nlb lines at a time, as many as
+// kSfPoints points hold, transforms them in LDS (Stockham passes of radix 8
+// and what is left of L), and adds their |.|^2 over all its batches in
+// registers, thread t those of k = t mod (kmax + 1), .. and the lines of
+// sub-row t / (kmax + 1); one row of sums per workgroup and sub-row.
+// Bound by the FP64 sine, cosine and butterflies (some 120 operations a site)
+// and the LDS passes, not by the 4 bytes a site it reads.  2048^2, one axis,
+// all k: 38 us rows, 41 us columns, then 5 us for the sum (before: a line per
+// workgroup with the general sincos, 61 us, columns through a transposed field
+// of rotors, 18 + 32 us, and every line's spectrum written and summed, 10 us;
+// 384 x 360, which then took the direct sum: 10 us against 32).
+template <typename R, int AXIS, bool SEVEN>
+__global__ __launch_bounds__(kSfThreads, SEVEN ? 2 : 4)
+void k_sf_lines(const R* __restrict__ th, int Lx, int sx, int sy, double q, const double2* __restrict__ tw, int L,
+                int nlines, int nlb, int kmax, int nsub, double* __restrict__ part) {
+    extern __shared__ double2 sm[];
+    constexpr int kAcc = (kSfPoints / 2 + 1 + kSfThreads - 1) / kSfThreads;
+    double acc[kAcc];
+#pragma unroll
+    for (int a = 0; a < kAcc; ++a) acc[a] = 0.0;
+    const int pitch = sf_pitch(L);
+    const int nk = kmax + 1;
+    const int sub = nsub > 1 ? (int)threadIdx.x / nk : 0;
+    const int k0 = nsub > 1 ? (int)threadIdx.x - sub * nk : (int)threadIdx.x;
+    // columns: the workgroups of an XCD (every eighth) take neighbouring lines,
+    // which share cache lines
+    const int lb = AXIS == 1 && gridDim.x % 8 == 0 ? (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3))
+                                                   : (int)blockIdx.x;
+    for (int l0 = lb * nlb; l0 < nlines; l0 += (int)gridDim.x * nlb) {
+        const int nl = min(nlb, nlines - l0);
+        // the staggered rotors, all of a thread's angles in flight at once;
+        // columns take the lines fastest across the threads, so that a row's
+        // angles are read together
+        constexpr int kPer = kSfPoints / kSfThreads;
+        const int npt = nl * L;
+        int d = AXIS == 0 ? L : nl;
+        asm volatile("" : "+s"(d));   // opaque, as in the passes below
+        const float inv_d = 1.0f / (float)d;
+        R ang[kPer];
+#pragma unroll
+        for (int g = 0; g < kPer; ++g) {
+            const int t = (int)threadIdx.x + g * kSfThreads;
+            const int a = small_div(t, inv_d), b = t - a * d;
+            if (t < npt) ang[g] = AXIS == 0 ? th[(size_t)l0 * Lx + t] : th[(size_t)a * Lx + l0 + b];
+        }
+        bool wild = false;
+#pragma unroll
+        for (int g = 0; g < kPer; ++g) {
+            const int t = (int)threadIdx.x + g * kSfThreads;
+            const int a = small_div(t, inv_d), b = t - a * d;
+            if (t < npt) {
+                const double x = q * (double)ang[g];
+                double sn, cs;
+                sincos_reduced(x, sn, cs);
+                wild |= !sincos_reducible(x);
+                const bool odd = AXIS == 0 ? (b * sx + (l0 + a) * sy) & 1 : ((l0 + b) * sx + a * sy) & 1;
+                const int slot = AXIS == 0 ? a * pitch + sf_slot(b) : b * pitch + sf_slot(a);
+                sm[slot] = odd ? make_double2(-cs, -sn) : make_double2(cs, sn);
+            }
+            if (g & 1) __builtin_amdgcn_sched_barrier(0);   // two at a time: more would spill
+        }
+        if (wild) {
+            // angles that no stepping leaves (a caller's own state)
+            for (int t = (int)threadIdx.x; t < npt; t += kSfThreads) {
+                const int a = small_div(t, inv_d), b = t - a * d;
+                const double x = q * (double)(AXIS == 0 ? th[(size_t)l0 * Lx + t] : th[(size_t)a * Lx + l0 + b]);
+                if (sincos_reducible(x)) continue;
+                const bool odd = AXIS == 0 ? (b * sx + (l0 + a) * sy) & 1 : ((l0 + b) * sx + a * sy) & 1;
+                const int slot = AXIS == 0 ? a * pitch + sf_slot(b) : b * pitch + sf_slot(a);
+                const double2 z = sincos_general(x);
+                sm[slot] = odd ? make_double2(-z.x, -z.y) : z;
             }
         }
-        dft_regs<R>(v, tw, L);
-    }
-    __syncthreads();
-    if (act) {
-        const int k = j & (Ns - 1);
-        const int base = (j - k) * R + k;
+        __syncthreads();
+        for (int Ns = 1; Ns < L;) {
+            // opaque here: the index arithmetic of all the passes, hoisted out
+            // of the loops, would spill
+            int Lv = L;
+            asm volatile("" : "+s"(Lv));
+            const int left = Lv / Ns;
+            if (left % 8 == 0) {
+                sf_pass<8>(sm, tw, Lv, nl, Ns);
+                Ns *= 8;
+            } else if (left % 4 == 0) {
+                sf_pass<4>(sm, tw, Lv, nl, Ns);
+                Ns *= 4;
+            } else if (left % 2 == 0) {
+                sf_pass<2>(sm, tw, Lv, nl, Ns);
+                Ns *= 2;
+            } else if (left % 3 == 0) {
+                sf_pass<3>(sm, tw, Lv, nl, Ns);
+                Ns *= 3;
+            } else if (left % 5 == 0) {
+                sf_pass<5>(sm, tw, Lv, nl, Ns);
+                Ns *= 5;
+            } else if constexpr (SEVEN) {
+                sf_pass<7>(sm, tw, Lv, nl, Ns);
+                Ns *= 7;
+            } else {
+                break;   // not reached
+            }
+        }
+        // sum_kappa |s~^kappa_k|^2 = (|Z_k|^2 + |Z_{L-k}|^2) / 2
+        if (sub < nsub) {
 #pragma unroll
-        for (int q = 0; q < R; ++q) buf[sf_slot(base + q * Ns)] = v[q];
+            for (int a = 0; a < kAcc; ++a) {
+                const int k = k0 + a * kSfThreads;
+                if (k > kmax || (a && nsub > 1)) break;
+                const int i = sf_slot(k), m = sf_slot(k ? L - k : 0);
+                for (int l = sub; l < nl; l += nsub) {
+                    const double2 x = sm[l * pitch + i], y = sm[l * pitch + m];
+                    acc[a] += 0.5 * (x.x * x.x + x.y * x.y + y.x * y.x + y.y * y.y);
+                }
+            }
+        }
+        __syncthreads();
     }
-    __syncthreads();
-}
-
-// The transform of one line of L = 2^n points (2 .. 4096) by one workgroup of
-// NT threads: Stockham passes of radix 16 with 256 threads, of radix 8 with
-// 512 (half the registers per thread and twice the waves per CU for the
-// 4096-point lines, whose 68 KiB of LDS allow two workgroups per CU), then
-// one of 8, 4 or 2 for the rest of n; then sum_kappa |s~^kappa_k|^2 for
-// k <= kmax into out.  Every pass has L / R <= NT groups.
-template <int NT, typename Src>
-__device__ __forceinline__ void sf_line(const Src& src, double2* sm, const double2* __restrict__ tw, int L, int kmax,
-                                        double* __restrict__ out) {
-    constexpr int RMAX = NT >= 512 ? 8 : 16;
-    int Ns = 1;
-    while (Ns < L) {
-        const int left = L / Ns;
-        if (left >= RMAX) {
-            sf_pass<RMAX>(src, sm, tw, L, Ns);
-            Ns *= RMAX;
-        } else if (left == 8) {
-            sf_pass<8>(src, sm, tw, L, Ns);
-            Ns *= 8;
-        } else if (left == 4) {
-            sf_pass<4>(src, sm, tw, L, Ns);
-            Ns *= 4;
-        } else {
-            sf_pass<2>(src, sm, tw, L, Ns);
-            Ns *= 2;
+    if (sub < nsub) {
+        double* o = part + ((size_t)blockIdx.x * nsub + sub) * nk;
+#pragma unroll
+        for (int a = 0; a < kAcc; ++a) {
+            const int k = k0 + a * kSfThreads;
+            if (k > kmax || (a && nsub > 1)) break;
+            o[k] = acc[a];
         }
     }
-    for (int k = threadIdx.x; k <= kmax; k += blockDim.x) {
-        const double2 a = sm[sf_slot(k)], b = sm[sf_slot((L - k) & (L - 1))];
-        out[k] = 0.5 * (a.x * a.x + a.y * a.y + b.x * b.x + b.y * b.y);
-    }
-}
-
-// Points of a line: complex values written by the rotor pass, or the staggered
-// rotors of one lattice row computed on the fly (the same arithmetic as
-// k_rotor_rows).
-struct ZLine {
-    const double2* z;
-    __device__ double2 operator()(int i) const { return z[i]; }
-};
-template <typename R>
-struct RotorRow {
-    const R* th;   // the row
-    int y, sx, sy;
-    double q;
-    __device__ double2 operator()(int x) const {
-        const double e = (((x * sx) + (y * sy)) & 1) ? -1.0 : 1.0;
-        double sn, cs;
-        sincos(q * (double)th[x], &sn, &cs);
-        return make_double2(e * cs, e * sn);
-    }
-};
-
-// Power-of-two lines, one per workgroup: columns from the transposed rotor
-// field z, rows straight from the angles.
-// (512 threads: at most 128 VGPRs, so that two workgroups share a CU)
-template <int NT>
-__global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_sf_fft(const double2* __restrict__ z, const double2* __restrict__ tw, int L,
-                                               int kmax, double* __restrict__ part) {
-    extern __shared__ double2 sm[];
-    sf_line<NT>(ZLine{z + (size_t)blockIdx.x * L}, sm, tw, L, kmax, part + (size_t)blockIdx.x * (kmax + 1));
-}
-template <typename R, int NT>
-__global__ __launch_bounds__(NT, NT >= 512 ? 4 : 1) void k_sf_fft_rows(const R* __restrict__ th, int sx, int sy, double q,
-                                                    const double2* __restrict__ tw, int L, int kmax,
-                                                    double* __restrict__ part) {
-    extern __shared__ double2 sm[];
-    const int y = blockIdx.x;
-    sf_line<NT>(RotorRow<R>{th + (size_t)y * L, y, sx, sy, q}, sm, tw, L, kmax, part + (size_t)y * (kmax + 1));
 }
 
 // Other lengths: the direct sum, one line per workgroup, with the full-circle
@@ -371,62 +471,52 @@ __global__ __launch_bounds__(256) void k_sf_direct(const double2* __restrict__ z
     }
 }
 
+void launch_sf_twiddles(double* tw, int L, hipStream_t s) {
+    k_sf_twiddles<<<(L + 255) / 256, 256, 0, s>>>(reinterpret_cast<double2*>(tw), L);
+    check_hip(hipGetLastError(), "twiddle kernel launch");
+}
+
 template <typename R>
-void launch_structure_factor(const R* th, int Lx, int Ly, int sx, int sy, int model, int axis, int kmax, void* zbuf,
-                             double* part, double* out, hipStream_t s) {
+void launch_structure_factor(const R* th, int Lx, int Ly, int sx, int sy, int model, int axis, int kmax,
+                             const double* tw, double* scratch, double* out, hipStream_t s) {
     const double q = model == kModelSI ? 2.0 : 1.0;
-    double2* z = static_cast<double2*>(zbuf);
     const int L = axis == 0 ? Lx : Ly;
     const int nlines = axis == 0 ? Ly : Lx;
-    const bool pow2 = (L & (L - 1)) == 0;
-    if (pow2) {
-        // rows go straight from the angles into the transform; columns are
-        // transposed into z first
-        double2* tw = z + (size_t)Lx * Ly;     // zbuf holds N + L complex values
-        k_sf_twiddles<<<(L + 255) / 256, 256, 0, s>>>(tw, L);
-        check_hip(hipGetLastError(), "twiddle kernel launch");
-        const size_t lds = sizeof(double2) * (size_t)(L + L / 16);
-        // rows of 4096 points with 512 threads (radix 8): 0.195 -> 0.174 ms per
-        // 4096^2 axis; columns, read from the transposed rotors, stay at 256
-        // (radix 16; 512 measured 4% slower there)
-        const bool wide = L >= 4096 && axis == 0;
-        if (axis == 0) {
-            const void* kf = wide ? reinterpret_cast<const void*>(k_sf_fft_rows<R, 512>)
-                                  : reinterpret_cast<const void*>(k_sf_fft_rows<R, 256>);
-            check_hip(hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                      "hipFuncSetAttribute");
-            if (wide) k_sf_fft_rows<R, 512><<<nlines, 512, lds, s>>>(th, sx, sy, q, tw, L, kmax, part);
-            else k_sf_fft_rows<R, 256><<<nlines, 256, lds, s>>>(th, sx, sy, q, tw, L, kmax, part);
-        } else {
-            const dim3 grid((Lx + 31) / 32, (Ly + 31) / 32);
-            k_rotor_cols<R><<<grid, 256, 0, s>>>(th, Lx, Ly, sx, sy, q, z);
-            check_hip(hipGetLastError(), "rotor kernel launch");
-            const void* kf = wide ? reinterpret_cast<const void*>(k_sf_fft<512>)
-                                  : reinterpret_cast<const void*>(k_sf_fft<256>);
-            check_hip(hipFuncSetAttribute(kf, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
-                      "hipFuncSetAttribute");
-            if (wide) k_sf_fft<512><<<nlines, 512, lds, s>>>(z, tw, L, kmax, part);
-            else k_sf_fft<256><<<nlines, 256, lds, s>>>(z, tw, L, kmax, part);
-        }
-        check_hip(hipGetLastError(), "structure factor kernel launch");
-    } else {
-        if (axis == 0) {
-            const size_t N = (size_t)Lx * Ly;
-            const unsigned nb = (unsigned)std::min<size_t>((N + 255) / 256, 65536);
-            k_rotor_rows<R><<<nb, 256, 0, s>>>(th, Lx, Ly, sx, sy, q, z);
-        } else {
-            const dim3 grid((Lx + 31) / 32, (Ly + 31) / 32);
-            k_rotor_cols<R><<<grid, 256, 0, s>>>(th, Lx, Ly, sx, sy, q, z);
-        }
-        check_hip(hipGetLastError(), "rotor kernel launch");
-        const size_t lds = sizeof(double2) * (size_t)(2 * L);
-        check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(k_sf_direct),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+    const double N = (double)Lx * (double)Ly;
+    if (sf_smooth(L)) {
+        const SfShape h = sf_shape(L, nlines, kmax);
+        const size_t lds = sizeof(double2) * (size_t)h.nlb * (size_t)sf_pitch(L);
+        const double2* t = reinterpret_cast<const double2*>(tw);
+        // the radix-7 pass alone needs more than 128 registers (two workgroups
+        // per CU): a kernel of its own for the lengths that have it
+        const auto kf = L % 7 == 0 ? (axis == 0 ? k_sf_lines<R, 0, true> : k_sf_lines<R, 1, true>)
+                                   : (axis == 0 ? k_sf_lines<R, 0, false> : k_sf_lines<R, 1, false>);
+        check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(kf), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)lds),
                   "hipFuncSetAttribute");
-        k_sf_direct<<<nlines, 256, lds, s>>>(z, L, kmax, part);
+        kf<<<h.grid, kSfThreads, lds, s>>>(th, Lx, sx, sy, q, t, L, nlines, h.nlb, kmax, h.nsub, scratch);
         check_hip(hipGetLastError(), "structure factor kernel launch");
+        launch_row_sum(scratch, h.grid * h.nsub, kmax, N, out, s);
+        return;
     }
-    launch_line_sum(part, nlines, kmax, (double)Lx * (double)Ly, out, s);
+    double2* z = reinterpret_cast<double2*>(scratch);
+    double* part = scratch + 2 * (size_t)Lx * Ly;
+    if (axis == 0) {
+        const size_t n = (size_t)Lx * Ly;
+        const unsigned nb = (unsigned)std::min<size_t>((n + 255) / 256, 65536);
+        k_rotor_rows<R><<<nb, 256, 0, s>>>(th, Lx, Ly, sx, sy, q, z);
+    } else {
+        const dim3 grid((Lx + 31) / 32, (Ly + 31) / 32);
+        k_rotor_cols<R><<<grid, 256, 0, s>>>(th, Lx, Ly, sx, sy, q, z);
+    }
+    check_hip(hipGetLastError(), "rotor kernel launch");
+    const size_t lds = sizeof(double2) * (size_t)(2 * L);
+    check_hip(hipFuncSetAttribute(reinterpret_cast<const void*>(k_sf_direct),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds),
+              "hipFuncSetAttribute");
+    k_sf_direct<<<nlines, 256, lds, s>>>(z, L, kmax, part);
+    check_hip(hipGetLastError(), "structure factor kernel launch");
+    launch_row_sum(part, nlines, kmax, N, out, s);
 }
 
 // -------------------------------------------------------------- domains
@@ -704,13 +794,13 @@ void launch_domains(const R* th, int Lx, int Ly, int sx, int sy, int model, int3
     check_hip(hipGetLastError(), "uf sizes launch");
 }
 
-template void launch_correlation<float>(const float*, int, int, int, int, int, int, int, double*, double*,
-                                        hipStream_t);
-template void launch_correlation<double>(const double*, int, int, int, int, int, int, int, double*, double*,
-                                         hipStream_t);
-template void launch_structure_factor<float>(const float*, int, int, int, int, int, int, int, void*, double*,
+template void launch_correlation<float>(const float*, int, int, int, int, int, int, int, const double*, double*,
+                                        double*, hipStream_t);
+template void launch_correlation<double>(const double*, int, int, int, int, int, int, int, const double*, double*,
+                                         double*, hipStream_t);
+template void launch_structure_factor<float>(const float*, int, int, int, int, int, int, int, const double*, double*,
                                              double*, hipStream_t);
-template void launch_structure_factor<double>(const double*, int, int, int, int, int, int, int, void*, double*,
+template void launch_structure_factor<double>(const double*, int, int, int, int, int, int, int, const double*, double*,
                                               double*, hipStream_t);
 template void launch_domains<float>(const float*, int, int, int, int, int, int32_t*, uint32_t*, uint32_t*, uint32_t*,
                                     hipStream_t);

@@ -144,6 +144,32 @@ struct PinnedBuf {
     ~PinnedBuf() { release(); }
 };
 
+// What a handle keeps for its structure factors and correlations: scratch, the
+// twiddle table of each axis length it has transformed (at most 64 KB each)
+// and the results' landing place.
+struct SpectrumBufs {
+    DevBuf<double> scratch;
+    std::map<int, DevBuf<double>> twiddles;
+    PinnedBuf<double> host;
+    // made, and waited for, by the first call of a length: a later call finds
+    // it complete on any stream
+    const double* table(int L, hipStream_t s) {
+        if (!sf_smooth(L)) return nullptr;
+        DevBuf<double>& t = twiddles[L];
+        if (!t.p) {
+            t.reserve(2 * (size_t)L);
+            try {
+                launch_sf_twiddles(t.p, L, s);
+                check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+            } catch (...) {
+                t.release();
+                throw;
+            }
+        }
+        return t.p;
+    }
+};
+
 // ------------------------------------------------------------ parameters
 struct Params {
     double Jx = 1.0, Jy = -0.1, h = 0.5, gamma = 1.0, dt = 0.01;
@@ -339,6 +365,7 @@ struct xyl_lattice {
     DevBuf<double> obs;
     PinnedBuf<double> obs_host;   // host landing place of the samples' copy
     DevBuf<double> dscratch;
+    SpectrumBufs spectrum;
     DevBuf<char> omega_buf;
     DevBuf<int32_t> parent;
     DevBuf<uint32_t> usz;
@@ -1368,18 +1395,21 @@ int xyl_correlation(xyl_lattice* h, int32_t axis, int32_t rmax, double* C) {
         require(C != nullptr, XYL_EINVAL, "C is NULL");
         DeviceGuard g(h->device);
         const size_t nscr = correlation_scratch(h->Lx, h->Ly, axis, rmax);
-        h->dscratch.reserve(nscr + (rmax + 1));
-        double* part = h->dscratch.p;
-        double* outd = h->dscratch.p + nscr;
+        SpectrumBufs& w = h->spectrum;
+        w.scratch.reserve(nscr + (rmax + 1));
+        w.host.reserve(rmax + 1);
+        const double* tw = w.table(L, h->stream);
+        double* outd = w.scratch.p + nscr;
         const int sx = h->p.Jx > 0.0, sy = h->p.Jy > 0.0;
         if (h->dtype == XYL_F64)
             launch_correlation<double>(static_cast<const double*>(h->cur_theta()), h->Lx, h->Ly, sx, sy, h->p.model,
-                                       axis, rmax, part, outd, h->stream);
+                                       axis, rmax, tw, w.scratch.p, outd, h->stream);
         else
             launch_correlation<float>(static_cast<const float*>(h->cur_theta()), h->Lx, h->Ly, sx, sy, h->p.model,
-                                      axis, rmax, part, outd, h->stream);
-        check_hip(hipMemcpyAsync(C, outd, sizeof(double) * (rmax + 1), hipMemcpyDeviceToHost, h->stream), "D2H");
+                                      axis, rmax, tw, w.scratch.p, outd, h->stream);
+        check_hip(hipMemcpyAsync(w.host.p, outd, sizeof(double) * (rmax + 1), hipMemcpyDeviceToHost, h->stream), "D2H");
         check_hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+        std::memcpy(C, w.host.p, sizeof(double) * (rmax + 1));
     });
 }
 
@@ -1388,19 +1418,16 @@ int xyl_correlation(xyl_lattice* h, int32_t axis, int32_t rmax, double* C) {
 // S_delta(k) of one lattice's current angles into host S[0..kmax].
 template <typename R>
 static void structure_factor_into(const void* th, int Lx, int Ly, int sx, int sy, int model, int axis, int kmax,
-                                  DevBuf<double>& scratch, hipStream_t s, double* S) {
-    const int nlines = axis == 0 ? Ly : Lx;
-    const int L = axis == 0 ? Lx : Ly;
-    const size_t N = (size_t)Lx * Ly;
-    // the lines (N complex), the twiddle table (L complex), the per-line
-    // spectra and the sum
-    scratch.reserve(2 * (N + (size_t)L) + (size_t)nlines * (kmax + 1) + (size_t)(kmax + 1));
-    double* z = scratch.p;
-    double* part = scratch.p + 2 * (N + (size_t)L);
-    double* outd = part + (size_t)nlines * (kmax + 1);
-    launch_structure_factor<R>(static_cast<const R*>(th), Lx, Ly, sx, sy, model, axis, kmax, z, part, outd, s);
-    check_hip(hipMemcpyAsync(S, outd, sizeof(double) * (kmax + 1), hipMemcpyDeviceToHost, s), "D2H");
+                                  SpectrumBufs& w, hipStream_t s, double* S) {
+    const size_t nscr = structure_factor_scratch(Lx, Ly, axis, kmax);
+    w.scratch.reserve(nscr + (kmax + 1));
+    w.host.reserve(kmax + 1);
+    const double* tw = w.table(axis == 0 ? Lx : Ly, s);
+    double* outd = w.scratch.p + nscr;
+    launch_structure_factor<R>(static_cast<const R*>(th), Lx, Ly, sx, sy, model, axis, kmax, tw, w.scratch.p, outd, s);
+    check_hip(hipMemcpyAsync(w.host.p, outd, sizeof(double) * (kmax + 1), hipMemcpyDeviceToHost, s), "D2H");
     check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+    std::memcpy(S, w.host.p, sizeof(double) * (kmax + 1));
     require_finite(S, (size_t)kmax + 1, "structure factor");
 }
 
@@ -1422,10 +1449,10 @@ int xyl_structure_factor(xyl_lattice* h, int32_t axis, int32_t kmax, double* S) 
         DeviceGuard g(h->device);
         const int sx = h->p.Jx > 0.0, sy = h->p.Jy > 0.0;
         if (h->dtype == XYL_F64)
-            structure_factor_into<double>(h->cur_theta(), h->Lx, h->Ly, sx, sy, h->p.model, axis, kmax, h->dscratch,
+            structure_factor_into<double>(h->cur_theta(), h->Lx, h->Ly, sx, sy, h->p.model, axis, kmax, h->spectrum,
                                           h->stream, S);
         else
-            structure_factor_into<float>(h->cur_theta(), h->Lx, h->Ly, sx, sy, h->p.model, axis, kmax, h->dscratch,
+            structure_factor_into<float>(h->cur_theta(), h->Lx, h->Ly, sx, sy, h->p.model, axis, kmax, h->spectrum,
                                          h->stream, S);
     });
 }
@@ -1995,7 +2022,7 @@ struct xyl_ensemble {
     DevBuf<double> obs;
     DevBuf<FinalizeJobHost> jobs;
     PinnedBuf<FinalizeJobHost> jobs_host;   // the source of each flush's copy into `jobs`
-    DevBuf<double> dscratch;
+    SpectrumBufs spectrum;
     DevBuf<char> omega_buf;
     DevBuf<int32_t> parent;
     DevBuf<uint32_t> usz, hist, stats;
@@ -3299,10 +3326,10 @@ int xyl_ensemble_structure_factor(xyl_ensemble* e, int32_t r, int32_t axis, int3
         check_hip(hipStreamSynchronize(e->side), "hipStreamSynchronize");
         const int sx = d.Jx > 0.0, sy = d.Jy > 0.0;
         if (e->dtype == XYL_F64)
-            structure_factor_into<double>(e->cur_theta(r), d.Lx, d.Ly, sx, sy, d.model, axis, kmax, e->dscratch,
+            structure_factor_into<double>(e->cur_theta(r), d.Lx, d.Ly, sx, sy, d.model, axis, kmax, e->spectrum,
                                           e->stream, S);
         else
-            structure_factor_into<float>(e->cur_theta(r), d.Lx, d.Ly, sx, sy, d.model, axis, kmax, e->dscratch,
+            structure_factor_into<float>(e->cur_theta(r), d.Lx, d.Ly, sx, sy, d.model, axis, kmax, e->spectrum,
                                          e->stream, S);
     });
 }
