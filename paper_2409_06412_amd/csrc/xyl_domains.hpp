@@ -11,7 +11,7 @@ namespace xyl {
 // launch_domains takes parent (N labels), size (N), hist (N + 1) and stats,
 // which receives the number of distinct sizes in stats[0] and the (size,
 // count) pairs, at most domain_size_cap(N) of them, from stats[kDomainPairs]
-// on; hist and stats[0] must be zero on entry.
+// on; it clears them itself.
 constexpr size_t kDomainPairs = 4;
 inline uint32_t domain_size_cap(size_t N) {
     // k distinct sizes sum to at least k (k + 1) / 2 <= N

@@ -605,54 +605,82 @@ __device__ __forceinline__ void uf_lds_union(int32_t* lab, int32_t a, int32_t b)
 // (every bond on the global atomics before).
 constexpr int kUfTile = 32;
 
+// The tile's rows as 32-bit words of spins (a wave's ballot covers two rows):
+// a site starts at the first site of its run in the row, and a run is united
+// with the row below once per stretch of equal columns, at its first one; the
+// other bonds join sites that are joined already.  At 2048^2 after a quench
+// 25 us a launch where every bond was united in LDS (49); also clears what the
+// later launches add to (size, hist, the count of sizes).
 template <typename R>
 __global__ __launch_bounds__(256) void k_uf_local(const R* __restrict__ th, int Lx, int Ly, int sx, int sy,
-                                                  int model, int ntx, int32_t* parent, uint32_t* size) {
+                                                  int model, int ntx, int32_t* parent, uint32_t* size,
+                                                  uint32_t* hist, uint32_t* stats) {
+    static_assert(kUfTile == 32, "a row per 32-bit word");
+    constexpr int kPer = kUfTile * kUfTile / 256;
     __shared__ int32_t lab[kUfTile * kUfTile];
-    __shared__ int8_t spin[kUfTile * kUfTile];
+    __shared__ uint32_t up[kUfTile];
     const int tx = (int)(blockIdx.x % (unsigned)ntx), ty = (int)(blockIdx.x / (unsigned)ntx);
     const int x0 = tx * kUfTile, y0 = ty * kUfTile;
     const int w = min(kUfTile, Lx - x0), h = min(kUfTile, Ly - y0);
-    for (int l = threadIdx.x; l < kUfTile * kUfTile; l += blockDim.x) {
-        const int ly = l / kUfTile, lx = l % kUfTile;
-        lab[l] = l;
-        spin[l] = (lx < w && ly < h) ? (int8_t)spin_of(th, Lx, x0 + lx, y0 + ly, sx, sy, model) : (int8_t)0;
+    const int lx = (int)threadIdx.x % kUfTile, r0 = (int)threadIdx.x / kUfTile;   // row r0 + 8 k of site k
+    if (blockIdx.x == 0 && threadIdx.x < kDomainPairs) stats[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) hist[0] = 0u;
+    int8_t sp[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ly = r0 + 8 * k;
+        sp[k] = (lx < w && ly < h) ? (int8_t)spin_of(th, Lx, x0 + lx, y0 + ly, sx, sy, model) : (int8_t)0;
+    }
+    uint32_t same[kPer];   // bit i: site i of the row has the spin of site i - 1
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ly = r0 + 8 * k;
+        const uint32_t m = (uint32_t)(__ballot(sp[k] > 0) >> ((threadIdx.x & 32) ? 32 : 0));
+        same[k] = ~(m ^ (m << 1)) & ~1u;
+        const uint32_t breaks = ~same[k] & (0xFFFFFFFFu >> (31 - lx));   // bit 0 is always one
+        lab[ly * kUfTile + lx] = ly * kUfTile + 31 - __clz((int)breaks);
+        if (lx == 0) up[ly] = m;
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < kUfTile * kUfTile; l += blockDim.x) {
-        const int ly = l / kUfTile, lx = l % kUfTile;
-        if (lx >= w || ly >= h) continue;
-        const int8_t s = spin[l];
-        if (lx + 1 < w && spin[l + 1] == s) uf_lds_union(lab, l, l + 1);
-        if (ly + 1 < h && spin[l + kUfTile] == s) uf_lds_union(lab, l, l + kUfTile);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ly = r0 + 8 * k;
+        if (lx >= w || ly + 1 >= h) continue;
+        const uint32_t v = ~(up[ly] ^ up[ly + 1]);          // bit i: equal to the site below
+        const uint32_t first = v & ~((v << 1) & same[k]);   // where the bond to the left does not say it too
+        if ((first >> lx) & 1u) uf_lds_union(lab, ly * kUfTile + lx, (ly + 1) * kUfTile + lx);
     }
     __syncthreads();
-    for (int l = threadIdx.x; l < kUfTile * kUfTile; l += blockDim.x) {
-        const int ly = l / kUfTile, lx = l % kUfTile;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int ly = r0 + 8 * k;
         if (lx >= w || ly >= h) continue;
-        const int32_t r = uf_lds_find(lab, l);
+        const int32_t r = uf_lds_find(lab, ly * kUfTile + lx);
         const size_t gi = (size_t)(y0 + ly) * Lx + (size_t)(x0 + lx);
         parent[gi] = (int32_t)((size_t)(y0 + r / kUfTile) * Lx + (size_t)(x0 + r % kUfTile));
         size[gi] = 0u;
+        hist[gi + 1] = 0u;
     }
 }
 
 // Bonds across tile edges: thread t < ntx Ly takes the right edge of tile
 // column t / Ly in row t % Ly (the last column's bond wraps to x = 0); the
 // next nty Lx threads take the bottom edges of the tile rows (the last row's
-// bond wraps to y = 0).
+// bond wraps to y = 0).  A bond whose four sites with the bond before it (in
+// the same pair of tiles) are alike joins what that one joins.
 template <typename R>
 __global__ void k_uf_boundary(const R* __restrict__ th, int Lx, int Ly, int sx, int sy, int model, int ntx, int nty,
                               int32_t* parent) {
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t nr = (size_t)ntx * Ly;
-    int x, y, xn, yn;
+    int x, y, xn, yn, dx = 0, dy = 0;
     if (t < nr) {
         const int tx = (int)(t / (size_t)Ly);
         y = (int)(t % (size_t)Ly);
         x = min((tx + 1) * kUfTile, Lx) - 1;
         xn = x + 1 == Lx ? 0 : x + 1;
         yn = y;
+        dy = y % kUfTile ? 1 : 0;
     } else if (t < nr + (size_t)nty * Lx) {
         const size_t u = t - nr;
         const int ty = (int)(u / (size_t)Lx);
@@ -660,11 +688,15 @@ __global__ void k_uf_boundary(const R* __restrict__ th, int Lx, int Ly, int sx, 
         y = min((ty + 1) * kUfTile, Ly) - 1;
         xn = x;
         yn = y + 1 == Ly ? 0 : y + 1;
+        dx = x % kUfTile ? 1 : 0;
     } else {
         return;
     }
-    if (spin_of(th, Lx, x, y, sx, sy, model) == spin_of(th, Lx, xn, yn, sx, sy, model))
-        uf_union(parent, (int32_t)((size_t)y * Lx + x), (int32_t)((size_t)yn * Lx + xn));
+    const int a = spin_of(th, Lx, x, y, sx, sy, model), b = spin_of(th, Lx, xn, yn, sx, sy, model);
+    const int ap = spin_of(th, Lx, x - dx, y - dy, sx, sy, model);
+    const int bp = spin_of(th, Lx, xn - dx, yn - dy, sx, sy, model);
+    if (a != b || (dx + dy && ap == a && bp == a)) return;
+    uf_union(parent, (int32_t)((size_t)y * Lx + x), (int32_t)((size_t)yn * Lx + xn));
 }
 
 // Labels and sizes per tile, after the edge merge.  Only roots had their
@@ -732,25 +764,29 @@ __global__ __launch_bounds__(256) void k_uf_flatten_tiles(int32_t* parent, uint3
     }
 }
 
-// After the flatten pass every parent is a root: histogram the cluster sizes
-// of the roots.  Each workgroup takes a contiguous chunk of sites and counts
+// After the flatten pass the sites with a size are the roots: histogram the
+// cluster sizes.  Each workgroup takes a contiguous chunk of sites and counts
 // sizes below kHistLds in LDS, flushing each nonzero bin with one atomic;
 // larger sizes (few, and spread over many bins) go to the histogram directly.
 // This keeps the many small domains from queueing on a few global addresses.
 constexpr int kHistLds = 1024;
-__global__ __launch_bounds__(256) void k_uf_finish(const int32_t* __restrict__ parent,
-                                                   const uint32_t* __restrict__ size, uint32_t* hist, size_t N) {
+__global__ __launch_bounds__(1024) void k_uf_finish(const uint32_t* __restrict__ size, uint32_t* hist, size_t N) {
     __shared__ uint32_t h[kHistLds];
     for (int b = threadIdx.x; b < kHistLds; b += blockDim.x) h[b] = 0u;
     __syncthreads();
-    const size_t chunk = (N + gridDim.x - 1) / gridDim.x;
+    // four sites per load (N is a multiple of 4)
+    const size_t nq = N / 4, chunk = (nq + gridDim.x - 1) / gridDim.x;
     const size_t i0 = (size_t)blockIdx.x * chunk;
-    const size_t i1 = i0 + chunk < N ? i0 + chunk : N;
+    const size_t i1 = i0 + chunk < nq ? i0 + chunk : nq;
+#pragma unroll 4
     for (size_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        if (parent[i] == (int32_t)i) {
-            const uint32_t sz = size[i];
-            if (sz < (uint32_t)kHistLds) atomicAdd(&h[sz], 1u);
-            else atomicAdd(hist + sz, 1u);
+        const uint4 v = reinterpret_cast<const uint4*>(size)[i];
+        const uint32_t sz[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (!sz[j]) continue;
+            if (sz[j] < (uint32_t)kHistLds) atomicAdd(&h[sz[j]], 1u);
+            else atomicAdd(hist + sz[j], 1u);
         }
     }
     __syncthreads();
@@ -781,14 +817,17 @@ void launch_domains(const R* th, int Lx, int Ly, int sx, int sy, int model, int3
     const size_t N = (size_t)Lx * Ly;
     const unsigned nb = (unsigned)((N + 255) / 256);
     const int ntx = (Lx + kUfTile - 1) / kUfTile, nty = (Ly + kUfTile - 1) / kUfTile;
-    k_uf_local<R><<<(unsigned)((size_t)ntx * nty), 256, 0, s>>>(th, Lx, Ly, sx, sy, model, ntx, parent, size);
+    k_uf_local<R><<<(unsigned)((size_t)ntx * nty), 256, 0, s>>>(th, Lx, Ly, sx, sy, model, ntx, parent, size,
+                                                                hist, stats);
     check_hip(hipGetLastError(), "uf local labelling launch");
     const size_t nbond = (size_t)ntx * Ly + (size_t)nty * Lx;
     k_uf_boundary<R><<<(unsigned)((nbond + 255) / 256), 256, 0, s>>>(th, Lx, Ly, sx, sy, model, ntx, nty, parent);
     check_hip(hipGetLastError(), "uf boundary merge launch");
     k_uf_flatten_tiles<kUfTile><<<(unsigned)((size_t)ntx * nty), 256, 0, s>>>(parent, size, Lx, Ly, ntx);
     check_hip(hipGetLastError(), "uf flatten launch");
-    k_uf_finish<<<(unsigned)std::min<size_t>(nb, 1024), 256, 0, s>>>(parent, size, hist, N);
+    // few workgroups: the flushes of one bin queue on its address (2048^2 after
+    // a quench: 256 of 1024 threads 8.6 us, 1024 of 256 threads 21 us)
+    k_uf_finish<<<(unsigned)std::min<size_t>((N + 16383) / 16384, 256), 1024, 0, s>>>(size, hist, N);
     check_hip(hipGetLastError(), "uf finish launch");
     k_uf_sizes<<<nb, 256, 0, s>>>(hist, stats, N, domain_size_cap(N));
     check_hip(hipGetLastError(), "uf sizes launch");

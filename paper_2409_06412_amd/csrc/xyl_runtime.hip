@@ -170,6 +170,13 @@ struct SpectrumBufs {
     }
 };
 
+// What a handle keeps for its domain labellings.
+struct DomainBufs {
+    DevBuf<int32_t> parent;
+    DevBuf<uint32_t> size, hist, stats;
+    PinnedBuf<uint32_t> stats_host;
+};
+
 // ------------------------------------------------------------ parameters
 struct Params {
     double Jx = 1.0, Jy = -0.1, h = 0.5, gamma = 1.0, dt = 0.01;
@@ -367,10 +374,7 @@ struct xyl_lattice {
     DevBuf<double> dscratch;
     SpectrumBufs spectrum;
     DevBuf<char> omega_buf;
-    DevBuf<int32_t> parent;
-    DevBuf<uint32_t> usz;
-    DevBuf<uint32_t> hist;
-    DevBuf<uint32_t> stats;
+    DomainBufs domains;
     DevBuf<uint32_t> flag;        // validation result of xyl_set_state_device
     DevBuf<double> phases;        // measurement phases: the x table (2 Lx), then the y table (2 Ly)
     // adjoint state (see xyl_adjoint.hip)
@@ -874,25 +878,22 @@ static void lattice_omega(xyl_lattice* h, double* omega) {
 }
 
 template <typename R>
-static void run_domains(const R* th, int Lx, int Ly, int sx, int sy, int model, DevBuf<int32_t>& parent,
-                        DevBuf<uint32_t>& usz,
-                        DevBuf<uint32_t>& hist, DevBuf<uint32_t>& stats, hipStream_t s, int32_t* labels,
-                        uint64_t* sizes, uint64_t* counts, uint64_t cap, uint64_t* n_sizes, uint64_t* n_domains,
-                        uint64_t* max_size) {
+static void run_domains(const R* th, int Lx, int Ly, int sx, int sy, int model, DomainBufs& w, hipStream_t s,
+                        int32_t* labels, uint64_t* sizes, uint64_t* counts, uint64_t cap, uint64_t* n_sizes,
+                        uint64_t* n_domains, uint64_t* max_size) {
     const size_t N = (size_t)Lx * Ly;
     const uint32_t pcap = domain_size_cap(N);
     const size_t nst = kDomainPairs + 2 * (size_t)pcap;
-    parent.reserve(N);
-    usz.reserve(N);
-    hist.reserve(N + 1);
-    stats.reserve(nst);
-    check_hip(hipMemsetAsync(hist.p, 0, sizeof(uint32_t) * (N + 1), s), "hipMemsetAsync");
-    check_hip(hipMemsetAsync(stats.p, 0, sizeof(uint32_t) * kDomainPairs, s), "hipMemsetAsync");
-    launch_domains<R>(th, Lx, Ly, sx, sy, model, parent.p, usz.p, hist.p, stats.p, s);
+    w.parent.reserve(N);
+    w.size.reserve(N);
+    w.hist.reserve(N + 1);
+    w.stats.reserve(nst);
+    w.stats_host.reserve(nst);
+    launch_domains<R>(th, Lx, Ly, sx, sy, model, w.parent.p, w.size.p, w.hist.p, w.stats.p, s);
     // the (size, count) pairs were compacted on the device: only they come back
-    std::vector<uint32_t> st(nst);
-    check_hip(hipMemcpyAsync(st.data(), stats.p, sizeof(uint32_t) * nst, hipMemcpyDeviceToHost, s), "D2H");
-    if (labels) check_hip(hipMemcpyAsync(labels, parent.p, sizeof(int32_t) * N, hipMemcpyDeviceToHost, s), "D2H");
+    const uint32_t* st = w.stats_host.p;
+    check_hip(hipMemcpyAsync(w.stats_host.p, w.stats.p, sizeof(uint32_t) * nst, hipMemcpyDeviceToHost, s), "D2H");
+    if (labels) check_hip(hipMemcpyAsync(labels, w.parent.p, sizeof(int32_t) * N, hipMemcpyDeviceToHost, s), "D2H");
     check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
     const uint64_t ns = st[0];
     require(ns >= 1 && ns <= pcap, XYL_EDEVICE, "domain size distribution overflowed its bound");
@@ -1466,12 +1467,10 @@ int xyl_domains(xyl_lattice* h, int32_t* labels, uint64_t* sizes, uint64_t* coun
         const int sx = h->p.Jx > 0.0, sy = h->p.Jy > 0.0;
         if (h->dtype == XYL_F64)
             run_domains<double>(static_cast<const double*>(h->cur_theta()), h->Lx, h->Ly, sx, sy, h->p.model,
-                                h->parent, h->usz,
-                                h->hist, h->stats, h->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
+                                h->domains, h->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
         else
             run_domains<float>(static_cast<const float*>(h->cur_theta()), h->Lx, h->Ly, sx, sy, h->p.model,
-                               h->parent, h->usz,
-                               h->hist, h->stats, h->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
+                               h->domains, h->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
     });
 }
 
@@ -1507,7 +1506,7 @@ static uint32_t* scratch_address(int dev) {
     return g_scratch_dev[dev];
 }
 
-// xyl_domains on the static scratch: zeroed by kernels (no memset), results
+// xyl_domains on the static scratch: cleared by the kernels (no memset), results
 // read back into the caller's arrays and a fixed stack buffer (no heap).
 template <typename R>
 static void domains_noalloc(xyl_lattice* h, int32_t* labels, uint64_t* sizes, uint64_t* counts, uint64_t cap,
@@ -1522,9 +1521,6 @@ static void domains_noalloc(xyl_lattice* h, int32_t* labels, uint64_t* sizes, ui
     uint32_t* usz = base + N;
     uint32_t* hist = base + 2 * N;
     uint32_t* stats = base + 3 * N + 1;
-    // the previous call's contents stay in the array: clear what must start at 0
-    launch_fill_u32(hist, N + 1, 0u, s);
-    launch_fill_u32(stats, kDomainPairs, 0u, s);
     const int sx = h->p.Jx > 0.0, sy = h->p.Jy > 0.0;
     launch_domains<R>(static_cast<const R*>(h->cur_theta()), h->Lx, h->Ly, sx, sy, h->p.model, parent, usz, hist,
                       stats, s);
@@ -2024,8 +2020,7 @@ struct xyl_ensemble {
     PinnedBuf<FinalizeJobHost> jobs_host;   // the source of each flush's copy into `jobs`
     SpectrumBufs spectrum;
     DevBuf<char> omega_buf;
-    DevBuf<int32_t> parent;
-    DevBuf<uint32_t> usz, hist, stats;
+    DomainBufs domains;
     // small FP32 replicas stepped whole-in-LDS on a second stream
     std::vector<char> lds;          // per replica: 1 = LDS path
     int lds_max_sites = 0, lds_threads = 0;
@@ -3307,13 +3302,11 @@ int xyl_ensemble_domains(xyl_ensemble* e, int32_t r, int32_t* labels, uint64_t* 
         const xyl_replica_desc& d = e->desc[r];
         const int sx = d.Jx > 0.0, sy = d.Jy > 0.0;
         if (e->dtype == XYL_F64)
-            run_domains<double>(static_cast<const double*>(e->cur_theta(r)), d.Lx, d.Ly, sx, sy, d.model, e->parent,
-                                e->usz,
-                                e->hist, e->stats, e->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
+            run_domains<double>(static_cast<const double*>(e->cur_theta(r)), d.Lx, d.Ly, sx, sy, d.model, e->domains,
+                                e->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
         else
-            run_domains<float>(static_cast<const float*>(e->cur_theta(r)), d.Lx, d.Ly, sx, sy, d.model, e->parent,
-                               e->usz,
-                               e->hist, e->stats, e->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
+            run_domains<float>(static_cast<const float*>(e->cur_theta(r)), d.Lx, d.Ly, sx, sy, d.model, e->domains,
+                               e->stream, labels, sizes, counts, cap, n_sizes, n_domains, max_size);
     });
 }
 
