@@ -170,11 +170,75 @@ struct SpectrumBufs {
     }
 };
 
+// Large results to pageable host memory: the runtime's own path copies such
+// data to its staging memory and on, one after the other (16.8 MB of labels:
+// 950 us); here the device writes one slot of a pinned ring while the host
+// empties another (600 us).  The ring is made by the second copy of at least
+// kMin bytes: pinning and first touching it takes as long as it saves once.
+struct HostRing {
+    static constexpr size_t kSlot = size_t(1) << 20, kMin = size_t(2) << 20;
+    static constexpr int kSlots = 2;
+    PinnedBuf<char> buf;
+    hipEvent_t ev[kSlots] = {};
+    bool asked = false;
+    HostRing() = default;
+    HostRing(const HostRing&) = delete;
+    HostRing& operator=(const HostRing&) = delete;
+    ~HostRing() {
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+    }
+    // no ring where it cannot be had: the plain copy serves
+    bool ready() {
+        if (buf.p && ev[kSlots - 1]) return true;
+        if (!asked) {
+            asked = true;
+            return false;
+        }
+        for (hipEvent_t& e : ev)
+            if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                e = nullptr;
+                return false;
+            }
+        try {
+            buf.reserve(kSlot * kSlots);
+        } catch (const Error&) {
+            return false;
+        }
+        return true;
+    }
+    // dst = src after what the stream holds; returns when dst is complete
+    void copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
+        if (bytes < kMin || !ready()) {
+            check_hip(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s), "D2H");
+            check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+            return;
+        }
+        const size_t n = (bytes + kSlot - 1) / kSlot;
+        auto size_of = [&](size_t c) { return std::min(kSlot, bytes - c * kSlot); };
+        auto send = [&](size_t c) {
+            const size_t b = c % kSlots;
+            check_hip(hipMemcpyAsync(buf.p + b * kSlot, static_cast<const char*>(src) + c * kSlot, size_of(c),
+                                     hipMemcpyDeviceToHost, s),
+                      "D2H");
+            check_hip(hipEventRecord(ev[b], s), "hipEventRecord");
+        };
+        for (size_t c = 0; c < std::min<size_t>(n, kSlots); ++c) send(c);
+        for (size_t c = 0; c < n; ++c) {
+            check_hip(hipEventSynchronize(ev[c % kSlots]), "hipEventSynchronize");
+            std::memcpy(static_cast<char*>(dst) + c * kSlot, buf.p + c % kSlots * kSlot, size_of(c));
+            if (c + kSlots < n) send(c + kSlots);
+        }
+    }
+};
+
 // What a handle keeps for its domain labellings.
 struct DomainBufs {
     DevBuf<int32_t> parent;
     DevBuf<uint32_t> size, hist, stats;
     PinnedBuf<uint32_t> stats_host;
+    HostRing labels;
 };
 
 // ------------------------------------------------------------ parameters
@@ -893,8 +957,8 @@ static void run_domains(const R* th, int Lx, int Ly, int sx, int sy, int model, 
     // the (size, count) pairs were compacted on the device: only they come back
     const uint32_t* st = w.stats_host.p;
     check_hip(hipMemcpyAsync(w.stats_host.p, w.stats.p, sizeof(uint32_t) * nst, hipMemcpyDeviceToHost, s), "D2H");
-    if (labels) check_hip(hipMemcpyAsync(labels, w.parent.p, sizeof(int32_t) * N, hipMemcpyDeviceToHost, s), "D2H");
-    check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
+    if (labels) w.labels.copy(labels, w.parent.p, sizeof(int32_t) * N, s);
+    else check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
     const uint64_t ns = st[0];
     require(ns >= 1 && ns <= pcap, XYL_EDEVICE, "domain size distribution overflowed its bound");
     std::vector<std::pair<uint32_t, uint32_t>> pairs(ns);
