@@ -697,7 +697,7 @@ static hipGraphExec_t capture_steps2(xyl_lattice* h, const Lat<float>& v, int S,
 // 48.5 us for 512^2, 1024^2 and 2048^2 (FP64).
 static double lattice_untiled_us(const xyl_lattice* h) {
     if (step2_eligible(h)) return step2_us(h->Lx, h->Ly, h->cus, step2_rows(h));
-    return h->dtype == XYL_F64 ? 6.5 + (double)h->N / 1.0e5 : 3.3 + (double)h->N / 3.7e5;
+    return h->dtype == XYL_F64 ? 6.5 + (double)h->N / 1.15e5 : 3.3 + (double)h->N / 3.7e5;
 }
 
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
@@ -2304,7 +2304,7 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
         } else {
             double N = 0.0;
             for (int r : unit[q]) N += (double)e->desc[r].Lx * e->desc[r].Ly;
-            flat_us[q] = f64 ? 6.5 + N / 1.0e5 : 3.3 + N / 3.7e5;
+            flat_us[q] = f64 ? 6.5 + N / 1.15e5 : 3.3 + N / 3.7e5;
         }
         used.push_back(q);
     }

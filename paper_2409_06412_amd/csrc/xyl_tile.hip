@@ -228,7 +228,7 @@ struct TileCost {
 };
 
 static const TileCost kCost32[] = {{4, 2.75, 0.25, 0.60, 0.317, 32}, {2, 2.75, 0.15, 0.45, 0.22, 32}};
-static const TileCost kCost64[] = {{2, 3.0, 0.5, 1.40, 1.05, 16}, {1, 3.0, 0.3, 0.85, 0.65, 12}};
+static const TileCost kCost64[] = {{2, 3.0, 0.5, 1.20, 0.90, 16}, {1, 3.0, 0.3, 0.73, 0.56, 16}};
 
 // Time per step (us) of n steps in nl launches of up to t: `wgs` workgroups of
 // `waves` waves and `lds` bytes on the busiest CU, a region's rows alive for
@@ -307,7 +307,7 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
 bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan) {
     // (FP64 regions of more than 512 lanes would spill)
     static const TileCost rev32[] = {{4, 4.0, 0.35, 0.80, 0.62, 16}, {2, 4.0, 0.2, 0.50, 0.36, 16}};
-    static const TileCost rev64[] = {{2, 4.0, 0.5, 1.60, 1.40, 8}, {1, 4.0, 0.3, 1.00, 1.00, 12}};
+    static const TileCost rev64[] = {{2, 4.0, 0.5, 1.50, 1.25, 8}, {1, 4.0, 0.3, 0.90, 0.88, 12}};
     if (Lx % kLaneSites != 0 || n < 1) return false;
     return tile_search(f64 ? rev64 : rev32, 6, false, f64 ? 512 : kTileMaxThreads, Lx, Ly, f64, cus, n, plan, nullptr);
 }
