@@ -273,7 +273,10 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps);
  * least two lanes of the last.  Wider rows (Lx a multiple of 4) run as the
  * fewest column tiles that fit one workgroup with one quad of halo on each
  * side (at most 4096 sites) under the same lane rules, where such a split
- * exists.  Other shapes, FP64 and measurement steps use single steps.
+ * exists.  Large FP32 lattices of any width take three steps per pass instead,
+ * each wave on a column tile of its own, where a rule of the sizes finds that
+ * faster (runs of 6m steps).  Other shapes, FP64 and measurement steps use
+ * single steps.
  * Results are bitwise identical either way; two steps per pass read and write
  * the state once per two steps.  The library allocates a second velocity
  * buffer (the state's size) on first use; the state returns to the lattice's own
@@ -293,7 +296,7 @@ int xyl_get_fusion(const xyl_lattice* h, int32_t* steps_per_pass, int32_t* rows)
  * row's own waves it splits rows up to 4096 sites wide as well, into at least
  * two tiles); 0 keeps the current value.  A tile width no split fits falls
  * back to whole rows (up to 4096 sites) or the fewest tiles.  A lattice whose
- * shape was set takes the two-step pass in place of several steps per launch.
+ * shape was set takes the two-step pass in place of tiles and of three steps.
  * Results do not depend on it.  xyl_autotune sets both.  EINVAL outside the
  * ranges. */
 int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves);
@@ -475,8 +478,9 @@ int xyl_adjoint_backward(xyl_lattice* h, uint64_t run, double* grad, double* dth
 int xyl_adjoint_backward_device(xyl_lattice* h, uint64_t run, double scale, double* grad, void* dtheta0,
                                 void* domega0, int32_t dtype);
 /* Reverse steps per pass of xyl_adjoint_backward (App. A.1's step, run
- * backwards): 2 (the default) takes two reverse steps per pass over the state
- * where a strip of rows fits one workgroup (one site per lane, Lx at most
+ * backwards): 2 (the default) takes several reverse (and recomputed) steps per
+ * launch on tiles where those fit and rows was never set, else two reverse
+ * steps per pass over the state where a strip of rows fits one workgroup (one site per lane, Lx at most
  * 1024, Ly >= 4, and (32 rows + 80) Lx bytes of FP32 state and draws, twice
  * that in FP64, within a CU's 160 KiB of LDS), and recomputes the checkpointed
  * segments two steps per pass too where the forward's two-step pass takes

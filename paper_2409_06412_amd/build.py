@@ -16,7 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxyl.so")
-SOURCES = ["xyl_step.hip", "xyl_tile.hip", "xyl_obs.hip", "xyl_adjoint.hip", "xyl_state.hip", "xyl_runtime.hip"]
+SOURCES = ["xyl_step.hip", "xyl_tile.hip", "xyl_march.hip",
+           "xyl_obs.hip", "xyl_adjoint.hip", "xyl_state.hip", "xyl_runtime.hip"]
 # pure-host C++ (no HIP header), compiled by the host compiler
 HOST_SOURCES = ["xyl_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -80,7 +80,7 @@ __device__ __forceinline__ AdjStep<R> adj_step_coef(const Lat<R>& v, const doubl
 // draw n^k and staggering sign eps.  Out: lt, lu; its parameter adjoints are
 // added to (rx, ry, rh, rg).  Sums of products are fused multiply-adds (73
 // operations a site; 95 with separate products and the gamma terms one by
-// one, which took the 512^2 tile launch 2.31 us per step against 2.0).
+// one, which took the 512^2 tile launch 2.31 us per step against 1.93).
 template <typename R>
 __device__ __forceinline__ void adj_site(const Lat<R>& v, const AdjStep<R>& K, R s, R c, R sxm, R cxm, R fxm, R sxp,
                                          R cxp, R fxp, R sym, R cym, R fym, R syp, R cyp, R fyp, R lf, R lt, R lu, R u,

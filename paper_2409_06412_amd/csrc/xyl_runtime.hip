@@ -30,6 +30,7 @@
 #include "xyl_device.hpp"
 #include "xyl_domains.hpp"
 #include "xyl_internal.hpp"
+#include "xyl_march.hpp"
 #include "xyl_obs.hpp"
 #include "xyl_tile.hpp"
 
@@ -421,6 +422,7 @@ struct xyl_lattice {
     bool counter_valid = false;
     int fusion = 2;                // steps per pass of plain FP32 stepping where the shape allows (1 or 2)
     int cus = 256;                 // compute units of the device
+    bool march = true;             // three steps per pass where the rule takes it (xyl_march.hip)
     int step2_rows_tuned = 0;      // rows per strip of the two-step pass from xyl_autotune (0: the size rule)
     int step2_tw_tuned = 0;        // most waves per column tile (widths above 4096) from xyl_autotune (0: the rule)
     bool tiles = true;             // several steps per launch on tiles allowed
@@ -695,9 +697,41 @@ static hipGraphExec_t capture_steps2(xyl_lattice* h, const Lat<float>& v, int S,
 // passes of whole rows, or single steps.  Single steps were measured at 7.0,
 // 15.1 and 28.2 us for 1028^2, 2052^2 and 3076 x 3000 (FP32) and 8.1, 19.4 and
 // 48.5 us for 512^2, 1024^2 and 2048^2 (FP64).
-static double lattice_untiled_us(const xyl_lattice* h) {
-    if (step2_eligible(h)) return step2_us(h->Lx, h->Ly, h->cus, step2_rows(h));
+// Wider than 4096 the two-step pass runs on column tiles, about 5.8e5 sites per
+// us (8192^2 114 us per step).
+static double lattice_step2_us(const xyl_lattice* h) {
+    return h->Lx > 16 * kWaveSites ? (double)h->N / 5.8e5 : step2_us(h->Lx, h->Ly, h->cus, step2_rows(h));
+}
+// Three steps per pass where that is faster than the two-step pass or, for
+// widths that pass does not take, than single steps, by the rules' times (never
+// for a lattice whose caller shaped the two-step pass).
+static double lattice_single_us(const xyl_lattice* h) {
     return h->dtype == XYL_F64 ? 6.5 + (double)h->N / 1.15e5 : 3.3 + (double)h->N / 3.7e5;
+}
+static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
+    if (!h->march || h->dtype != XYL_F32 || h->fusion != 2 || !kick_factored(h->p) || h->Ly < 4) return false;
+    *p = march_plan(h->Lx, h->Ly, h->cus);
+    return p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
+}
+static double lattice_untiled_us(const xyl_lattice* h) {
+    MarchPlan p;
+    if (lattice_march_plan(h, &p)) return p.us;
+    if (step2_eligible(h)) return lattice_step2_us(h);
+    return lattice_single_us(h);
+}
+
+// The second velocity buffer of a path that the lattice can do without: where
+// it does not fit, the path is given up.
+static bool lattice_second_u(xyl_lattice* h, bool* path) {
+    try {
+        h->u2.reserve(elem_size(h->dtype) * h->N);
+    } catch (const Error& e) {
+        if (e.code != XYL_ENOMEM) throw;
+        (void)hipGetLastError();
+        *path = false;
+        return false;
+    }
+    return true;
 }
 
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
@@ -711,22 +745,19 @@ static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
     auto it = h->tile_plans.find(key);
     if (it == h->tile_plans.end()) {
         TilePlan p;
+        MarchPlan mp;
         double us = 0.0;
+        // Against three steps per pass the tiles' time counts 8% more: at the
+        // sizes where the two meet it comes out so much short (measured, tiles
+        // and march: 1500^2 5.8 and 6.5 us per step, 1604^2 8.0 and 6.7, 1800^2
+        // 7.8 and 7.5, 2048 x 1024 5.3 and 5.9, 3000 x 1000 6.9 and 7.1).
         // (tiles reach 4.7e5 sites per us at best)
         const bool hopeless = !h->tiles_tuned && (double)h->N > 4.8e5 * lattice_untiled_us(h);
         if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
-            (!h->tiles_tuned && us > lattice_untiled_us(h)))
-            p = TilePlan();
+            (!h->tiles_tuned && us > lattice_untiled_us(h)) || (lattice_march_plan(h, &mp) && 1.08 * us > mp.us))
+            p = TilePlan();   // (the tuner weighs tiles against the two-step pass and single steps only)
         if (p.T) {
-            // where the second velocity buffer does not fit, the other paths do
-            try {
-                h->u2.reserve(elem_size(h->dtype) * h->N);
-            } catch (const Error& e) {
-                if (e.code != XYL_ENOMEM) throw;
-                (void)hipGetLastError();
-                h->tiles = false;
-                return nullptr;
-            }
+            if (!lattice_second_u(h, &h->tiles)) return nullptr;
         }
         it = h->tile_plans.emplace(key, p).first;
     }
@@ -772,6 +803,26 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
         }
     }
     if constexpr (sizeof(R) == 4) {
+        MarchPlan mp;
+        if (mode == kStore && part_stride == 0 && n >= 2 * kMarchSteps && lattice_march_plan(h, &mp) &&
+            lattice_second_u(h, &h->march)) {
+            // pairs of passes, (A, u) -> (B, u2) -> (A, u): six steps later A
+            // again holds the angles of its parity
+            Lat<float> v3 = h->view<float>();
+            v3.k_base = 0;
+            const int parity = (int)((h->k + (uint64_t)h->cur) & 1);
+            float* A = static_cast<float*>(h->th[parity]);
+            float* B = static_cast<float*>(h->th[parity ^ 1]);
+            float* u = static_cast<float*>(h->u);
+            float* u2 = reinterpret_cast<float*>(h->u2.p);
+            for (; n >= 2 * kMarchSteps; n -= 2 * kMarchSteps) {
+                launch_march(v3, MarchBuffers{A, u, B, u2}, mp, h->k, h->stream);
+                launch_march(v3, MarchBuffers{B, u2, A, u}, mp, h->k + kMarchSteps, h->stream);
+                h->k += 2 * kMarchSteps;
+            }
+            h->counter_valid = false;
+            if (n == 0) return;
+        }
         if (mode == kStore && part_stride == 0 && step2_eligible(h) && n >= 4) {
             h->u2.reserve(sizeof(float) * h->N);
             Lat<float> v2 = h->view<float>();
@@ -1938,7 +1989,7 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves) {
                 "waves per tile must be 0 or in [2, 16]");
         if (rows) h->step2_rows_tuned = rows;
         if (tile_waves) h->step2_tw_tuned = tile_waves;
-        if (rows || tile_waves) h->tiles = false;   // the caller shapes the two-step pass: take it
+        if (rows || tile_waves) h->tiles = h->march = false;   // the caller shapes the two-step pass: take it
         h->touch();
     });
 }
@@ -3508,8 +3559,8 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
     const int rows2 = adjoint2_rows(h);
     const bool fuse = h->adj_fusion == 2 && adjoint2_fits<R>(v, rows2);
     // several reverse (and recompute) steps per launch on tiles, unless the
-    // caller shaped the two-step pass: 512^2 FP32 takes 2.2 us per reverse
-    // step so, with the recompute beside it, against 4.9
+    // caller shaped the two-step pass: 512^2 FP32 takes 2.8 us per reverse step
+    // so over 5000 steps, the recompute (1.4 us alone) beside it, against 4.9
     bool tiles = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && h->Lx <= 16 * kWaveSites &&
                  h->N <= (size_t(1) << 24);
     if (tiles && a->tile_K != std::min<uint64_t>(K, 64)) {
