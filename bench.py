@@ -9,9 +9,11 @@ correlation length) fused into every 500th step.  One "step" is one BBK
 step of the whole lattice.  The state is resident in HBM before timing.
 
 Also reported on the same line:
-  * roofline of the dominant kernel, the two-steps-per-pass FP32 kernel
-    (k_step2: one launch advances every site two steps, reading angle and
-    velocity once and writing both once, 16 B per site per launch): its
+  * roofline of the two-steps-per-pass FP32 kernel (k_step2, selected by
+    shaping it; the timed region takes three steps per pass, k_march, where
+    the library finds that faster: plain_stepping beside it.  One launch
+    advances every site two steps, reading angle and velocity once and
+    writing both once, 16 B per site per launch): its
     average launch duration from HIP events on the lattice's stream around
     back-to-back launches; the VALU instructions per launch from rocprofv3
     counters (bound "alu": against the VALU issue rate of 256 CUs x 4 SIMDs
@@ -70,7 +72,7 @@ def kernel_source_hash() -> str:
     committed counter summaries as taken of another kernel."""
     import re
     h = hashlib.sha256()
-    for f in ("xyl_step.hip", "xyl_device.hpp", "xyl_internal.hpp"):
+    for f in ("xyl_step.hip", "xyl_march.hip", "xyl_device.hpp", "xyl_internal.hpp"):
         with open(os.path.join(ROOT, "paper_2409_06412_amd", "csrc", f)) as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -653,7 +655,7 @@ def summarize_valu(d, out_json, out_md, L, command, kernel):
            "active_inst_valu_quad_cycles": mean.get("SQ_ACTIVE_INST_VALU"),
            "grbm_gui_active": mean.get("GRBM_GUI_ACTIVE"),
            "valu_busy_percent": mean.get("VALUBusy"),
-           "valu_instructions_per_site_update": mean["SQ_INSTS_VALU"] * 64 / (L * L * (2 if "step2" in kernel else 1)),
+           "valu_instructions_per_site_update": mean["SQ_INSTS_VALU"] * 64 / (L * L * (3 if "march" in kernel else 2 if "step2" in kernel else 1)),
            "command": command}
     json.dump(res, open(out_json, "w"), indent=1)
     md = ["# VALU work of %s, %dx%d lattice" % (kernel, L, L), "",
@@ -809,6 +811,9 @@ def main():
                     "kernel": dom["kernel"], "avg_kernel_us": us, "hbm": hbm,
                     "valu_profile": "absent or taken of another kernel source"}
     roofline["single_step_kernel"] = kern["single_step"]
+    # the timed region's own path: three steps per pass (k_march) where the
+    # library finds that faster than the two-step pass above
+    roofline["plain_stepping"] = kern["plain_stepping"]
     log("stepping kernels:", json.dumps(kern))
     log("roofline:", json.dumps(roofline))
 

@@ -721,10 +721,20 @@ static double lattice_untiled_us(const xyl_lattice* h) {
 }
 
 // The second velocity buffer of a path that the lattice can do without: where
-// it does not fit, the path is given up.
+// it does not fit, the path is given up.  While the caller captures the stream
+// nothing is allocated: such a call takes another path.
 static bool lattice_second_u(xyl_lattice* h, bool* path) {
+    const size_t bytes = elem_size(h->dtype) * h->N;
+    if (!h->u2.p || h->u2.n < bytes) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (st != hipStreamCaptureStatusNone) return false;
+    }
     try {
-        h->u2.reserve(elem_size(h->dtype) * h->N);
+        h->u2.reserve(bytes);
     } catch (const Error& e) {
         if (e.code != XYL_ENOMEM) throw;
         (void)hipGetLastError();
