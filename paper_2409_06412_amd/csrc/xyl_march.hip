@@ -171,6 +171,11 @@ MarchPlan march_plan(int Lx, int Ly, int cus) {
     return p;
 }
 
+void load_march_kernels() {
+    hipFuncAttributes a;
+    check_hip(hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_march<kModelXY>)), "hipFuncGetAttributes");
+}
+
 void launch_march(const Lat<float>& v, const MarchBuffers& b, const MarchPlan& p, uint64_t k, hipStream_t s) {
     if (v.Lx % kLaneSites != 0 || v.Ly < kMarchSteps || p.ntx < 1 || p.strips < 1 || p.strips > v.Ly ||
         (v.Lx / kLaneSites + p.ntx - 1) / p.ntx > kWave - 2 || !v.fact)

@@ -708,8 +708,9 @@ static double lattice_step2_us(const xyl_lattice* h) {
 static double lattice_single_us(const xyl_lattice* h) {
     return h->dtype == XYL_F64 ? 6.5 + (double)h->N / 1.15e5 : 3.3 + (double)h->N / 3.7e5;
 }
+static bool march_shape_ok(int dtype, int Ly) { return dtype == XYL_F32 && Ly >= 4; }
 static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
-    if (!h->march || h->dtype != XYL_F32 || h->fusion != 2 || !kick_factored(h->p) || h->Ly < 4) return false;
+    if (!h->march || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
     *p = march_plan(h->Lx, h->Ly, h->cus);
     return p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
 }
@@ -744,13 +745,16 @@ static bool lattice_second_u(xyl_lattice* h, bool* path) {
     return true;
 }
 
+// Widths above 4096 and lattices beyond 2^24 sites never gain by tiles (their
+// passes are bound by issue already, and tiles recompute more halo).
+static bool tile_shape_ok(int Lx, int Ly) {
+    return Lx <= 16 * kWaveSites && (size_t)Lx * Ly <= (size_t(1) << 24);
+}
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
 // steps (n >= 2), or NULL where another path is faster by the rules' times.
-// Widths above 4096 and lattices beyond 2^24 sites never gain (their passes
-// are bound by issue already, and tiles recompute more halo).  Plans are kept
-// per run length (64 steps and more share one).
+// Plans are kept per run length (64 steps and more share one).
 static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
-    if (!h->tiles || h->fusion != 2 || n < 2 || h->Lx > 16 * kWaveSites || h->N > (size_t(1) << 24)) return nullptr;
+    if (!h->tiles || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
     const uint64_t key = std::min<uint64_t>(n, 64);
     auto it = h->tile_plans.find(key);
     if (it == h->tile_plans.end()) {
@@ -1068,6 +1072,10 @@ static int create_impl(xyl_lattice** out, int32_t Lx, int32_t Ly, int32_t dtype,
         h->Lx = Lx;
         h->Ly = Ly;
         h->N = (size_t)Lx * Ly;
+        // the kernels that the stepping rules may choose are loaded here, once
+        // per process, not in a caller's step
+        if (tile_shape_ok(Lx, Ly)) load_tile_kernels();
+        if (march_shape_ok(dtype, Ly)) load_march_kernels();
         const uint64_t k0[1] = {0};
         const double T0[1] = {0.0};
         h->sched = make_schedule(k0, T0, 1);
@@ -2315,7 +2323,7 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
     for (int r : active) {
         const xyl_replica_desc& d = e->desc[r];
         const bool fact = f64 || replica_factored(d);
-        const bool fits = fact && d.Lx <= 16 * kWaveSites && (size_t)d.Lx * d.Ly <= (size_t(1) << 24);
+        const bool fits = fact && tile_shape_ok(d.Lx, d.Ly);
         if (!fits && e->lds[r]) lds_fixed_sites += (double)d.Lx * d.Ly;
         if (!fits) continue;
         if (e->lds[r]) unit[0].push_back(r);
@@ -3233,6 +3241,10 @@ int xyl_ensemble_create(xyl_ensemble** out, const xyl_replica_desc* desc, int32_
             e->poff.push_back(e->ptotal);
             e->ptotal += part_elems(e->nrp(r));
         }
+        // loaded here, once per process, not in a caller's step
+        if (std::any_of(e->desc.begin(), e->desc.end(),
+                        [](const xyl_replica_desc& d) { return tile_shape_ok(d.Lx, d.Ly); }))
+            load_tile_kernels();
         const size_t bytes = elem_size(dtype) * e->total;
         for (int b = 0; b < 2; ++b) check_alloc(hipMalloc(&e->th[b], bytes), "hipMalloc theta");
         check_alloc(hipMalloc(&e->u, bytes), "hipMalloc velocity");
@@ -3571,8 +3583,7 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
     // several reverse (and recompute) steps per launch on tiles, unless the
     // caller shaped the two-step pass: 512^2 FP32 takes 2.8 us per reverse step
     // so over 5000 steps, the recompute (1.4 us alone) beside it, against 4.9
-    bool tiles = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && h->Lx <= 16 * kWaveSites &&
-                 h->N <= (size_t(1) << 24);
+    bool tiles = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && tile_shape_ok(h->Lx, h->Ly);
     if (tiles && a->tile_K != std::min<uint64_t>(K, 64)) {
         a->tile_K = std::min<uint64_t>(K, 64);
         const bool f64 = h->dtype == XYL_F64;

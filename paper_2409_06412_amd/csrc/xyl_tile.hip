@@ -592,6 +592,11 @@ __global__ __launch_bounds__(256) void k_tile_order_sum(const double* __restrict
     if (threadIdx.x == 0) out[6 * (size_t)blockIdx.x + 2] = ((red[0] + red[1]) + (red[2] + red[3])) / N;
 }
 
+void load_tile_kernels() {
+    hipFuncAttributes a;
+    check_hip(hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_tile_order_sum)), "hipFuncGetAttributes");
+}
+
 void launch_tile_order_sum(const double* order, int n, double N, double* out, int steps, hipStream_t s) {
     if (steps <= 0) return;
     k_tile_order_sum<<<steps, 256, 0, s>>>(order, n, N, out);
