@@ -265,7 +265,7 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps);
 /* Steps per pass over the state for plain stepping (1 or 2; default 2).
  * With 2, lattices up to 4096 sites wide take several steps per launch on
  * tiles held in registers and LDS (either precision) where a rule of the sizes
- * (or xyl_autotune) finds that faster, runs of an even number of steps; else,
+ * (or xyl_autotune) finds that faster, in runs of two steps and more; else,
  * in FP32, runs of 4m steps without measurements advance two steps per pass
  * (one workgroup per strip of rows across the whole width, the second step
  * one row behind the first) where Ly >= 4 and Lx is at most 4096, uses at
@@ -282,13 +282,21 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps);
  * buffer (the state's size) on first use; the state returns to the lattice's own
  * buffers at the end of every call. */
 int xyl_set_fusion(xyl_lattice* h, int32_t steps_per_pass);
-/* The stepping mode in effect: *steps_per_pass = the value set by
- * xyl_set_fusion or chosen by xyl_autotune; *rows = rows per strip of the
- * two-step pass for this lattice on its device (xyl_autotune's choice, else a
- * rule from the CU count and the workgroups a CU holds), 0 where two steps
- * per pass do not apply (shape, FP64, or steps_per_pass 1).  Either pointer
- * may be NULL. */
+/* *steps_per_pass = the value set by xyl_set_fusion or chosen by
+ * xyl_autotune; *rows = rows per strip of the two-step pass for this lattice
+ * on its device (xyl_autotune's choice, else a rule from the CU count and the
+ * workgroups a CU holds), 0 where two steps per pass do not apply (shape,
+ * FP64, or steps_per_pass 1).  Which path a run takes: xyl_stepping_path.
+ * Either pointer may be NULL. */
 int xyl_get_fusion(const xyl_lattice* h, int32_t* steps_per_pass, int32_t* rows);
+/* How a run of nsteps steps without measurements goes: *path = XYL_PATH_* of
+ * its launches (what is left over at its end may take another: the last steps
+ * of a run that is no multiple of 6 or 4 with three or two steps per pass), and
+ * *steps_per_launch the most steps that one launch takes.  Where the second
+ * velocity buffer turns out not to fit, or is missing while the caller captures
+ * the stream, a run takes XYL_PATH_SINGLE instead.  Either pointer may be NULL. */
+enum { XYL_PATH_SINGLE = 1, XYL_PATH_TWO_STEP = 2, XYL_PATH_MARCH = 3, XYL_PATH_TILES = 4 };
+int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* steps_per_launch);
 /* Shape of the two-step pass (App. B's data-parallel sweep, two BBK steps of
  * App. A.1 per pass): rows per strip (2 to 64) and, for widths above 4096,
  * the most waves (of 256 sites) a column tile may span (2 to 16: narrower

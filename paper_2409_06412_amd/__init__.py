@@ -57,6 +57,9 @@ class ReplicaDesc(ctypes.Structure):
 # dimer mapping (q = 2, p-fold field, half-circle angles)
 MODELS = {"xy": 0, "si": 1}
 
+# XYL_PATH_*: how a run of steps is launched
+PATHS = {1: "single", 2: "two_step", 3: "march", 4: "tiles"}
+
 
 def _model_code(model) -> int:
     return MODELS[model] if isinstance(model, str) else int(model)
@@ -78,6 +81,7 @@ _SIGS = {
     "xyl_set_model": (_i32, [_vp, _i32, _d]),
     "xyl_set_fusion": (_i32, [_vp, _i32]),
     "xyl_get_fusion": (_i32, [_vp, P(_i32), P(_i32)]),
+    "xyl_stepping_path": (_i32, [_vp, _u64, P(_i32), P(_i32)]),
     "xyl_set_step2_shape": (_i32, [_vp, _i32, _i32]),
     "xyl_get_step2_shape": (_i32, [_vp, P(_i32), P(_i32), P(_i32)]),
     "xyl_ensemble_set_fusion": (_i32, [_vp, _i32]),
@@ -272,6 +276,14 @@ class Lattice:
         sp, rows = _i32(), _i32()
         _check(load().xyl_get_fusion(self._h, ctypes.byref(sp), ctypes.byref(rows)))
         return sp.value, rows.value
+
+    def stepping_path(self, nsteps: int):
+        """(path, most steps per launch) of a run of nsteps steps without
+        measurements; path is "single", "two_step", "march" (three steps per
+        pass) or "tiles"."""
+        p, t = _i32(), _i32()
+        _check(load().xyl_stepping_path(self._h, int(nsteps), ctypes.byref(p), ctypes.byref(t)))
+        return PATHS[p.value], t.value
 
     def set_step2_shape(self, rows=0, tile_waves=0):
         """Rows per strip of the two-step pass and, for widths above 4096, the

@@ -753,7 +753,7 @@ static bool tile_shape_ok(int Lx, int Ly) {
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
 // steps (n >= 2), or NULL where another path is faster by the rules' times.
 // Plans are kept per run length (64 steps and more share one).
-static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
+static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
     if (!h->tiles || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
     const uint64_t key = std::min<uint64_t>(n, 64);
     auto it = h->tile_plans.find(key);
@@ -770,12 +770,14 @@ static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
         if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
             (!h->tiles_tuned && us > lattice_untiled_us(h)) || (lattice_march_plan(h, &mp) && 1.08 * us > mp.us))
             p = TilePlan();   // (the tuner weighs tiles against the two-step pass and single steps only)
-        if (p.T) {
-            if (!lattice_second_u(h, &h->tiles)) return nullptr;
-        }
         it = h->tile_plans.emplace(key, p).first;
     }
     return it->second.T ? &it->second : nullptr;
+}
+// The same with the second velocity buffer that the tiles need.
+static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
+    const TilePlan* p = lattice_tile_choice(h, n);
+    return p && lattice_second_u(h, &h->tiles) ? p : nullptr;
 }
 
 // n steps through an even number of launches, (A, u) -> (B, u2) -> (A, u), A
@@ -1996,6 +1998,27 @@ int xyl_get_fusion(const xyl_lattice* h, int32_t* steps_per_pass, int32_t* rows)
         require(h != nullptr, XYL_EINVAL, "NULL handle");
         if (steps_per_pass) *steps_per_pass = h->fusion;
         if (rows) *rows = step2_eligible(h) ? step2_rows(h) : 0;
+    });
+}
+
+int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* steps_per_launch) {
+    return guarded([&] {
+        require(h != nullptr, XYL_EINVAL, "NULL handle");
+        int p = XYL_PATH_SINGLE, t = 1;
+        MarchPlan mp;
+        if (const TilePlan* tp = lattice_tile_choice(h, nsteps)) {
+            const uint64_t nl = tile_launches(nsteps, tp->T);
+            p = XYL_PATH_TILES;
+            t = (int)((nsteps + nl - 1) / nl);
+        } else if (nsteps >= 2 * kMarchSteps && lattice_march_plan(h, &mp)) {
+            p = XYL_PATH_MARCH;
+            t = kMarchSteps;
+        } else if (nsteps >= 4 && step2_eligible(h)) {
+            p = XYL_PATH_TWO_STEP;
+            t = 2;
+        }
+        if (path) *path = p;
+        if (steps_per_launch) *steps_per_launch = t;
     });
 }
 
