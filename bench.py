@@ -9,18 +9,16 @@ correlation length) fused into every 500th step.  One "step" is one BBK
 step of the whole lattice.  The state is resident in HBM before timing.
 
 Also reported on the same line:
-  * roofline of the two-steps-per-pass FP32 kernel (k_step2, selected by
-    shaping it; the timed region takes three steps per pass, k_march, where
-    the library finds that faster: plain_stepping beside it.  One launch
-    advances every site two steps, reading angle and velocity once and
-    writing both once, 16 B per site per launch): its
-    average launch duration from HIP events on the lattice's stream around
-    back-to-back launches; the VALU instructions per launch from rocprofv3
-    counters (bound "alu": against the VALU issue rate of 256 CUs x 4 SIMDs
-    at 2.4 GHz, one wave64 instruction per SIMD every 4 cycles) and the
-    algorithmic HBM rate (16 B per site / duration, against 8 TB/s and the
-    measured streaming ceiling of the same access shape); the single-step
-    kernel measured the same way beside it;
+  * roofline of the kernel that the timed region steps with (three steps per
+    pass, k_march, or two, k_step2: one launch advances every site so many
+    steps, reading angle and velocity once and writing both once, 16 B per
+    site per launch): its average launch duration from HIP events on the
+    lattice's stream around back-to-back launches; the VALU instructions per
+    launch from rocprofv3 counters (bound "alu": against the VALU issue rate
+    of 256 CUs x 4 SIMDs at 2.4 GHz, one wave64 instruction per SIMD every 4
+    cycles) and the algorithmic HBM rate (16 B per site / duration, against 8
+    TB/s and the measured streaming ceiling of the same access shape); the
+    other stepping kernels measured the same way beside it;
   * HBM traffic per launch from rocprofv3 counters when the committed
     counter summary matches the current kernel source, else null;
   * batched-ensemble vs one-launch-per-replica throughput on the 288-replica
@@ -58,21 +56,30 @@ HBM_PEAK_GBS = 8000.0
 # two (measured: SQ_ACTIVE_INST_VALU = SQ_INSTS_VALU + SQ_INSTS_VALU_TRANS_F32).
 VALU_PEAK_GINST = 256 * 4 * 2.4 / 4
 BYTES_PER_SITE_F32 = 16
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step2_f32_4096_traffic.json")
-VALU_FILE = os.path.join(ROOT, "profiles", "step2_f32_4096_valu.json")
+# the counter summaries of a stepping kernel: profiles/<name>_f32_4096_{traffic,valu}.json
+PROFILES = {"march": "march_f32_4096", "two_step": "step2_f32_4096", "single_step": "step_f32_4096"}
+# the sources that a kernel's code comes from
+_SHARED = ("xyl_device.hpp", "xyl_sincos.hpp", "xyl_internal.hpp")
+_TILE = ("xyl_tile.hpp", "xyl_tile_device.hpp") + _SHARED
+KERNEL_SOURCES = {"step": ("xyl_step.hip",) + _SHARED,
+                  "march": ("xyl_march.hip", "xyl_march.hpp") + _SHARED,
+                  "tile": ("xyl_tile.hip",) + _TILE,
+                  "adjoint": ("xyl_adjoint.hip",) + _TILE}
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash() -> str:
-    """Hash of the step kernels' code: the sources with comments and
-    whitespace removed, so that only a change to the code itself marks the
-    committed counter summaries as taken of another kernel."""
+def kernel_source_hash(kernel: str = "xyl::k_step") -> str:
+    """Hash of a kernel's code: its sources with comments and whitespace
+    removed, so that only a change to the code itself marks the committed
+    counter summaries as taken of another kernel."""
     import re
+    group = ("march" if "k_march" in kernel else "adjoint" if "k_adjoint" in kernel else
+             "tile" if "_tile" in kernel and "step2" not in kernel else "step")
     h = hashlib.sha256()
-    for f in ("xyl_step.hip", "xyl_march.hip", "xyl_device.hpp", "xyl_internal.hpp"):
+    for f in KERNEL_SOURCES[group]:
         with open(os.path.join(ROOT, "paper_2409_06412_amd", "csrc", f)) as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -81,15 +88,15 @@ def kernel_source_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def load_profile(path, L, key):
-    """A figure from a committed counter summary, if it was taken of the
-    current kernel source at this lattice size, else None."""
+def load_profile(name, what, L, key):
+    """A figure from a committed counter summary (what: traffic or valu), if it
+    was taken of the current kernel source at this lattice size, else None."""
     try:
-        with open(path) as f:
+        with open(os.path.join(ROOT, "profiles", "%s_%s.json" % (PROFILES[name], what))) as f:
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    if t.get("kernel_hash") != kernel_source_hash() or t.get("L") != L:
+    if t.get("kernel_hash") != kernel_source_hash(t.get("kernel", "")) or t.get("L") != L:
         return None
     return t.get(key)
 
@@ -97,13 +104,13 @@ def load_profile(path, L, key):
 def time_steps(torch, lat, nsteps):
     """Average time per step of plain stepping, no graph, no measurement: HIP
     events on the lattice's stream (torch's current stream) around nsteps
-    steps (a multiple of 4, so that with two steps per pass every launch is a
-    two-step pass).  In ms."""
-    assert nsteps % 4 == 0
+    steps, rounded down to a multiple of 12 so that with two or three steps per
+    pass every launch is such a pass.  In ms."""
+    nsteps = max(12, nsteps - nsteps % 12)
     lat.set_graph_steps(0)
     s = torch.cuda.current_stream()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    lat.step(8)
+    lat.step(12)
     e0.record(s)
     lat.step(nsteps)
     e1.record(s)
@@ -113,32 +120,33 @@ def time_steps(torch, lat, nsteps):
 
 
 def step_kernels(torch, lat, L, nsteps):
-    """Launch durations of the two stepping kernels on this lattice: the
-    two-step pass where it applies (16 B per site per launch for two
-    site-updates) and the single step (16 B per site per launch for one)."""
+    """Launch durations of the stepping kernels on this lattice, 16 B per site
+    per launch each: the one that plain stepping takes ("plain"), the two-step
+    pass where it applies and the single step."""
     sp, rows = lat.fusion()
     out = {}
-    # plain stepping as the library runs this lattice (three steps per pass, k_march,
-    # where it finds that faster), then the two-step pass by itself: shaping it selects it
-    out["plain_stepping"] = {"us_per_step": 1e3 * time_steps(torch, lat, nsteps)}
-    if rows:
-        lat.set_step2_shape(rows)
+
+    def add(name, kernel, steps, **more):
         ms = time_steps(torch, lat, nsteps)
-        us = 2e3 * ms
+        us = 1e3 * ms * steps
         gbs = BYTES_PER_SITE_F32 * L * L / (us * 1e-6) / 1e9
+        out[name] = dict(kernel=kernel, steps_per_launch=steps, avg_kernel_us=us, us_per_step=1e3 * ms,
+                         site_updates_per_s=L * L / (ms * 1e-3), algorithmic_GBs=gbs,
+                         frac_of_8TBs=gbs / HBM_PEAK_GBS, **more)
+
+    path = lat.stepping_path(nsteps)[0]
+    if path == "march":
+        add("march", "k_march", 3)
+    if rows:
+        # shaping the two-step pass selects it
+        lat.set_step2_shape(rows)
         _, tile_waves, tiles = lat.step2_shape()
-        out["two_step"] = {"kernel": "k_step2_tiled" if tiles > 1 else "k_step2", "rows_per_strip": rows,
-                           "tiles": tiles, "tile_waves": tile_waves,
-                           "avg_kernel_us": us,
-                           "us_per_step": 1e3 * ms, "site_updates_per_s": L * L / (ms * 1e-3),
-                           "algorithmic_GBs": gbs, "frac_of_8TBs": gbs / HBM_PEAK_GBS}
+        add("two_step", "k_step2_tiled" if tiles > 1 else "k_step2", 2, rows_per_strip=rows, tiles=tiles,
+            tile_waves=tile_waves)
     lat.set_fusion(1)
-    ms = time_steps(torch, lat, nsteps)
+    add("single_step", "k_step", 1, launch=list(lat.launch()))
     lat.set_fusion(sp)
-    gbs = BYTES_PER_SITE_F32 * L * L / (ms * 1e-3) / 1e9
-    out["single_step"] = {"kernel": "k_step", "launch": list(lat.launch()), "avg_kernel_us": 1e3 * ms,
-                          "site_updates_per_s": L * L / (ms * 1e-3), "algorithmic_GBs": gbs,
-                          "frac_of_8TBs": gbs / HBM_PEAK_GBS}
+    out["plain"] = path if path in out else "single_step"
     return out
 
 
@@ -307,7 +315,7 @@ def bench_control_8192(torch, xyl, workloads, nlaunch=200):
     out = step_kernels(torch, lat, 8192, nlaunch)
     lat.close()
     ceiling = xyl.stream_ceiling(8192 * 8192, 30)
-    for k in (v for v in out.values() if "algorithmic_GBs" in v):
+    for k in (v for v in out.values() if isinstance(v, dict)):
         k["stream_ceiling_GBs"] = ceiling
         k["frac_of_stream_ceiling"] = k["algorithmic_GBs"] / ceiling
     return {"L": 8192, **out}
@@ -609,7 +617,7 @@ def summarize_traffic(fetch_dir, write_dir, out_json, out_md, L, commands, kerne
     fetch_b = f_step * 1024.0 * f_scale
     write_b = w_step * 1024.0 * w_scale
     alg = BYTES_PER_SITE_F32 * L * L
-    res = {"kernel": kernel, "L": L, "kernel_hash": kernel_source_hash(), "grid_workgroup": list(key),
+    res = {"kernel": kernel, "L": L, "kernel_hash": kernel_source_hash(kernel), "grid_workgroup": list(key),
            "fetch_kib_per_launch": f_step, "write_kib_per_launch": w_step,
            "copy_fetch_kib": f_copy, "copy_write_kib": w_copy, "fetch_scale": f_scale, "write_scale": w_scale,
            "fetch_bytes": fetch_b, "write_bytes": write_b, "bytes_per_launch": fetch_b + write_b,
@@ -634,9 +642,11 @@ def summarize_traffic(fetch_dir, write_dir, out_json, out_md, L, commands, kerne
 VALU_COUNTERS = ("SQ_INSTS_VALU", "SQ_INSTS_VALU_TRANS_F32", "SQ_ACTIVE_INST_VALU", "GRBM_GUI_ACTIVE", "VALUBusy")
 
 
-def summarize_valu(d, out_json, out_md, L, command, kernel):
+def summarize_valu(d, out_json, out_md, L, command, kernel, steps_per_launch=0):
     """VALU instructions per launch of the kernel (summed over the device) and
-    the VALU busy fraction, from one rocprofv3 --pmc run."""
+    the VALU busy fraction, from one rocprofv3 --pmc run.  steps_per_launch: of
+    the kernels that take any number (the others' is known: 0)."""
+    steps_per_launch = steps_per_launch or (3 if "march" in kernel else 2 if "step2" in kernel else 1)
     import csv
     from collections import defaultdict
     files = _csvs(d, "counter_collection.csv")
@@ -648,14 +658,14 @@ def summarize_valu(d, out_json, out_md, L, command, kernel):
             vals[(r["Grid_Size"], r["Workgroup_Size"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
     key = max(vals, key=lambda k: len(vals[k]["SQ_INSTS_VALU"]))
     mean = {c: sum(v) / len(v) for c, v in vals[key].items()}
-    res = {"kernel": kernel, "L": L, "kernel_hash": kernel_source_hash(), "grid_workgroup": list(key),
+    res = {"kernel": kernel, "L": L, "kernel_hash": kernel_source_hash(kernel), "grid_workgroup": list(key),
            "dispatches": len(vals[key]["SQ_INSTS_VALU"]),
            "valu_instructions_per_launch": mean["SQ_INSTS_VALU"],
            "transcendental_f32_per_launch": mean.get("SQ_INSTS_VALU_TRANS_F32"),
            "active_inst_valu_quad_cycles": mean.get("SQ_ACTIVE_INST_VALU"),
            "grbm_gui_active": mean.get("GRBM_GUI_ACTIVE"),
            "valu_busy_percent": mean.get("VALUBusy"),
-           "valu_instructions_per_site_update": mean["SQ_INSTS_VALU"] * 64 / (L * L * (3 if "march" in kernel else 2 if "step2" in kernel else 1)),
+           "valu_instructions_per_site_update": mean["SQ_INSTS_VALU"] * 64 / (L * L * steps_per_launch),
            "command": command}
     json.dump(res, open(out_json, "w"), indent=1)
     md = ["# VALU work of %s, %dx%d lattice" % (kernel, L, L), "",
@@ -684,7 +694,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--cpu-steps", type=int, default=100)
     ap.add_argument("--kernel-steps", type=int, default=1000,
-                    help="steps (a multiple of 4) over which each stepping kernel is timed alone")
+                    help="steps over which each stepping kernel is timed alone")
     ap.add_argument("--only", type=str, default="",
                     help="comma list of extras to run alone (copy, ensemble, quench, adjoint, domains, control, "
                          "si, si_fss, structure); "
@@ -699,6 +709,8 @@ def main():
     ap.add_argument("--summarize-traffic", nargs=6,
                     metavar=("FETCH_DIR", "WRITE_DIR", "OUT_JSON", "OUT_MD", "FETCH_CMD", "WRITE_CMD"))
     ap.add_argument("--summarize-valu", nargs=4, metavar=("DIR", "OUT_JSON", "OUT_MD", "COMMAND"))
+    ap.add_argument("--steps-per-launch", type=int, default=0,
+                    help="with --summarize-valu of a tile kernel: the steps of its launches")
     ap.add_argument("--kernel", type=str, default=STEP2_KERNEL,
                     help="kernel name the counter summaries select (default: the two-step pass)")
     args = ap.parse_args()
@@ -711,7 +723,7 @@ def main():
         return
     if args.summarize_valu:
         a = args.summarize_valu
-        summarize_valu(a[0], a[1], a[2], args.L, a[3], args.kernel)
+        summarize_valu(a[0], a[1], a[2], args.L, a[3], args.kernel, args.steps_per_launch)
         return
     if args.gpus != 1:
         print("bench.py measures one GPU only: the library runs the hot path on a single MI355X "
@@ -756,11 +768,13 @@ def main():
         launch = lat.launch()
     else:
         launch = lat.autotune()
-    fusion = lat.fusion()
-    log("single-step launch shape (rows per strip, waves per workgroup):", launch,
-        "; steps per pass, rows per strip of the two-step pass:", fusion)
-    # the warm-up runs the timed path itself (samples and stepping), so that no
-    # kernel is loaded or launched for the first time inside the timed region
+    # the timed call's runs between samples are this long
+    path = lat.stepping_path(min(args.steps, args.every))
+    log("single-step launch shape (rows per strip, waves per workgroup):", launch, "; stepping path, steps per launch:",
+        path, "; steps per pass, rows per strip of the two-step pass:", lat.fusion())
+    # the warm-up runs the sampling and, where it is long enough for a pass of
+    # the timed region's kernel (six steps), that kernel too; the stepping
+    # kernels are loaded since the lattice's creation in any case
     if args.warmup:
         lat.step_measured(args.warmup, args.every)
     torch.cuda.synchronize()
@@ -779,10 +793,10 @@ def main():
     # the practical ceiling of the state's access shape: a plain stream reading
     # two and writing two arrays of L*L floats, ping-ponging like the state
     ceiling = xyl.stream_ceiling(L * L, 100)
-    for k in (v for v in kern.values() if "algorithmic_GBs" in v):
+    for k in (v for v in kern.values() if isinstance(v, dict)):
         k["frac_of_stream_ceiling"] = k["algorithmic_GBs"] / ceiling
-    two = kern.get("two_step")
-    dom = two or kern["single_step"]
+    plain = kern["plain"]
+    dom = kern[plain]
     us = dom["avg_kernel_us"]
     hbm = {"algorithmic_bytes_per_launch": BYTES_PER_SITE_F32 * L * L, "achieved_GBs": dom["algorithmic_GBs"],
            "peak_GBs": HBM_PEAK_GBS, "frac": dom["algorithmic_GBs"] / HBM_PEAK_GBS,
@@ -792,17 +806,17 @@ def main():
            "single_step_roofline_site_updates_per_s": HBM_PEAK_GBS * 1e9 / BYTES_PER_SITE_F32,
            "site_updates_over_single_step_roofline":
                dom["site_updates_per_s"] / (HBM_PEAK_GBS * 1e9 / BYTES_PER_SITE_F32)}
-    traffic = load_profile(TRAFFIC_FILE, L, "bytes_per_launch") if two else None
-    slots = load_profile(VALU_FILE, L, "active_inst_valu_quad_cycles") if two else None
+    traffic = load_profile(plain, "traffic", L, "bytes_per_launch")
+    slots = load_profile(plain, "valu", L, "active_inst_valu_quad_cycles")
     if slots:
         # VALU issue slots (one wave64 instruction = 4 cycles of a SIMD; the
         # transcendentals take two) per launch over the launch duration
         achieved = slots / (us * 1e-6) / 1e9
         roofline = {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_GINST, "unit": "G VALU issue slots/s",
                     "frac": achieved / VALU_PEAK_GINST, "traffic": traffic,
-                    "kernel": "k_step2<XY> (two steps per pass)", "avg_kernel_us": us,
-                    "valu_issue_slots_per_launch": slots,
-                    "valu_instructions_per_launch": load_profile(VALU_FILE, L, "valu_instructions_per_launch"),
+                    "kernel": "%s<XY> (%d steps per launch)" % (dom["kernel"], dom["steps_per_launch"]),
+                    "avg_kernel_us": us, "valu_issue_slots_per_launch": slots,
+                    "valu_instructions_per_launch": load_profile(plain, "valu", L, "valu_instructions_per_launch"),
                     "hbm": hbm}
     else:
         # no counter summary of the current kernel source: the HBM figure alone
@@ -810,10 +824,9 @@ def main():
                     "frac": dom["algorithmic_GBs"] / HBM_PEAK_GBS, "traffic": traffic,
                     "kernel": dom["kernel"], "avg_kernel_us": us, "hbm": hbm,
                     "valu_profile": "absent or taken of another kernel source"}
-    roofline["single_step_kernel"] = kern["single_step"]
-    # the timed region's own path: three steps per pass (k_march) where the
-    # library finds that faster than the two-step pass above
-    roofline["plain_stepping"] = kern["plain_stepping"]
+    for name in ("two_step", "single_step"):
+        if name in kern and name != plain:
+            roofline[name + "_kernel"] = kern[name]
     log("stepping kernels:", json.dumps(kern))
     log("roofline:", json.dumps(roofline))
 
@@ -855,13 +868,13 @@ def main():
         "config": {"workload": "single %dx%d periodic lattice, fp32 state, fp64 observables every %d steps"
                                % (L, L, args.every),
                    "L": L, "T": spec.schedule[0][1], "seed": spec.seed, "launch": list(launch),
-                   "steps_per_pass": fusion[0], "rows_per_strip": fusion[1]},
+                   "stepping_path": path[0], "steps_per_pass": path[1]},
         "roofline": roofline,
         "cpu_baseline": cpu,
         "device": device_info(torch),
     }
     # the metric's "% HBM roofline": site-updates/s x 16 B per site-update over
-    # 8 TB/s (above 100 when two steps share one pass over the state)
+    # 8 TB/s (above 100 when steps share a pass over the state)
     line["pct_hbm_roofline"] = 100.0 * value * BYTES_PER_SITE_F32 / (HBM_PEAK_GBS * 1e9)
     if "adjoint_512" in extras and "adjoint_over_forward" in extras["adjoint_512"]:
         line["adjoint_over_forward"] = extras["adjoint_512"]["adjoint_over_forward"]
