@@ -714,6 +714,17 @@ static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
     *p = march_plan(h->Lx, h->Ly, h->cus);
     return p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
 }
+// Steps of a run of n that go three per pass: pairs of passes, 6m steps.  The
+// last two or three of a run would be single steps; where six, two of them
+// single, take longer than eight on two-step passes, eight are left to those
+// (4096^2: a call of 8 steps 238 us so against 260, of 20 steps 512 against 538).
+static uint64_t lattice_march_steps(const xyl_lattice* h, uint64_t n, MarchPlan* p) {
+    if (n < 2 * kMarchSteps || !lattice_march_plan(h, p)) return 0;
+    const uint64_t r = n % (2 * kMarchSteps), m = n - r;
+    const bool eight = (r == 2 || r == 3) && step2_eligible(h) &&
+                       2 * kMarchSteps * p->us + 2 * lattice_single_us(h) > 8 * lattice_step2_us(h);
+    return eight ? m - 2 * kMarchSteps : m;
+}
 static double lattice_untiled_us(const xyl_lattice* h) {
     MarchPlan p;
     if (lattice_march_plan(h, &p)) return p.us;
@@ -820,8 +831,8 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
     }
     if constexpr (sizeof(R) == 4) {
         MarchPlan mp;
-        if (mode == kStore && part_stride == 0 && n >= 2 * kMarchSteps && lattice_march_plan(h, &mp) &&
-            lattice_second_u(h, &h->march)) {
+        uint64_t m = mode == kStore && part_stride == 0 ? lattice_march_steps(h, n, &mp) : 0;
+        if (m && lattice_second_u(h, &h->march)) {
             // pairs of passes, (A, u) -> (B, u2) -> (A, u): six steps later A
             // again holds the angles of its parity
             Lat<float> v3 = h->view<float>();
@@ -831,7 +842,7 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
             float* B = static_cast<float*>(h->th[parity ^ 1]);
             float* u = static_cast<float*>(h->u);
             float* u2 = reinterpret_cast<float*>(h->u2.p);
-            for (; n >= 2 * kMarchSteps; n -= 2 * kMarchSteps) {
+            for (n -= m; m > 0; m -= 2 * kMarchSteps) {
                 launch_march(v3, MarchBuffers{A, u, B, u2}, mp, h->k, h->stream);
                 launch_march(v3, MarchBuffers{B, u2, A, u}, mp, h->k + kMarchSteps, h->stream);
                 h->k += 2 * kMarchSteps;
@@ -2010,7 +2021,7 @@ int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* s
             const uint64_t nl = tile_launches(nsteps, tp->T);
             p = XYL_PATH_TILES;
             t = (int)((nsteps + nl - 1) / nl);
-        } else if (nsteps >= 2 * kMarchSteps && lattice_march_plan(h, &mp)) {
+        } else if (lattice_march_steps(h, nsteps, &mp)) {
             p = XYL_PATH_MARCH;
             t = kMarchSteps;
         } else if (nsteps >= 4 && step2_eligible(h)) {
