@@ -314,6 +314,9 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves);
 int xyl_get_step2_shape(const xyl_lattice* h, int32_t* rows, int32_t* tile_waves, int32_t* tiles);
 
 /* -------------------------------------------------------------- test hooks */
+/* Goes on as if the lattice's second velocity buffer did not fit: single steps
+ * from now on. */
+int xyl_deny_second_buffer(xyl_lattice* h);
 /* Raw Philox4x32-10 blocks computed on the device: for j < n, counter
  * ctr[4j..4j+3] and key (seed_lo, seed_hi) -> out[4j..4j+3]. */
 int xyl_philox_blocks(int32_t device, uint64_t seed, const uint32_t* ctr, uint32_t* out, uint64_t n);

@@ -430,7 +430,8 @@ struct xyl_lattice {
     std::map<uint64_t, TilePlan> tile_plans;   // by the steps to take (T = 0: none)
     int adj2_rows = 0;             // rows per strip of the two-step reverse pass (0: the rule)
     int adj_fusion = 2;            // reverse steps per pass of the adjoint sweep (1 or 2)
-    DevBuf<char> u2;               // second velocity buffer of the two-step passes
+    DevBuf<char> u2;               // second velocity buffer of the paths with several steps per launch
+    bool second_u = true;          // false: it did not fit
     // device scratch
     DevBuf<uint64_t> kdev;
     DevBuf<double> part;
@@ -732,28 +733,33 @@ static double lattice_untiled_us(const xyl_lattice* h) {
     return lattice_single_us(h);
 }
 
-// The second velocity buffer of a path that the lattice can do without: where
-// it does not fit, the path is given up.  While the caller captures the stream
-// nothing is allocated: such a call takes another path.
-static bool lattice_second_u(xyl_lattice* h, bool* path) {
-    const size_t bytes = elem_size(h->dtype) * h->N;
-    if (!h->u2.p || h->u2.n < bytes) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
-        if (st != hipStreamCaptureStatusNone) return false;
+// Whether the caller captures the lattice's stream (or it cannot be told):
+// nothing is allocated and no graph of the library's is launched then.
+static bool stream_captured(const xyl_lattice* h) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
     }
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The second velocity buffer, which every path but single steps needs: where it
+// does not fit, and in a caller's capture before it exists, the steps go one by
+// one.
+static bool lattice_second_u(xyl_lattice* h) {
+    const size_t bytes = elem_size(h->dtype) * h->N;
+    if (!h->second_u) return false;
+    if (h->u2.p && h->u2.n >= bytes) return true;
+    if (stream_captured(h)) return false;
     try {
         h->u2.reserve(bytes);
     } catch (const Error& e) {
         if (e.code != XYL_ENOMEM) throw;
         (void)hipGetLastError();
-        *path = false;
-        return false;
+        h->second_u = false;
     }
-    return true;
+    return h->second_u;
 }
 
 // Widths above 4096 and lattices beyond 2^24 sites never gain by tiles (their
@@ -788,7 +794,7 @@ static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
 // The same with the second velocity buffer that the tiles need.
 static const TilePlan* lattice_tile_plan(xyl_lattice* h, uint64_t n) {
     const TilePlan* p = lattice_tile_choice(h, n);
-    return p && lattice_second_u(h, &h->tiles) ? p : nullptr;
+    return p && lattice_second_u(h) ? p : nullptr;
 }
 
 // n steps through an even number of launches, (A, u) -> (B, u2) -> (A, u), A
@@ -832,7 +838,7 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
     if constexpr (sizeof(R) == 4) {
         MarchPlan mp;
         uint64_t m = mode == kStore && part_stride == 0 ? lattice_march_steps(h, n, &mp) : 0;
-        if (m && lattice_second_u(h, &h->march)) {
+        if (m && lattice_second_u(h)) {
             // pairs of passes, (A, u) -> (B, u2) -> (A, u): six steps later A
             // again holds the angles of its parity
             Lat<float> v3 = h->view<float>();
@@ -850,13 +856,13 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
             h->counter_valid = false;
             if (n == 0) return;
         }
-        if (mode == kStore && part_stride == 0 && step2_eligible(h) && n >= 4) {
-            h->u2.reserve(sizeof(float) * h->N);
+        if (mode == kStore && part_stride == 0 && step2_eligible(h) && n >= 4 && lattice_second_u(h)) {
             Lat<float> v2 = h->view<float>();
             v2.k_base = 0;
             const uint64_t n4 = n - n % 4;
             uint64_t done = 0;
-            const int S = h->graph_steps - h->graph_steps % 4;
+            int S = h->graph_steps - h->graph_steps % 4;
+            if (S >= 4 && n4 >= (uint64_t)S && stream_captured(h)) S = 0;
             while (done < n4) {
                 const int parity = (int)((h->k + (uint64_t)h->cur) & 1);
                 if (S >= 4 && n4 - done >= (uint64_t)S) {
@@ -903,8 +909,9 @@ static void lattice_steps_mode(xyl_lattice* h, uint64_t n, int mode, double* par
         v.part_k0 = part_k0;
         v.part_stride = part_stride;
     }
+    int S = h->graph_steps;
+    if (S > 1 && n >= (uint64_t)S && stream_captured(h)) S = 0;
     while (n > 0) {
-        const int S = h->graph_steps;
         if (S > 1 && n >= (uint64_t)S) {
             xyl_lattice::GraphEntry* ge = nullptr;
             for (auto& g : h->graphs)
@@ -2017,7 +2024,8 @@ int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* s
         require(h != nullptr, XYL_EINVAL, "NULL handle");
         int p = XYL_PATH_SINGLE, t = 1;
         MarchPlan mp;
-        if (const TilePlan* tp = lattice_tile_choice(h, nsteps)) {
+        if (!h->second_u) {
+        } else if (const TilePlan* tp = lattice_tile_choice(h, nsteps)) {
             const uint64_t nl = tile_launches(nsteps, tp->T);
             p = XYL_PATH_TILES;
             t = (int)((nsteps + nl - 1) / nl);
@@ -2074,6 +2082,13 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps) {
         require(steps >= 0 && steps <= 4096, XYL_EINVAL, "graph steps must be in [0, 4096]");
         h->graph_steps = steps;
         h->touch();
+    });
+}
+
+int xyl_deny_second_buffer(xyl_lattice* h) {
+    return guarded([&] {
+        require(h != nullptr, XYL_EINVAL, "NULL handle");
+        h->second_u = false;
     });
 }
 
