@@ -251,12 +251,15 @@ int xyl_sync(xyl_lattice* h);
  * workgroup (1, 2, 4 or 8); 0 keeps the current value.  Results do not
  * depend on it.  xyl_autotune times candidates on this lattice (as captured
  * graphs on scratch copies of the state, which it leaves untouched) and keeps
- * the fastest; for FP32 lattices that two steps per pass apply to, it also
- * times that pass at several strip heights and sets the steps per pass
- * (xyl_set_fusion) to whichever of 1 and 2 is faster per step; it also picks
+ * the fastest; it then times the paths with more steps per launch that the
+ * lattice's shape, precision and parameters allow (two steps per pass at
+ * several strip heights, three steps per pass, tiles) and keeps the fastest
+ * path, with single steps (xyl_set_fusion's 1) where those are; it also picks
  * the launch shape of the measurements that sampled runs take (results do
- * not depend on it either).  The choices are cached per (shape, precision)
- * for the process and applied to lattices created later. */
+ * not depend on it either).  The choices are kept for the process, the launch
+ * shapes per shape and precision, the path per model and form of the kick
+ * (whether the couplings allow its factored FP32 form) too, and applied to
+ * lattices created later whose caller sets no path. */
 int xyl_set_launch(xyl_lattice* h, int32_t rows_per_strip, int32_t waves_per_block);
 int xyl_get_launch(xyl_lattice* h, int32_t* rows_per_strip, int32_t* waves_per_block);
 int xyl_autotune(xyl_lattice* h);

@@ -352,13 +352,17 @@ static size_t elem_size(int dtype) { return dtype == XYL_F64 ? sizeof(double) : 
 // -------------------------------------------------------- launch tuning
 static std::mutex g_tune_mu;
 static std::map<std::tuple<int, int, int>, Launch> g_tuned;
-// steps per pass, rows per strip and waves per column tile of the two-step
-// pass, chosen by xyl_autotune
+// How runs of steps go, as xyl_autotune measured it: the steps per pass, the
+// rows per strip and the waves per column tile of the two-step pass, and
+// whether tiles or the three-step pass were the fastest (the rules' choice
+// where nothing was measured).
+enum : int { kByRule = 0, kChosen = 1, kSlower = 2 };
 struct Tuned2 {
-    int fusion, rows, tile_waves;
-    bool tiles;            // several steps per launch on tiles
+    int fusion = 2, rows = 0, tile_waves = 0;
+    int tiles = kByRule, march = kByRule;
 };
-static std::map<std::tuple<int, int, int>, Tuned2> g_tuned2;
+// by Lx, Ly, precision, model and form of the FP32 kick
+static std::map<std::tuple<int, int, int, int, int>, Tuned2> g_tuned2;
 // launch shape of measurements without a step, chosen by xyl_autotune
 static std::map<std::tuple<int, int, int>, Launch> g_tunedm;
 
@@ -422,11 +426,11 @@ struct xyl_lattice {
     bool counter_valid = false;
     int fusion = 2;                // steps per pass of plain FP32 stepping where the shape allows (1 or 2)
     int cus = 256;                 // compute units of the device
-    bool march = true;             // three steps per pass where the rule takes it (xyl_march.hip)
+    int march = kByRule;           // three steps per pass (xyl_march.hip)
     int step2_rows_tuned = 0;      // rows per strip of the two-step pass from xyl_autotune (0: the size rule)
     int step2_tw_tuned = 0;        // most waves per column tile (widths above 4096) from xyl_autotune (0: the rule)
-    bool tiles = true;             // several steps per launch on tiles allowed
-    bool tiles_tuned = false;      // xyl_autotune timed them faster: no rule needed
+    int tiles = kByRule;           // several steps per launch on tiles
+    bool own_path = false;         // the caller set or tuned the path: the process's record is not looked up again
     std::map<uint64_t, TilePlan> tile_plans;   // by the steps to take (T = 0: none)
     int adj2_rows = 0;             // rows per strip of the two-step reverse pass (0: the rule)
     int adj_fusion = 2;            // reverse steps per pass of the adjoint sweep (1 or 2)
@@ -711,9 +715,9 @@ static double lattice_single_us(const xyl_lattice* h) {
 }
 static bool march_shape_ok(int dtype, int Ly) { return dtype == XYL_F32 && Ly >= 4; }
 static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
-    if (!h->march || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
+    if (h->march == kSlower || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
     *p = march_plan(h->Lx, h->Ly, h->cus);
-    return p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
+    return h->march == kChosen || p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
 }
 // Steps of a run of n that go three per pass: pairs of passes, 6m steps.  The
 // last two or three of a run would be single steps; where six, two of them
@@ -771,7 +775,7 @@ static bool tile_shape_ok(int Lx, int Ly) {
 // steps (n >= 2), or NULL where another path is faster by the rules' times.
 // Plans are kept per run length (64 steps and more share one).
 static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
-    if (!h->tiles || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
+    if (h->tiles == kSlower || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
     const uint64_t key = std::min<uint64_t>(n, 64);
     auto it = h->tile_plans.find(key);
     if (it == h->tile_plans.end()) {
@@ -783,10 +787,11 @@ static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
         // and march: 1500^2 5.8 and 6.5 us per step, 1604^2 8.0 and 6.7, 1800^2
         // 7.8 and 7.5, 2048 x 1024 5.3 and 5.9, 3000 x 1000 6.9 and 7.1).
         // (tiles reach 4.7e5 sites per us at best)
-        const bool hopeless = !h->tiles_tuned && (double)h->N > 4.8e5 * lattice_untiled_us(h);
+        const bool rule = h->tiles == kByRule;
+        const bool hopeless = rule && (double)h->N > 4.8e5 * lattice_untiled_us(h);
         if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
-            (!h->tiles_tuned && us > lattice_untiled_us(h)) || (lattice_march_plan(h, &mp) && 1.08 * us > mp.us))
-            p = TilePlan();   // (the tuner weighs tiles against the two-step pass and single steps only)
+            (rule && (us > lattice_untiled_us(h) || (lattice_march_plan(h, &mp) && 1.08 * us > mp.us))))
+            p = TilePlan();
         it = h->tile_plans.emplace(key, p).first;
     }
     return it->second.T ? &it->second : nullptr;
@@ -1077,6 +1082,24 @@ int xyl_device_count(void) {
     return m;
 }
 
+// The path that xyl_autotune chose in this process for such a lattice, else the
+// rules'.
+static void apply_tuned_path(xyl_lattice* h) {
+    if (h->own_path) return;
+    Tuned2 t;
+    {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        auto it = g_tuned2.find({h->Lx, h->Ly, h->dtype, h->p.model, (int)kick_factored(h->p)});
+        if (it != g_tuned2.end()) t = it->second;
+    }
+    h->fusion = t.fusion;
+    h->step2_rows_tuned = t.rows;
+    h->step2_tw_tuned = t.tile_waves;
+    if (h->tiles != t.tiles || h->march != t.march) h->tile_plans.clear();
+    h->tiles = t.tiles;
+    h->march = t.march;
+}
+
 static int create_impl(xyl_lattice** out, int32_t Lx, int32_t Ly, int32_t dtype, int32_t device, void* ta, void* tb,
                        void* vel) {
     return guarded([&] {
@@ -1128,14 +1151,8 @@ static int create_impl(xyl_lattice** out, int32_t Lx, int32_t Ly, int32_t dtype,
                 h->mlaunch = itm->second;
                 h->mlaunch_tuned = true;
             }
-            auto it2 = g_tuned2.find({Lx, Ly, dtype});
-            if (it2 != g_tuned2.end()) {
-                h->fusion = it2->second.fusion;
-                h->tiles = h->tiles_tuned = it2->second.tiles;
-                h->step2_rows_tuned = it2->second.rows;
-                h->step2_tw_tuned = it2->second.tile_waves;
-            }
         }
+        apply_tuned_path(h.get());
         *out = h.release();
     });
 }
@@ -1188,6 +1205,7 @@ int xyl_set_params(xyl_lattice* h, double Jx, double Jy, double hf, double gamma
         p.dt = dt;
         validate_params(p);
         h->p = p;
+        apply_tuned_path(h);
         h->touch();
     });
 }
@@ -1199,6 +1217,7 @@ int xyl_set_model(xyl_lattice* h, int32_t model, double pfield) {
         if (model != h->p.model) h->initialized = false;   // the angle ranges differ
         h->p.model = model;
         h->p.p = pfield;
+        apply_tuned_path(h);
         h->touch();
     });
 }
@@ -1754,12 +1773,13 @@ int xyl_get_launch(xyl_lattice* h, int32_t* rows, int32_t* wpb) {
 
 }  // extern "C"
 
-// Times the single-step launch shapes and, for FP32 lattices of a shape the
-// two-step pass takes, the two-step pass at several strip heights; returns
-// the best single-step shape and sets *fusion (1 or 2, whichever is faster
-// per step) and *rows2 (rows per strip of the best two-step pass, 0 if none).
+// Times the single-step launch shapes, for FP32 lattices of a shape the
+// two-step pass takes that pass at several strip heights, the three-step pass
+// and tiles; returns the best single-step shape and sets *t to the fastest path
+// (fusion 1: single steps) with the best two-step shape (rows 0 if none).
 template <typename R>
-static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, bool* tiles, Launch* mlaunch) {
+static Launch autotune_impl(xyl_lattice* h, Tuned2* t, Launch* mlaunch) {
+    int *fusion = &t->fusion, *rows2 = &t->rows, *tw2 = &t->tile_waves;
     // time candidates on scratch copies so the lattice state is untouched;
     // each candidate runs as a captured graph of back-to-back steps, so the
     // host's launch overhead does not mask kernel time on small lattices
@@ -1855,7 +1875,7 @@ static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, b
     }
     float best_step = best_ms / (float)reps;
     // two steps per pass: the same timing over a multiple of 4 steps, per step
-    *fusion = 1;
+    *fusion = sizeof(R) == 4 ? 1 : 2;
     *rows2 = 0;
     *tw2 = 0;
     if constexpr (std::is_same<R, float>::value) {
@@ -1937,34 +1957,55 @@ static Launch autotune_impl(xyl_lattice* h, int* fusion, int* rows2, int* tw2, b
             best_step = std::min(best_step, best2);
         }
     }
-    // several steps per launch on tiles, where a tile fits: 64 steps issued as
-    // the stepping issues them
-    *tiles = false;
-    {
-        TilePlan p;
-        if (h->Lx <= 16 * kWaveSites && tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, 64, &p, nullptr)) {
-            R* th[2] = {v.th[0], v.th[1]};
-            R* u[2] = {v.u, reinterpret_cast<R*>(tmp.p + 3 * bytes)};
-            float t = 1e30f;
-            for (int rep = 0; rep < 4; ++rep) {
-                check_hip(hipEventRecord(e0, h->stream), "hipEventRecord");
-                const uint64_t nl = tile_launches(64, p.T);
-                uint64_t k = 0;
-                for (uint64_t i = 0; i < nl; ++i) {
-                    const int n = (int)(64 / nl + (i < 64 % nl ? 1 : 0)), a = (int)(i & 1);
-                    launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, n, k, h->stream);
-                    k += (uint64_t)n;
+    // the paths with more steps per launch: 60 or 64 steps issued as the
+    // stepping issues them
+    t->tiles = t->march = kSlower;
+    R* th[2] = {v.th[0], v.th[1]};
+    R* u[2] = {v.u, reinterpret_cast<R*>(tmp.p + 3 * bytes)};
+    auto time_direct = [&](int nsteps, auto&& issue) {
+        float best_t = 1e30f;
+        for (int rep = 0; rep < 4; ++rep) {
+            check_hip(hipEventRecord(e0, h->stream), "hipEventRecord");
+            issue();
+            check_hip(hipEventRecord(e1, h->stream), "hipEventRecord");
+            check_hip(hipEventSynchronize(e1), "hipEventSynchronize");
+            float ms = 0.f;
+            check_hip(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
+            if (rep) best_t = std::min(best_t, ms / (float)nsteps);
+        }
+        return best_t;
+    };
+    if constexpr (std::is_same<R, float>::value) {
+        if (march_shape_ok(h->dtype, h->Ly) && kick_factored(h->p)) {
+            const MarchPlan p = march_plan(h->Lx, h->Ly, h->cus);
+            const float ms = time_direct(60, [&] {
+                for (int i = 0; i < 60; i += kMarchSteps) {
+                    const int a = (i / kMarchSteps) & 1;
+                    launch_march(v, MarchBuffers{th[a], u[a], th[a ^ 1], u[a ^ 1]}, p, (uint64_t)i, h->stream);
                 }
-                check_hip(hipEventRecord(e1, h->stream), "hipEventRecord");
-                check_hip(hipEventSynchronize(e1), "hipEventSynchronize");
-                float ms = 0.f;
-                check_hip(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
-                if (rep) t = std::min(t, ms / 64.f);
-            }
-            if (t < best_step) {
-                *tiles = true;
+            });
+            if (ms < best_step) {
+                best_step = ms;
+                t->march = kChosen;
                 *fusion = 2;
             }
+        }
+    }
+    TilePlan p;
+    if (tile_shape_ok(h->Lx, h->Ly) && tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, 64, &p, nullptr)) {
+        const float ms = time_direct(64, [&] {
+            const uint64_t nl = tile_launches(64, p.T);
+            uint64_t k = 0;
+            for (uint64_t i = 0; i < nl; ++i) {
+                const int n = (int)(64 / nl + (i < 64 % nl ? 1 : 0)), a = (int)(i & 1);
+                launch_tile<R>(v, th[a], u[a], th[a ^ 1], u[a ^ 1], p, n, k, h->stream);
+                k += (uint64_t)n;
+            }
+        });
+        if (ms < best_step) {
+            t->tiles = kChosen;
+            t->march = kSlower;
+            *fusion = 2;
         }
     }
     (void)hipEventDestroy(e0);
@@ -1978,28 +2019,22 @@ int xyl_autotune(xyl_lattice* h) {
     return guarded([&] {
         require_init(h);
         DeviceGuard g(h->device);
-        int fusion = 1, rows2 = 0, tw2 = 0;
-        bool tiles = false;
+        Tuned2 t;
         Launch lm;
-        Launch l = h->dtype == XYL_F64 ? autotune_impl<double>(h, &fusion, &rows2, &tw2, &tiles, &lm)
-                                       : autotune_impl<float>(h, &fusion, &rows2, &tw2, &tiles, &lm);
+        const Launch l = h->dtype == XYL_F64 ? autotune_impl<double>(h, &t, &lm) : autotune_impl<float>(h, &t, &lm);
         h->launch = l;
         h->mlaunch = lm;
         h->mlaunch_tuned = true;
-        if (h->dtype == XYL_F32) {
-            h->fusion = fusion;
-            h->step2_rows_tuned = rows2;
-            h->step2_tw_tuned = tw2;
-        } else if (tiles) {
-            h->fusion = 2;
+        {
+            std::lock_guard<std::mutex> lk(g_tune_mu);
+            g_tuned[{h->Lx, h->Ly, h->dtype}] = l;
+            g_tunedm[{h->Lx, h->Ly, h->dtype}] = lm;
+            g_tuned2[{h->Lx, h->Ly, h->dtype, h->p.model, (int)kick_factored(h->p)}] = t;
         }
-        h->tiles = h->tiles_tuned = tiles;
-        h->tile_plans.clear();
+        h->own_path = false;
+        apply_tuned_path(h);
+        h->own_path = true;
         h->touch();
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[{h->Lx, h->Ly, h->dtype}] = l;
-        g_tunedm[{h->Lx, h->Ly, h->dtype}] = lm;
-        g_tuned2[{h->Lx, h->Ly, h->dtype}] = {h->fusion, h->step2_rows_tuned, h->step2_tw_tuned, tiles};
     });
 }
 
@@ -2008,6 +2043,7 @@ int xyl_set_fusion(xyl_lattice* h, int32_t steps_per_pass) {
         require(h != nullptr, XYL_EINVAL, "NULL handle");
         require(steps_per_pass == 1 || steps_per_pass == 2, XYL_EINVAL, "steps_per_pass must be 1 or 2");
         h->fusion = steps_per_pass;
+        h->own_path = true;
     });
 }
 
@@ -2049,7 +2085,10 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves) {
                 "waves per tile must be 0 or in [2, 16]");
         if (rows) h->step2_rows_tuned = rows;
         if (tile_waves) h->step2_tw_tuned = tile_waves;
-        if (rows || tile_waves) h->tiles = h->march = false;   // the caller shapes the two-step pass: take it
+        if (rows || tile_waves) {
+            h->tiles = h->march = kSlower;   // the caller shapes the two-step pass: take it
+            h->own_path = true;
+        }
         h->touch();
     });
 }
