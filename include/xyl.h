@@ -307,9 +307,9 @@ int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* s
  * row's own waves it splits rows up to 4096 sites wide as well, into at least
  * two tiles); 0 keeps the current value.  A tile width no split fits falls
  * back to whole rows (up to 4096 sites) or the fewest tiles.  A lattice whose
- * shape was set takes the two-step pass in place of tiles and of three steps.
- * Results do not depend on it.  xyl_autotune sets both.  EINVAL outside the
- * ranges. */
+ * shape was set takes the two-step pass, where that applies, in place of tiles
+ * and of three steps per pass, until xyl_autotune chooses anew.  Results do not
+ * depend on it.  xyl_autotune sets both.  EINVAL outside the ranges. */
 int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves);
 /* The shape in effect: rows per strip, most waves per tile and the number of
  * column tiles (whole rows: the row's waves and 1); zeros where two steps

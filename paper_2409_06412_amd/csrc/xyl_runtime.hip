@@ -430,6 +430,7 @@ struct xyl_lattice {
     int step2_rows_tuned = 0;      // rows per strip of the two-step pass from xyl_autotune (0: the size rule)
     int step2_tw_tuned = 0;        // most waves per column tile (widths above 4096) from xyl_autotune (0: the rule)
     int tiles = kByRule;           // several steps per launch on tiles
+    bool shaped = false;           // the caller shaped the two-step pass
     bool own_path = false;         // the caller set or tuned the path: the process's record is not looked up again
     std::map<uint64_t, TilePlan> tile_plans;   // by the steps to take (T = 0: none)
     int adj2_rows = 0;             // rows per strip of the two-step reverse pass (0: the rule)
@@ -581,6 +582,9 @@ static bool step2_lattice_shape(int Lx, int Ly) {
 static bool step2_eligible(const xyl_lattice* h) {
     return h->dtype == XYL_F32 && h->fusion == 2 && kick_factored(h->p) && step2_lattice_shape(h->Lx, h->Ly);
 }
+// The caller shaped the two-step pass, and the lattice can take it: it does, in
+// place of tiles and of three steps per pass.
+static bool step2_shaped(const xyl_lattice* h) { return h->shaped && step2_eligible(h); }
 
 // Waves per column tile of the two-step pass when not tuned: rows up to 4096
 // sites wide run whole (one workgroup per strip); wider ones as tiles of at
@@ -715,7 +719,7 @@ static double lattice_single_us(const xyl_lattice* h) {
 }
 static bool march_shape_ok(int dtype, int Ly) { return dtype == XYL_F32 && Ly >= 4; }
 static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
-    if (h->march == kSlower || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
+    if (h->march == kSlower || step2_shaped(h) || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
     *p = march_plan(h->Lx, h->Ly, h->cus);
     return h->march == kChosen || p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
 }
@@ -775,7 +779,7 @@ static bool tile_shape_ok(int Lx, int Ly) {
 // steps (n >= 2), or NULL where another path is faster by the rules' times.
 // Plans are kept per run length (64 steps and more share one).
 static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
-    if (h->tiles == kSlower || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
+    if (h->tiles == kSlower || step2_shaped(h) || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
     const uint64_t key = std::min<uint64_t>(n, 64);
     auto it = h->tile_plans.find(key);
     if (it == h->tile_plans.end()) {
@@ -2031,7 +2035,7 @@ int xyl_autotune(xyl_lattice* h) {
             g_tunedm[{h->Lx, h->Ly, h->dtype}] = lm;
             g_tuned2[{h->Lx, h->Ly, h->dtype, h->p.model, (int)kick_factored(h->p)}] = t;
         }
-        h->own_path = false;
+        h->own_path = h->shaped = false;
         apply_tuned_path(h);
         h->own_path = true;
         h->touch();
@@ -2085,10 +2089,7 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves) {
                 "waves per tile must be 0 or in [2, 16]");
         if (rows) h->step2_rows_tuned = rows;
         if (tile_waves) h->step2_tw_tuned = tile_waves;
-        if (rows || tile_waves) {
-            h->tiles = h->march = kSlower;   // the caller shapes the two-step pass: take it
-            h->own_path = true;
-        }
+        if (rows || tile_waves) h->shaped = h->own_path = true;
         h->touch();
     });
 }
