@@ -432,7 +432,8 @@ struct xyl_lattice {
     int tiles = kByRule;           // several steps per launch on tiles
     bool shaped = false;           // the caller shaped the two-step pass
     bool own_path = false;         // the caller set or tuned the path: the process's record is not looked up again
-    std::map<uint64_t, TilePlan> tile_plans;   // by the steps to take (T = 0: none)
+    // by the steps to take and the form of the kick (T = 0: none)
+    std::map<std::pair<uint64_t, bool>, TilePlan> tile_plans;
     int adj2_rows = 0;             // rows per strip of the two-step reverse pass (0: the rule)
     int adj_fusion = 2;            // reverse steps per pass of the adjoint sweep (1 or 2)
     DevBuf<char> u2;               // second velocity buffer of the paths with several steps per launch
@@ -777,10 +778,12 @@ static bool tile_shape_ok(int Lx, int Ly) {
 }
 // Several steps per launch on tiles (xyl_tile.hip): the plan for a run of n
 // steps (n >= 2), or NULL where another path is faster by the rules' times.
-// Plans are kept per run length (64 steps and more share one).
+// Plans are kept per run length (64 steps and more share one) and form of the
+// kick (the three-step pass that tiles are weighed against has one only).
 static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
     if (h->tiles == kSlower || step2_shaped(h) || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
-    const uint64_t key = std::min<uint64_t>(n, 64);
+    n = std::min<uint64_t>(n, 64);
+    const auto key = std::make_pair(n, kick_factored(h->p));
     auto it = h->tile_plans.find(key);
     if (it == h->tile_plans.end()) {
         TilePlan p;
@@ -793,7 +796,7 @@ static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
         // (tiles reach 4.7e5 sites per us at best)
         const bool rule = h->tiles == kByRule;
         const bool hopeless = rule && (double)h->N > 4.8e5 * lattice_untiled_us(h);
-        if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, key, &p, &us) ||
+        if (hopeless || !tile_plan(h->Lx, h->Ly, h->dtype == XYL_F64, h->cus, n, &p, &us) ||
             (rule && (us > lattice_untiled_us(h) || (lattice_march_plan(h, &mp) && 1.08 * us > mp.us))))
             p = TilePlan();
         it = h->tile_plans.emplace(key, p).first;
@@ -2036,6 +2039,7 @@ int xyl_autotune(xyl_lattice* h) {
             g_tuned2[{h->Lx, h->Ly, h->dtype, h->p.model, (int)kick_factored(h->p)}] = t;
         }
         h->own_path = h->shaped = false;
+        h->tile_plans.clear();
         apply_tuned_path(h);
         h->own_path = true;
         h->touch();

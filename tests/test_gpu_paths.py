@@ -52,3 +52,14 @@ def test_large_lattices_take_three_steps_per_pass(xyl, Lx, Ly, model):
     lat.set_fusion(1)
     assert lat.stepping_path(500) == ("single", 1)
     lat.close()
+
+
+def test_path_follows_the_parameters(xyl):
+    # 1604^2: three steps per pass with the factored kick, tiles without it,
+    # whichever the lattice had first
+    for first in (1.0, 0.0):
+        lat = make(xyl, 1604, 1604, Jx=first)
+        for Jx in (first, 1.0 - first, first):
+            lat.set_params(Jx, -0.1, 0.5, 1.0, 0.01)
+            assert lat.stepping_path(60)[0] == ("march" if Jx else "tiles"), (first, Jx)
+        lat.close()
