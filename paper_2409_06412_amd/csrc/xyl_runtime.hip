@@ -500,9 +500,10 @@ struct AdjState {
     hipGraphExec_t rec_graph[2] = {nullptr, nullptr};        // K recompute steps into buffer b
     hipGraphExec_t rev_graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};   // [b][adjoint parity]
     // tile plans of the recompute and of the reverse steps for segments of
-    // tile_K steps (64 and more share one; rev.T = 0: none fits)
+    // tile_K steps (64 and more share one; T = 0: none fits)
     uint64_t tile_K = 0;
     TilePlan rec, rev;
+    double rec_us = 0.0, rev_us = 0.0;   // their modelled times per step
     // what the captured graphs bake in; they are rebuilt when it changes
     std::vector<uint64_t> graph_key;
     void drop_graphs() {
@@ -3655,6 +3656,28 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
 // where it does not (FP64 rows above 568 sites), single reverse steps.
 static int adjoint2_rows(const xyl_lattice* h) { return h->adj2_rows ? h->adj2_rows : 2; }
 
+// Times per step (us) of the sweep without tiles, for choosing: reverse steps
+// one by one or two per pass (a pass in FP64 by the rounds of its strips: their
+// LDS leaves one workgroup per CU from 288 sites a row on), and recomputed
+// steps one by one or two per pass (storing twice the state, a seventh more
+// than stepping).  Sweeps measured, us per step, tiles for both and neither:
+// FP32 512^2 3.8 and 6.3, 1024^2 9.9 and 15.2, 2048^2 32.4 and 43.2, 4096^2 124
+// and 154 (121 with the recompute two steps per pass); FP64 256^2 5.8 and 11.0,
+// 560^2 13.7 and 22.1, 320 x 1000 13.8 and 17.1, 1024^2 35.6 and 51.9, 1448^2
+// 69.8 and 79.5, but 512^2 12.1 and 11.4 with the reverse two steps per pass,
+// 2048 x 1024 86 and 73, 2048^2 134 and 121, 4096 x 2048 276 and 212.
+static double adjoint_untiled_us(const xyl_lattice* h, bool fuse) {
+    const double N = (double)h->N;
+    if (h->dtype == XYL_F32) return (fuse ? 3.3 : 6.0) + N / 1.5e5;
+    if (!fuse) return 18.0 + N / 7.6e4;
+    const int rows = adjoint2_rows(h), strips = (h->Ly + rows - 1) / rows;
+    const int slots = h->cus * std::max(1, (int)(160 * 1024 / adjoint2_lds<double>(h->Lx, rows)));
+    return 0.95 * ((strips + slots - 1) / slots) * (4.2 + 0.0055 * h->Lx);
+}
+static double adjoint_recompute_us(const xyl_lattice* h, bool two_step) {
+    return two_step ? 1.15 * step2_us(h->Lx, h->Ly, h->cus, step2_rows(h)) : lattice_single_us(h);
+}
+
 template <typename R>
 static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void* dom0, bool dev_out, int out_f64,
                                   double scale) {
@@ -3673,20 +3696,25 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
     // two reverse steps per pass where the rows fit one workgroup's LDS rings
     const int rows2 = adjoint2_rows(h);
     const bool fuse = h->adj_fusion == 2 && adjoint2_fits<R>(v, rows2);
-    // several reverse (and recompute) steps per launch on tiles, unless the
-    // caller shaped the two-step pass: 512^2 FP32 takes 2.8 us per reverse step
-    // so over 5000 steps, the recompute (1.4 us alone) beside it, against 4.9
-    bool tiles = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && tile_shape_ok(h->Lx, h->Ly);
-    if (tiles && a->tile_K != std::min<uint64_t>(K, 64)) {
+    // two recompute steps per pass (storing the state after each) where the
+    // forward's two-step pass takes the lattice whole-row: the same states
+    bool rec2 = false;
+    if constexpr (std::is_same<R, float>::value)
+        rec2 = h->adj_fusion == 2 && v.fact == 1 && v.model == kModelXY && step2_shape(h->Lx, h->Ly);
+    // several reverse and several recompute steps per launch on tiles where
+    // those are faster by the rules' times, unless the caller shaped the
+    // two-step pass
+    const bool may_tile = h->adj_fusion == 2 && h->adj2_rows == 0 && K >= 2 && tile_shape_ok(h->Lx, h->Ly);
+    if (may_tile && a->tile_K != std::min<uint64_t>(K, 64)) {
         a->tile_K = std::min<uint64_t>(K, 64);
         const bool f64 = h->dtype == XYL_F64;
-        if (!tile_plan(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rec, nullptr) ||
-            !tile_plan_reverse(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rev))
-            a->rev = TilePlan();
+        if (!tile_plan(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rec, &a->rec_us)) a->rec = TilePlan();
+        if (!tile_plan_reverse(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rev, &a->rev_us)) a->rev = TilePlan();
     }
     const TilePlan &rev = a->rev, &rec = a->rec;
-    tiles = tiles && rev.T > 0;
-    const int ntasks = tiles ? rev.ntx * rev.nty : adjoint_tasks<R>(v, l.rows, fuse ? rows2 : 0);
+    const bool rev_tiles = may_tile && rev.T > 0 && a->rev_us < adjoint_untiled_us(h, fuse);
+    const bool rec_tiles = may_tile && rec.T > 0 && a->rec_us < adjoint_recompute_us(h, rec2);
+    const int ntasks = rev_tiles ? rev.ntx * rev.nty : adjoint_tasks<R>(v, l.rows, fuse ? rows2 : 0);
     a->gacc.reserve((size_t)ntasks * 4);
     check_hip(hipMemsetAsync(a->gacc.p, 0, sizeof(double) * ntasks * 4, h->stream), "hipMemsetAsync");
     a->lam.reserve(4 * bytes);
@@ -3718,11 +3746,6 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         w.u_out = slot_u(b, j + 1);
         launch_step<R>(w, kStore, h->launch, kdev, kj, st);
     };
-    // two recompute steps per pass (storing the state after each) where the
-    // forward's two-step pass takes the lattice whole-row: the same states
-    bool rec2 = false;
-    if constexpr (std::is_same<R, float>::value)
-        rec2 = h->adj_fusion == 2 && v.fact == 1 && v.model == kModelXY && step2_shape(h->Lx, h->Ly);
     const int rows_rec2 = rec2 ? step2_rows(h) : 0;
     auto recompute_run = [&](int b, uint64_t len, const uint64_t* kdev, uint64_t kbase, hipStream_t st) {
         uint64_t j = 0;
@@ -3815,7 +3838,7 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         const uint64_t ks = k0 + s * K;
         const uint64_t len = std::min<uint64_t>(K, k0 + N - ks);
         const char* ck = a->ckpt.p + s * 2 * bytes;
-        if (tiles && len >= 2) {
+        if (rec_tiles && len >= 2) {
             // states 1 .. len - 1 (the reverse steps need no more), the
             // checkpoint itself into slot 0 on the way
             const uint64_t n = len - 1, nl = (n + rec.T - 1) / rec.T;
@@ -3834,7 +3857,7 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         }
         check_hip(hipMemcpyAsync(slot_th(b, 0), ck, bytes, hipMemcpyDeviceToDevice, a->side), "D2D");
         check_hip(hipMemcpyAsync(slot_u(b, 0), ck + bytes, bytes, hipMemcpyDeviceToDevice, a->side), "D2D");
-        if (tiles) {
+        if (len == 1) {
             // a single step: its state is the checkpoint
         } else if (use_graph && len == K) {
             if (!a->rec_graph[b])
@@ -3862,7 +3885,7 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         check_hip(hipStreamWaitEvent(h->stream, a->ev_rec[b], 0), "hipStreamWaitEvent");
         const uint64_t ks = k0 + s * K;
         const uint64_t len = std::min<uint64_t>(K, k0 + N - ks);
-        if (tiles) {
+        if (rev_tiles) {
             const uint64_t nl = (len + rev.T - 1) / rev.T;
             uint64_t j = len;
             for (uint64_t i = 0; i < nl; ++i) {

@@ -246,8 +246,8 @@ static double tile_alive(int H, int Ly, int t) {
     return H == Ly ? 1.0 : 0.5 + 0.5 * (double)std::max(0, H - t - 1) / H;
 }
 
-// The cheapest plan for n steps with `tables` LDS numbers per site, in an even
-// number of launches or (pairs = false) in any.
+// The cheapest plan for n >= 2 steps, two or more per launch, with `tables` LDS
+// numbers per site, in an even number of launches or (pairs = false) in any.
 static bool tile_search(const TileCost* costs, int tables, bool pairs, int max_lanes, int Lx, int Ly, bool f64, int cus, uint64_t n,
                         TilePlan* plan, double* us) {
     const size_t es = f64 ? 8 : 4;
@@ -255,7 +255,7 @@ static bool tile_search(const TileCost* costs, int tables, bool pairs, int max_l
     double best = 1e30;
     for (int i = 0; i < 2; ++i) {
         const TileCost& c = costs[i];
-        for (int T = pairs ? 2 : 1; T <= 12; ++T) {
+        for (int T = 2; T <= 12; ++T) {
             const uint64_t nl = pairs ? tile_launches(n, T) : (n + T - 1) / T;
             const int t = (int)((n + nl - 1) / nl);      // the longest launch's steps
             if (t < T && T > 2) continue;                // as a smaller T
@@ -304,12 +304,12 @@ bool tile_plan(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, do
     return tile_search(f64 ? kCost64 : kCost32, 4, true, kTileMaxThreads, Lx, Ly, f64, cus, n, plan, us);
 }
 
-bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan) {
+bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us) {
     // (FP64 regions of more than 512 lanes would spill)
     static const TileCost rev32[] = {{4, 4.0, 0.35, 0.80, 0.62, 16}, {2, 4.0, 0.2, 0.50, 0.36, 16}};
     static const TileCost rev64[] = {{2, 4.0, 0.5, 1.50, 1.25, 8}, {1, 4.0, 0.3, 0.90, 0.88, 12}};
-    if (Lx % kLaneSites != 0 || n < 1) return false;
-    return tile_search(f64 ? rev64 : rev32, 6, false, f64 ? 512 : kTileMaxThreads, Lx, Ly, f64, cus, n, plan, nullptr);
+    if (Lx % kLaneSites != 0 || n < 2) return false;
+    return tile_search(f64 ? rev64 : rev32, 6, false, f64 ? 512 : kTileMaxThreads, Lx, Ly, f64, cus, n, plan, us);
 }
 
 // The fewest tiles of a lattice whose regions fit `lanes` lanes of S sites;

@@ -125,6 +125,6 @@ void launch_adjoint_tile(const Lat<R>& v, const R* states, const R* lt_in, const
                          const double* cm, uint64_t cm_base, double* gacc, const TilePlan& p, int T, uint64_t k,
                          hipStream_t s);
 // tile_plan for the reverse steps of the adjoint (any number of launches).
-bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan);
+bool tile_plan_reverse(int Lx, int Ly, bool f64, int cus, uint64_t n, TilePlan* plan, double* us);
 
 }  // namespace xyl
