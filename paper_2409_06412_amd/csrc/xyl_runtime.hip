@@ -3588,6 +3588,8 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
     // the window's measurement partials, one block per step, reduced together
     // at the end (falls back to one reduction per step for huge lattices)
     const uint64_t stride = (uint64_t)h->nrowparts() * kNPart;
+    // (on tiles in pieces whose partials take 64 MB at most)
+    constexpr uint64_t kMaxWindowBytes = uint64_t(64) << 20;
     const bool tiles = lattice_tile_plan(h, std::min<uint64_t>(K, W)) != nullptr;
     const bool batched = !tiles && (double)W * (double)stride * 8.0 <= 1.0e9;
     if (batched) a->win.reserve(W * stride);
@@ -3603,8 +3605,9 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
                 // (single steps where a piece of the window is too short)
                 const TilePlan* tp = tiles ? lattice_tile_plan(h, kend - h->k) : nullptr;
                 if (tp) {
-                    const uint64_t n = kend - h->k, i = h->k - kw;
                     const size_t parts = (size_t)tile_order_parts(*tp);
+                    const uint64_t most = std::max<uint64_t>(kMaxWindowBytes / (parts * sizeof(double)), 64);
+                    const uint64_t n = std::min(kend - h->k, most), i = h->k - kw;
                     a->win.reserve(n * parts);
                     lattice_tile_steps<R>(h, *tp, n, a->win.p);
                     launch_tile_order_sum(a->win.p, (int)parts, (double)h->N, a->obs.p + 6 * i, (int)n, h->stream);
