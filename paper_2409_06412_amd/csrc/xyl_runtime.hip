@@ -176,6 +176,8 @@ struct SpectrumBufs {
 // 950 us); here the device writes one slot of a pinned ring while the host
 // empties another (600 us).  The ring is made by the second copy of at least
 // kMin bytes: pinning and first touching it takes as long as it saves once.
+// Memory that the runtime knows (pinned by the caller) takes the copy directly:
+// 2048^2 with labels 425 us, through the ring 750.
 struct HostRing {
     static constexpr size_t kSlot = size_t(1) << 20, kMin = size_t(2) << 20;
     static constexpr int kSlots = 2;
@@ -209,9 +211,17 @@ struct HostRing {
         }
         return true;
     }
+    static bool pageable(const void* p) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+            (void)hipGetLastError();
+            return true;
+        }
+        return a.type == hipMemoryTypeUnregistered;
+    }
     // dst = src after what the stream holds; returns when dst is complete
     void copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
-        if (bytes < kMin || !ready()) {
+        if (bytes < kMin || !pageable(dst) || !ready()) {
             check_hip(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s), "D2H");
             check_hip(hipStreamSynchronize(s), "hipStreamSynchronize");
             return;
