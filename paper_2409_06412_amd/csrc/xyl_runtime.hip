@@ -2237,6 +2237,11 @@ struct xyl_ensemble {
     // replica ids the tables were built for (every replica that steps), and
     // those of them that the strip kernels measure (not the LDS path's)
     std::vector<int> task_active, task_meas;
+    // the tables serve neither steps nor measurements any more
+    void drop_tables() {
+        task_active.clear();
+        task_meas.clear();
+    }
     // tasks: [0, ntasks_flat) stepped by two-step classes or tile-table steps,
     // [ntasks_flat, ntasks) on tiles; [0, ntasks_meas) those of task_meas
     int ntasks_flat = 0, ntasks_meas = 0;
@@ -3306,7 +3311,7 @@ int xyl_ensemble_autotune(xyl_ensemble* e) {
         require(e != nullptr, XYL_EINVAL, "NULL handle");
         DeviceGuard g(e->device);
         e->launch = e->dtype == XYL_F64 ? ensemble_autotune_impl<double>(e) : ensemble_autotune_impl<float>(e);
-        e->task_active.clear();   // rebuild the tile table with the new strip height
+        e->drop_tables();   // the strips have a new height
     });
 }
 
@@ -3522,7 +3527,7 @@ int xyl_ensemble_set_state(xyl_ensemble* e, int32_t r, const double* theta, cons
         e->k[r] = step;
         e->fresh_k[r] = step;
         e->last_sample[r] = 0;
-        e->task_active.clear();   // force a table rebuild
+        e->drop_tables();   // they hold the replica's former step
         const size_t es = elem_size(e->dtype);
         void* up = static_cast<char*>(e->u) + es * e->off[r];
         if (e->dtype == XYL_F64) {
