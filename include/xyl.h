@@ -298,7 +298,7 @@ int xyl_get_fusion(const xyl_lattice* h, int32_t* steps_per_pass, int32_t* rows)
  * *steps_per_launch the most steps that one launch takes.  Where the second
  * velocity buffer turns out not to fit, or is missing while the caller captures
  * the stream, a run takes XYL_PATH_SINGLE instead.  Either pointer may be NULL. */
-enum { XYL_PATH_SINGLE = 1, XYL_PATH_TWO_STEP = 2, XYL_PATH_MARCH = 3, XYL_PATH_TILES = 4 };
+enum { XYL_PATH_SINGLE = 1, XYL_PATH_TWO_STEP = 2, XYL_PATH_MARCH = 3, XYL_PATH_TILES = 4, XYL_PATH_LDS = 5 };
 int xyl_stepping_path(xyl_lattice* h, uint64_t nsteps, int32_t* path, int32_t* steps_per_launch);
 /* Shape of the two-step pass (App. B's data-parallel sweep, two BBK steps of
  * App. A.1 per pass): rows per strip (2 to 64) and, for widths above 4096,
@@ -435,6 +435,12 @@ int xyl_ensemble_set_mode(xyl_ensemble* e, int32_t mode);
  * task tables, the launch shape or the steps per pass change.  Results are
  * bitwise the same in every mode. */
 int xyl_ensemble_set_graphs(xyl_ensemble* e, int32_t enable);
+/* The path (XYL_PATH_*) on which each replica took, or would have taken, the
+ * last chunk of the batched mode: the steps between two samples or ends.
+ * XYL_PATH_LDS: whole in one workgroup's LDS, several steps per launch.  The
+ * choice follows the chunk's length: fewer than 4 steps, fewer than 8, fewer
+ * than 16, and longer ones have a plan each. */
+int xyl_ensemble_paths(xyl_ensemble* e, int32_t* path);
 /* Steps per pass for the batched mode (1 or 2; default 2).  With 2 (FP32),
  * runs of 4m steps between samples advance the replicas on the tile path
  * whose width the two-step pass takes (as for xyl_set_fusion) two steps per

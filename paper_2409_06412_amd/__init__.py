@@ -58,7 +58,7 @@ class ReplicaDesc(ctypes.Structure):
 MODELS = {"xy": 0, "si": 1}
 
 # XYL_PATH_*: how a run of steps is launched
-PATHS = {1: "single", 2: "two_step", 3: "march", 4: "tiles"}
+PATHS = {1: "single", 2: "two_step", 3: "march", 4: "tiles", 5: "lds"}
 
 
 def _model_code(model) -> int:
@@ -129,6 +129,7 @@ _SIGS = {
     "xyl_ensemble_set_state": (_i32, [_vp, _i32, P(_d), P(_d), _u64]),
     "xyl_ensemble_domains": (_i32, [_vp, _i32, P(_i32), P(_u64), P(_u64), _u64, P(_u64), P(_u64), P(_u64)]),
     "xyl_ensemble_sync": (_i32, [_vp]),
+    "xyl_ensemble_paths": (_i32, [_vp, P(_i32)]),
     "xyl_adjoint_forward": (_i32, [_vp, _u64, _u64, _u64, P(_d), P(_u64)]),
     "xyl_adjoint_backward": (_i32, [_vp, _u64, P(_d), P(_d), P(_d)]),
     "xyl_adjoint_backward_device": (_i32, [_vp, _u64, _d, P(_d), _vp, _vp, _i32]),
@@ -665,6 +666,13 @@ class Ensemble:
         S = np.empty(int(kmax) + 1)
         _check(load().xyl_ensemble_structure_factor(self._h, int(r), int(axis), int(kmax), _pd(S)))
         return S
+
+    def paths(self):
+        """The path of each replica in the last chunk of batched steps:
+        "single", "two_step", "tiles" or "lds" (whole in LDS)."""
+        p = (_i32 * self.n)()
+        _check(load().xyl_ensemble_paths(self._h, p))
+        return [PATHS[v] for v in p]
 
     def sync(self):
         _check(load().xyl_ensemble_sync(self._h))

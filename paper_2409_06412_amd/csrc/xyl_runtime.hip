@@ -2232,28 +2232,65 @@ struct xyl_ensemble {
     uint64_t j = 0;                 // batched launches issued
     Launch launch;
     DevBuf<char> reps;              // Lat<R>[n]
-    DevBuf<Task> tasks;
-    int ntasks = 0;
-    // replica ids the tables were built for (every replica that steps), and
-    // those of them that the strip kernels measure (not the LDS path's)
-    std::vector<int> task_active, task_meas;
+    bool reps_ok = false;           // reps holds every active replica's view
+    // two steps per pass for FP32 replicas on the tile path: one batched launch
+    // per class of replicas spanning the same number of waves, per pass; the
+    // other tile-path replicas keep one tile launch per step (tasks_rest)
+    struct Step2Class {
+        int waves = 0;
+        bool partial = false;
+        int max_lx = 0;
+        int rows = 0;
+        DevBuf<Task2> tasks;
+        int ntasks = 0;
+    };
+    // How the replicas step in chunks of one class of lengths, and the launches'
+    // tables.  They are kept per class, so that a first short chunk decides
+    // nothing for long ones, and alternating lengths rebuild nothing.
+    struct Tables {
+        bool built = false;
+        std::vector<int> planned_for;   // the active replicas that the plan was made for
+        std::vector<int> strips;        // those of them in the tables: all but the LDS path's own
+        std::vector<int> meas;          // those that the strip kernels measure: not the LDS path's
+        // tasks: [0, ntasks_flat) stepped by two-step classes or tile-table
+        // steps, [ntasks_flat, ntasks) on tiles; [0, ntasks_meas) those of meas
+        DevBuf<Task> tasks;
+        int ntasks = 0, ntasks_flat = 0, ntasks_meas = 0;
+        // replicas that take several steps per launch on tiles (xyl_tile.hip)
+        TilePlan tile_shape;            // T = 0: none
+        size_t tile_lds = 0;
+        std::map<std::pair<int, int>, std::pair<int, int>> boxes;   // tiles of each distinct size
+        DevBuf<TileTask> tiles;
+        int ntiles = 0;
+        std::vector<char> tiled;        // per replica: on tiles (one of the LDS path then only measures in LDS)
+        std::vector<Step2Class> s2cls;
+        DevBuf<Task> tasks_rest;
+        int ntasks_rest = 0;
+        // groups of replicas stepped in parallel: the two-step classes, the tiles
+        size_t groups() const { return s2cls.size() + (ntiles ? 1 : 0); }
+        // the tile fits of the sizes met so far
+        std::unique_ptr<TileFits> fits;
+        std::vector<TileSize> fit_sizes;
+    };
+    static constexpr int kLengths = 4;
+    Tables tables[kLengths];
+    Tables* tab = &tables[0];       // of the last chunk
+    static int length_class(uint64_t n) { return n < 4 ? 0 : n < 8 ? 1 : n < 16 ? 2 : 3; }
+    // the length that a class' plan is made for
+    static uint64_t plan_length(int cls) {
+        constexpr uint64_t n[kLengths] = {1, 6, 12, 200};
+        return n[cls];
+    }
+    bool tiles_ok = true;           // false: no memory for the second velocity buffer
     // the tables serve neither steps nor measurements any more
     void drop_tables() {
-        task_active.clear();
-        task_meas.clear();
+        reps_ok = false;
+        for (Tables& t : tables) {
+            t.built = false;
+            t.planned_for.clear();
+            t.meas.clear();
+        }
     }
-    // tasks: [0, ntasks_flat) stepped by two-step classes or tile-table steps,
-    // [ntasks_flat, ntasks) on tiles; [0, ntasks_meas) those of task_meas
-    int ntasks_flat = 0, ntasks_meas = 0;
-    // replicas that take several steps per launch on tiles (xyl_tile.hip)
-    TilePlan tile_shape;            // T = 0: none
-    size_t tile_lds = 0;
-    DevBuf<TileTask> tiles;
-    int ntiles = 0;
-    bool tiles_ok = true;           // false: no memory for the second velocity buffer
-    std::vector<char> tiled;        // per replica: on tiles (one of the LDS path then only measures in LDS)
-    // groups of replicas stepped in parallel: the two-step classes, the tiles
-    size_t groups() const { return s2cls.size() + (ntiles ? 1 : 0); }
     DevBuf<double> part;
     DevBuf<double> phases;                  // measurement phase tables, one per side length
     std::map<int, size_t> phase_off;        // side length -> offset of its table in phases
@@ -2281,23 +2318,9 @@ struct xyl_ensemble {
     hipEvent_t ev_lds[2] = {nullptr, nullptr};
     bool ev_lds_used[2] = {false, false};
     int lds_buf = 0;
-    // two steps per pass for FP32 replicas on the tile path: one batched launch
-    // per class of replicas spanning the same number of waves, per pass; the
-    // other tile-path replicas keep one tile launch per step (tasks_rest)
-    struct Step2Class {
-        int waves = 0;
-        bool partial = false;
-        int max_lx = 0;
-        int rows = 0;
-        DevBuf<Task2> tasks;
-        int ntasks = 0;
-    };
     int fusion = 2;
     int cus = 256;
     int tables_fusion = 0;          // fusion setting the task tables were built for
-    std::vector<Step2Class> s2cls;
-    DevBuf<Task> tasks_rest;
-    int ntasks_rest = 0;
     DevBuf<char> u2;                // second velocity buffer, allocated on first use
     // the classes hold different replicas: all but the first run on streams of
     // their own (default priority), forked from and joined to the ensemble's
@@ -2412,22 +2435,26 @@ static int class_rows(const xyl_ensemble* e, int waves, const std::vector<int>& 
 //     all of them take about 3.
 //   * Other widths: single tile-table steps, lattice_untiled_us's form.
 //   * Tiles: TileFits::best.
-// Sets e->tile_shape (T = 0: no tiles) and on_tiles[r], and returns the tiles
-// of each distinct size.  Another split than none is taken only where it gains
-// 5%.
-static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ensemble* e, const std::vector<int>& active,
-                                                                       uint64_t n, std::vector<char>& on_tiles) {
-    std::map<std::pair<int, int>, std::pair<int, int>> out;
-    on_tiles.assign(e->n, 0);
-    e->tile_shape = TilePlan();
-    e->tile_lds = 0;
+// For chunks of n steps; another split than none is taken only where it gains
+// 5%, 30% in chunks of fewer than 16 steps: those pay two launches and more for
+// tiles, one whole in LDS, and new tables whenever one of the replicas ends (48
+// replicas of 32^2 to 64^2 that end 7 steps apart: 2.8 ms with a few of them on
+// tiles, 2.4 all in LDS).
+struct EnsTilePlan {
+    TilePlan shape;                 // T = 0: no tiles
+    size_t lds = 0;
+    std::map<std::pair<int, int>, std::pair<int, int>> boxes;
+    std::vector<char> tiled;
+};
+static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, const std::vector<int>& active, uint64_t n) {
+    EnsTilePlan out;
+    out.tiled.assign(e->n, 0);
     if (e->fusion != 2 || n < 4 || !e->tiles_ok) return out;
     const bool f64 = e->dtype == XYL_F64;
     // units that step on tiles or not: 0 the LDS replicas, 1..16 the two-step
     // classes, 17 the others
     constexpr int kUnits = 18;
     std::vector<std::vector<int>> unit(kUnits);
-    std::vector<char> fixed(kUnits, 0);
     double lds_fixed_sites = 0.0;
     for (int r : active) {
         const xyl_replica_desc& d = e->desc[r];
@@ -2487,8 +2514,10 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
         used.push_back(q);
     }
     if (used.empty()) return out;
-    std::vector<TileSize> sizes;
+    // the sizes' fits are kept: a replica that ends changes the counts only
+    std::vector<TileSize>& sizes = tab.fit_sizes;
     std::vector<int> size_of(e->n, -1);
+    const size_t known = sizes.size();
     for (int q : used)
         for (int r : unit[q]) {
             const int Lx = e->desc[r].Lx, Ly = e->desc[r].Ly;
@@ -2502,9 +2531,11 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
             }
             size_of[r] = (int)i;
         }
+    if (!tab.fits || sizes.size() != known) tab.fits.reset(new TileFits(sizes, f64, e->cus, n));
+    const TileFits& fits = *tab.fits;
     // (more than 6 units never occur in practice; the first ones are split then)
     const int nu = std::min<int>((int)used.size(), 6);
-    const TileFits fits(sizes, f64, e->cus, n);
+    const double gain = n < 16 ? 0.7 : 0.95;
     double best = 1e30;
     unsigned pick = 0;
     std::vector<long> pick_count;
@@ -2535,7 +2566,7 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
         if (groups > 1) main_us *= 0.9;
         main_us += single_us;
         const double us = main_us > 0.0 ? std::max(lds_us, main_us + lds_share) : lds_us;
-        if (us < best * (m ? 0.95 : 1.0)) {
+        if (us < best * (m ? gain : 1.0)) {
             best = us;
             pick = m;
             pick_count = count;
@@ -2543,27 +2574,44 @@ static std::map<std::pair<int, int>, std::pair<int, int>> ens_plan_tiles(xyl_ens
     }
     if (!pick) return out;
     std::vector<TileSize> tiles;
-    fits.best(pick_count, &e->tile_shape, &tiles, &e->tile_lds);
+    fits.best(pick_count, &out.shape, &tiles, &out.lds);
     for (int b = 0; b < nu; ++b)
         if (pick >> b & 1u)
-            for (int r : unit[used[b]]) on_tiles[r] = 1;
+            for (int r : unit[used[b]]) out.tiled[r] = 1;
     for (const TileSize& z : tiles)
-        if (z.ntx) out[{z.Lx, z.Ly}] = {z.ntx, z.nty};
+        if (z.ntx) out.boxes[{z.Lx, z.Ly}] = {z.ntx, z.nty};
     return out;
 }
 
-// Tables for the steps of `active` replicas (LDS replicas among them), planned
-// for chunks of about n steps.
+// What the ensemble's stream and the LDS path's each hold so far is done before
+// either goes on: a replica may change between them.
+static void ens_join_streams(xyl_ensemble* e) {
+    if (!e->side) return;
+    check_hip(hipEventRecord(e->ev_main, e->stream), "hipEventRecord");
+    check_hip(hipEventRecord(e->ev_side, e->side), "hipEventRecord");
+    check_hip(hipStreamWaitEvent(e->side, e->ev_main, 0), "hipStreamWaitEvent");
+    check_hip(hipStreamWaitEvent(e->stream, e->ev_side, 0), "hipStreamWaitEvent");
+}
+
+// Makes e->tab the tables for a chunk of n steps of the `active` replicas (LDS
+// replicas among them).  What the tables hold of the replicas that step on
+// strips and tiles stays while those and their plan do: an LDS replica that
+// ends changes nothing, and an ensemble that only the LDS path steps uploads
+// nothing.
 template <typename R>
 static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<int>& active, uint64_t n) {
-    // a replica may change between the streams
-    if (e->side) check_hip(hipStreamSynchronize(e->side), "hipStreamSynchronize");
-    std::vector<Lat<R>> tab(e->n);
-    for (int r = 0; r < e->n; ++r) tab[r] = e->view<R>(r, jbase);
-    e->reps.reserve(sizeof(Lat<R>) * e->n);
-    check_hip(hipMemcpyAsync(e->reps.p, tab.data(), sizeof(Lat<R>) * e->n, hipMemcpyHostToDevice, e->stream), "H2D");
-    auto box = ens_plan_tiles(e, active, n, e->tiled);
-    if (!box.empty()) {
+    if (e->tables_fusion != e->fusion) e->drop_tables();
+    e->tables_fusion = e->fusion;
+    const int cls = xyl_ensemble::length_class(n);
+    xyl_ensemble::Tables* before = e->tab;
+    xyl_ensemble::Tables& t = e->tables[cls];
+    e->tab = &t;
+    if (t.built && t.planned_for == active) {
+        if (before != &t) ens_join_streams(e);
+        return;
+    }
+    EnsTilePlan plan = ens_plan_tiles(e, t, active, xyl_ensemble::plan_length(cls));
+    if (plan.shape.T) {
         // where the second velocity buffer does not fit, the other paths do
         // (the classes, which need it too, report that)
         try {
@@ -2572,8 +2620,42 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
             if (err.code != XYL_ENOMEM) throw;
             (void)hipGetLastError();
             e->tiles_ok = false;
-            box = ens_plan_tiles(e, active, n, e->tiled);
+            e->drop_tables();
+            plan = ens_plan_tiles(e, t, active, xyl_ensemble::plan_length(cls));
         }
+    }
+    std::vector<int> strips, meas;
+    for (int r : active) {
+        if (!e->lds[r]) meas.push_back(r);
+        if (!e->lds[r] || plan.tiled[r]) strips.push_back(r);
+    }
+    const bool same = t.built && t.strips == strips && t.tiled == plan.tiled && t.boxes == plan.boxes &&
+                      t.tile_shape.T == plan.shape.T && t.tile_shape.S == plan.shape.S &&
+                      t.tile_shape.threads == plan.shape.threads;
+    t.planned_for = active;
+    if (!same || before != &t) ens_join_streams(e);
+    if (same) return;
+    t.built = false;
+    t.strips = strips;
+    t.meas = meas;
+    t.tiled = plan.tiled;
+    t.boxes = plan.boxes;
+    t.tile_shape = plan.shape;
+    t.tile_lds = plan.lds;
+    t.ntasks = t.ntasks_flat = t.ntasks_meas = t.ntiles = t.ntasks_rest = 0;
+    t.s2cls.clear();
+    e->graph_version += 1;
+    if (strips.empty()) {
+        t.built = true;
+        return;
+    }
+    std::vector<Lat<R>> views;
+    if (!e->reps_ok) {
+        views.resize(e->n);
+        for (int r = 0; r < e->n; ++r) views[r] = e->view<R>(r, jbase);
+        e->reps.reserve(sizeof(Lat<R>) * e->n);
+        check_hip(hipMemcpyAsync(e->reps.p, views.data(), sizeof(Lat<R>) * e->n, hipMemcpyHostToDevice, e->stream),
+                  "H2D");
     }
     std::vector<TileTask> tt;
     std::vector<Task> tk;
@@ -2583,43 +2665,38 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
         for (int s = 0; s < nstrips; ++s)
             for (int x = 0; x < nxw; ++x) tk.push_back(Task{r, x, s, 0});
     };
-    e->task_meas.clear();
     for (int r : active)
-        if (!e->lds[r]) {
-            e->task_meas.push_back(r);
-            if (!e->tiled[r]) tile_rows(r);
-        }
-    e->ntasks_flat = (int)tk.size();
+        if (!e->lds[r] && !t.tiled[r]) tile_rows(r);
+    t.ntasks_flat = (int)tk.size();
     for (int r : active)
-        if (!e->lds[r] && e->tiled[r]) tile_rows(r);
-    e->ntasks_meas = (int)tk.size();
+        if (!e->lds[r] && t.tiled[r]) tile_rows(r);
+    t.ntasks_meas = (int)tk.size();
     for (int r : active)
-        if (e->lds[r] && e->tiled[r]) tile_rows(r);
+        if (e->lds[r] && t.tiled[r]) tile_rows(r);
     for (int r : active)
-        if (e->tiled[r]) {
-            const auto& b = box.at({e->desc[r].Lx, e->desc[r].Ly});
+        if (t.tiled[r]) {
+            const auto& b = t.boxes.at({e->desc[r].Lx, e->desc[r].Ly});
             tile_tasks(r, e->desc[r].Lx, e->desc[r].Ly, b.first, b.second, &tt);
         }
-    e->ntiles = (int)tt.size();
-    e->tiles.reserve(std::max<size_t>(tt.size(), 1));
+    t.ntiles = (int)tt.size();
+    t.tiles.reserve(std::max<size_t>(tt.size(), 1));
     if (!tt.empty())
-        check_hip(hipMemcpyAsync(e->tiles.p, tt.data(), sizeof(TileTask) * tt.size(), hipMemcpyHostToDevice, e->stream),
+        check_hip(hipMemcpyAsync(t.tiles.p, tt.data(), sizeof(TileTask) * tt.size(), hipMemcpyHostToDevice, e->stream),
                   "H2D");
-    e->ntasks = (int)tk.size();
-    e->tasks.reserve(std::max<size_t>(tk.size(), 1));
+    t.ntasks = (int)tk.size();
+    t.tasks.reserve(std::max<size_t>(tk.size(), 1));
     if (!tk.empty())
-        check_hip(hipMemcpyAsync(e->tasks.p, tk.data(), sizeof(Task) * tk.size(), hipMemcpyHostToDevice, e->stream),
+        check_hip(hipMemcpyAsync(t.tasks.p, tk.data(), sizeof(Task) * tk.size(), hipMemcpyHostToDevice, e->stream),
                   "H2D");
-    // two-step classes (FP32): replicas whose width the two-step pass takes,
-    // grouped by waves per row; the rest of the tile-path replicas
+    // two-step classes (FP32, chunks of four steps and more): replicas whose
+    // width the two-step pass takes, grouped by waves per row; the rest of the
+    // tile-path replicas
     std::vector<std::vector<Task2>> t2(17);
     std::vector<Task> rest;
-    e->s2cls.clear();
-    e->ntasks_rest = 0;
-    if (e->dtype == XYL_F32 && e->fusion == 2) {
+    if (e->dtype == XYL_F32 && e->fusion == 2 && cls > 0) {
         std::vector<std::vector<int>> byw(17);
         for (int r : active) {
-            if (e->lds[r] || e->tiled[r]) continue;
+            if (e->lds[r] || t.tiled[r]) continue;
             const xyl_replica_desc& d = e->desc[r];
             if (step2_shape(d.Lx, d.Ly) && replica_factored(d))
                 byw[(d.Lx + kWaveSites - 1) / kWaveSites].push_back(r);
@@ -2645,26 +2722,25 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
             check_hip(hipMemcpyAsync(cl.tasks.p, t2[w].data(), sizeof(Task2) * t2[w].size(), hipMemcpyHostToDevice,
                                      e->stream),
                       "H2D");
-            e->s2cls.push_back(std::move(cl));
+            t.s2cls.push_back(std::move(cl));
         }
-        e->ntasks_rest = (int)rest.size();
-        e->tasks_rest.reserve(std::max<size_t>(rest.size(), 1));
+        t.ntasks_rest = (int)rest.size();
+        t.tasks_rest.reserve(std::max<size_t>(rest.size(), 1));
         if (!rest.empty())
-            check_hip(hipMemcpyAsync(e->tasks_rest.p, rest.data(), sizeof(Task) * rest.size(), hipMemcpyHostToDevice,
+            check_hip(hipMemcpyAsync(t.tasks_rest.p, rest.data(), sizeof(Task) * rest.size(), hipMemcpyHostToDevice,
                                      e->stream),
                       "H2D");
     }
     // the second velocity buffer and the group streams now, not in the first
     // chunk that steps through the groups
-    if (e->groups()) {
+    if (t.groups()) {
         e->u2.reserve(sizeof(R) * e->total);
-        e->class_streams(e->groups());
+        e->class_streams(t.groups());
     }
     // the host vectors must outlive the copies
     check_hip(hipStreamSynchronize(e->stream), "hipStreamSynchronize");
-    e->task_active = active;
-    e->tables_fusion = e->fusion;
-    e->graph_version += 1;
+    e->reps_ok = true;
+    t.built = true;
 }
 
 // Sample bookkeeping of one xyl_ensemble_step call: observables gathered in
@@ -2817,14 +2893,14 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
             chunk = any_active ? std::min(chunk, c) : c;
             any_active = true;
         }
-        if (!active.empty() && (active != e->task_active || e->tables_fusion != e->fusion))
-            ens_upload_table<R>(e, e->j, active, chunk);
+        if (!active.empty()) ens_upload_table<R>(e, e->j, active, chunk);
+        xyl_ensemble::Tables& t = *e->tab;
         bool step_g = false;   // replicas that step on the ensemble's stream and its class streams
-        for (int r : active) step_g = step_g || !e->lds[r] || e->tiled[r];
+        for (int r : active) step_g = step_g || !e->lds[r] || t.tiled[r];
         for (int r = 0; r < e->n; ++r) {
             if (!e->lds[r]) {
                 if (meas[r]) (act[r] ? meas_g : only_meas_g).push_back(r);
-            } else if (meas[r] || (act[r] && !e->tiled[r])) {
+            } else if (meas[r] || (act[r] && !t.tiled[r])) {
                 lds_set.push_back(r);
             }
         }
@@ -2836,7 +2912,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
         // over it waits for the sample
         hipEvent_t lds_sample = nullptr;
         bool lds_from_tiles = false;
-        for (int r : lds_set) lds_from_tiles = lds_from_tiles || (meas[r] && !e->tiled.empty() && e->tiled[r]);
+        for (int r : lds_set) lds_from_tiles = lds_from_tiles || (meas[r] && !t.tiled.empty() && t.tiled[r]);
         if (lds_from_tiles) {
             check_hip(hipEventRecord(e->ev_main, e->stream), "hipEventRecord");
             check_hip(hipStreamWaitEvent(e->side, e->ev_main, 0), "hipStreamWaitEvent");
@@ -2858,7 +2934,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                     const bool f = kick_factored(Params{d.Jx, d.Jy, d.h, d.gamma, d.dt, d.model, d.p});
                     if (f != (pass == 0)) continue;
                     nfact += f ? 1 : 0;
-                    jh.push_back(LdsJobHost{r, meas[r] ? 1 : 0, act[r] && !e->tiled[r] ? (int32_t)chunk : 0, 0,
+                    jh.push_back(LdsJobHost{r, meas[r] ? 1 : 0, act[r] && !t.tiled[r] ? (int32_t)chunk : 0, 0,
                                             meas[r] ? smp.take(r) : nullptr});
                 }
             // (pinned table b's last copy went with that launch, so it is free)
@@ -2888,7 +2964,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
         // the replicas on the ensemble's stream
         if (step_g) {
             const Lat<R>* reps = reinterpret_cast<const Lat<R>*>(e->reps.p);
-            const size_t ncls = e->s2cls.size(), groups = e->groups();
+            const size_t ncls = t.s2cls.size(), groups = t.groups();
             const R* ub = static_cast<const R*>(e->u);
             R* u2b = reinterpret_cast<R*>(e->u2.p);
             // group g (a class, or the tiles last) runs on the ensemble's
@@ -2898,7 +2974,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
             auto tile_launch = [&](uint64_t i, uint64_t nl, uint64_t n, const uint64_t* kdev, uint64_t jb,
                                    hipStream_t st) {
                 const uint64_t q = n / nl, m = n % nl, off = i * q + std::min(i, m);
-                launch_ensemble_tile<R>(reps, e->tiles.p, e->ntiles, e->tile_shape, e->tile_lds, e->model(),
+                launch_ensemble_tile<R>(reps, t.tiles.p, t.ntiles, t.tile_shape, t.tile_lds, e->model(),
                                         (int)(q + (i < m ? 1 : 0)), (int)(i & 1), off, ub, u2b, kdev, jb + off, st);
             };
             // With groups the sample is a measurement without a step, and the
@@ -2920,18 +2996,18 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                         check_hip(hipStreamWaitEvent(st, e->cls_events[0], 0), "hipStreamWaitEvent");
                         if (g < ncls) {
                             if constexpr (std::is_same<R, float>::value) {
-                                const auto& cl = e->s2cls[g];
+                                const auto& cl = t.s2cls[g];
                                 launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial, cl.max_lx,
                                                       e->model(), 0, ub, u2b, nullptr, e->j, st);
                             }
                         } else {
                             const uint64_t n2 = chunk / 2 * 2;
-                            tile_launch(0, tile_launches(n2, e->tile_shape.T), n2, nullptr, e->j, st);
+                            tile_launch(0, tile_launches(n2, t.tile_shape.T), n2, nullptr, e->j, st);
                         }
                     }
                     preforked = true;
                 }
-                launch_ensemble_step<R>(reps, e->tasks.p, e->ntasks_meas, passes ? kMeasure : (kStore | kMeasure),
+                launch_ensemble_step<R>(reps, t.tasks.p, t.ntasks_meas, passes ? kMeasure : (kStore | kMeasure),
                                         e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
                 if (preforked) check_hip(hipEventRecord(e->cls_events[groups], e->stream), "hipEventRecord");
                 for (int r : meas_g)
@@ -2944,8 +3020,8 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                 lds_sample = nullptr;
                 // (the tiles' replicas measured in LDS take that step here)
                 if (!meas_g.empty()) {
-                    if (e->ntasks > e->ntasks_meas)
-                        launch_ensemble_step<R>(reps, e->tasks.p + e->ntasks_meas, e->ntasks - e->ntasks_meas, kStore,
+                    if (t.ntasks > t.ntasks_meas)
+                        launch_ensemble_step<R>(reps, t.tasks.p + t.ntasks_meas, t.ntasks - t.ntasks_meas, kStore,
                                                 e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
                     c = 1;
                 }
@@ -2956,7 +3032,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                 // classes: 4m steps; tiles: an even number; the rest of the
                 // chunk in single tile-table steps
                 const uint64_t n4 = passes && ncls ? n / 4 * 4 : 0;
-                const uint64_t n2 = passes && e->ntiles ? n / 2 * 2 : 0;
+                const uint64_t n2 = passes && t.ntiles ? n / 2 * 2 : 0;
                 if (n4 || n2) {
                     // with `preforked` (a direct chunk of several groups, from
                     // its start), the later groups are forked and their first
@@ -2972,7 +3048,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                     // launch of the groups before it to be issued (in a
                     // replayed graph, dispatched), and the groups would hardly
                     // overlap
-                    const uint64_t np = n4 / 2, nl = n2 ? tile_launches(n2, e->tile_shape.T) : 0;
+                    const uint64_t np = n4 / 2, nl = n2 ? tile_launches(n2, t.tile_shape.T) : 0;
                     const uint64_t rounds = std::max(np, nl);
                     uint64_t p = 0, l = 0;
                     for (uint64_t r = 0; r < rounds; ++r) {
@@ -2984,7 +3060,7 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                                     check_hip(hipStreamWaitEvent(st, e->cls_events[groups], 0), "hipStreamWaitEvent");
                                 }
                                 if constexpr (std::is_same<R, float>::value) {
-                                    const auto& cl = e->s2cls[g];
+                                    const auto& cl = t.s2cls[g];
                                     launch_ensemble_step2(reps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial,
                                                           cl.max_lx, e->model(), (int)(p & 1), ub, u2b, kdev,
                                                           jb + c0 + 2 * p, st);
@@ -3005,26 +3081,26 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                         check_hip(hipEventRecord(e->cls_events[g], e->cls_streams[g - 1]), "hipEventRecord");
                         check_hip(hipStreamWaitEvent(main, e->cls_events[g], 0), "hipStreamWaitEvent");
                     }
-                    if (n4 && e->ntasks_rest)
+                    if (n4 && t.ntasks_rest)
                         for (uint64_t i = 0; i < n4; ++i)
-                            launch_ensemble_step<R>(reps, e->tasks_rest.p, e->ntasks_rest, kStore, e->model(),
+                            launch_ensemble_step<R>(reps, t.tasks_rest.p, t.ntasks_rest, kStore, e->model(),
                                                     e->launch.rows, e->launch.wpb, kdev, jb + c0 + i, main);
                 }
                 // single steps: tasks [a, b), both sets where both have them left
                 for (uint64_t i = std::min(n4, n2); i < n; ++i) {
-                    const int a = i >= n4 ? 0 : e->ntasks_flat, b = i >= n2 ? e->ntasks : e->ntasks_flat;
+                    const int a = i >= n4 ? 0 : t.ntasks_flat, b = i >= n2 ? t.ntasks : t.ntasks_flat;
                     if (b > a)
-                        launch_ensemble_step<R>(reps, e->tasks.p + a, b - a, kStore, e->model(), e->launch.rows,
+                        launch_ensemble_step<R>(reps, t.tasks.p + a, b - a, kStore, e->model(), e->launch.rows,
                                                 e->launch.wpb, kdev, jb + c0 + i, main);
                 }
             };
             const uint64_t n = chunk - c;
             // launches the chunk's stepping takes
             uint64_t nl = n;
-            if (passes && ncls) nl = n / 4 * 2 * ncls + n % 4 + (e->ntasks_rest ? n / 4 * 4 : 0);
+            if (passes && ncls) nl = n / 4 * 2 * ncls + n % 4 + (t.ntasks_rest ? n / 4 * 4 : 0);
             xyl_ensemble::ChunkGraph* cg = nullptr;
             // (tile launches are few and long enough to be issued directly)
-            const bool graphs = e->use_graphs == 2 || (e->use_graphs == 1 && groups <= 1 && e->ntiles == 0);
+            const bool graphs = e->use_graphs == 2 || (e->use_graphs == 1 && groups <= 1 && t.ntiles == 0);
             if (graphs && nl >= 8) {
                 if (e->graphs_built_for != e->graph_version) {
                     e->drop_graphs();
@@ -3077,9 +3153,9 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
         // one batched measurement over the task table when they are the
         // replicas it was built for (the same strips and sums as one launch
         // per replica, which took about 1 ms for the 288-replica ensemble)
-        const bool batched_only = !only_meas_g.empty() && only_meas_g == e->task_meas && e->ntasks_meas > 0;
+        const bool batched_only = !only_meas_g.empty() && only_meas_g == t.meas && t.ntasks_meas > 0;
         if (batched_only)
-            launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(e->reps.p), e->tasks.p, e->ntasks_meas, kMeasure,
+            launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(e->reps.p), t.tasks.p, t.ntasks_meas, kMeasure,
                                     e->model(), e->launch.rows, e->launch.wpb, nullptr, e->j, e->stream);
         for (int r : only_meas_g) {
             if (!batched_only) {
@@ -3199,7 +3275,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
         e->fusion = 2;
         const int steps4 = (steps + 3) / 4 * 4;
         if (!active.empty()) ens_upload_table<R>(e, e->j, active, (uint64_t)steps4);
-        if (!active.empty() && e->groups()) {
+        if (!active.empty() && e->tab->groups()) {
             const Lat<float>* dreps = reinterpret_cast<const Lat<float>*>(dtab.p);
             const float* ub = reinterpret_cast<const float*>(tmp.p + 2 * bytes);
             float* u2b = reinterpret_cast<float*>(tmp.p + 3 * bytes);
@@ -3230,7 +3306,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
             // streams, pass by pass across the classes, where a chunk with
             // several classes runs direct; one after the other in a graph
             // otherwise
-            const size_t ncls = e->s2cls.size();
+            const size_t ncls = e->tab->s2cls.size();
             auto classes = [&](hipStream_t main, bool fork) {
                 if (fork) {
                     e->class_streams(ncls);
@@ -3242,7 +3318,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
                 for (int i = 0; i < steps4; i += 4)
                     for (int ph = 0; ph < 2; ++ph)
                         for (size_t c2 = 0; c2 < ncls; ++c2) {
-                            const auto& cl = e->s2cls[c2];
+                            const auto& cl = e->tab->s2cls[c2];
                             launch_ensemble_step2(dreps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial, cl.max_lx,
                                                   e->model(), ph, ub, u2b, kc.p, (uint64_t)(i + 2 * ph),
                                                   fork && c2 > 0 ? e->cls_streams[c2 - 1] : main);
@@ -3252,18 +3328,18 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
                         check_hip(hipEventRecord(e->cls_events[c2], e->cls_streams[c2 - 1]), "hipEventRecord");
                         check_hip(hipStreamWaitEvent(main, e->cls_events[c2], 0), "hipStreamWaitEvent");
                     }
-                if (e->ntiles) {
-                    const uint64_t nl = tile_launches((uint64_t)steps4, e->tile_shape.T);
+                if (e->tab->ntiles) {
+                    const uint64_t nl = tile_launches((uint64_t)steps4, e->tab->tile_shape.T);
                     const uint64_t q = (uint64_t)steps4 / nl, m = (uint64_t)steps4 % nl;
                     for (uint64_t i = 0, off = 0; i < nl; ++i) {
                         const uint64_t t = q + (i < m ? 1 : 0);
-                        launch_ensemble_tile<R>(dreps, e->tiles.p, e->ntiles, e->tile_shape, e->tile_lds, e->model(),
+                        launch_ensemble_tile<R>(dreps, e->tab->tiles.p, e->tab->ntiles, e->tab->tile_shape, e->tab->tile_lds, e->model(),
                                                 (int)t, (int)(i & 1), off, ub, u2b, kc.p, off, main);
                         off += t;
                     }
                 }
-                const Task* single = ncls ? e->tasks_rest.p : e->tasks.p;
-                const int nsingle = ncls ? e->ntasks_rest : e->ntasks_flat;
+                const Task* single = ncls ? e->tab->tasks_rest.p : e->tab->tasks.p;
+                const int nsingle = ncls ? e->tab->ntasks_rest : e->tab->ntasks_flat;
                 if (nsingle)
                     for (int i = 0; i < steps4; ++i)
                         launch_ensemble_step<R>(dreps, single, nsingle, kStore, e->model(), best.rows, best.wpb, kc.p,
@@ -3288,7 +3364,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
             const float t1 = time_graph(
                 [&] {
                     for (int i = 0; i < steps4; ++i)
-                        launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(dtab.p), e->tasks.p, e->ntasks,
+                        launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(dtab.p), e->tab->tasks.p, e->tab->ntasks,
                                                 kStore, e->model(), best.rows, best.wpb, kc.p, (uint64_t)i, cap);
                 },
                 steps4);
@@ -3368,7 +3444,7 @@ int xyl_ensemble_create(xyl_ensemble** out, const xyl_replica_desc* desc, int32_
             check_hip(hipStreamSynchronize(nullptr), "hipStreamSynchronize");
         }
         e->lds.assign(n, 0);
-        e->tiled.assign(n, 0);
+        for (auto& t : e->tables) t.tiled.assign(n, 0);
         for (int r = 0; r < n; ++r) {
             const int N = desc[r].Lx * desc[r].Ly;
             if (dtype == XYL_F32 && N <= kLdsMaxSites) {
@@ -3570,6 +3646,18 @@ int xyl_ensemble_structure_factor(xyl_ensemble* e, int32_t r, int32_t axis, int3
         else
             structure_factor_into<float>(e->cur_theta(r), d.Lx, d.Ly, sx, sy, d.model, axis, kmax, e->spectrum,
                                          e->stream, S);
+    });
+}
+
+int xyl_ensemble_paths(xyl_ensemble* e, int32_t* path) {
+    return guarded([&] {
+        require(e != nullptr && path != nullptr, XYL_EINVAL, "NULL argument");
+        const xyl_ensemble::Tables& t = *e->tab;
+        for (int r = 0; r < e->n; ++r) {
+            const xyl_replica_desc& d = e->desc[r];
+            const bool two = !t.s2cls.empty() && step2_shape(d.Lx, d.Ly) && replica_factored(d);
+            path[r] = t.tiled[r] ? XYL_PATH_TILES : e->lds[r] ? XYL_PATH_LDS : two ? XYL_PATH_TWO_STEP : XYL_PATH_SINGLE;
+        }
     });
 }
 

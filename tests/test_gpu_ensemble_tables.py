@@ -1,6 +1,7 @@
 """What an ensemble keeps between calls follows its state: samples taken without
 a step after a replica's state was set, or after the launch shape was tuned, are
-those of an ensemble that never had another state or shape."""
+those of an ensemble that never had another state or shape; and the plan follows each
+chunk's length, whichever length came first."""
 import sys
 
 import numpy as np
@@ -64,3 +65,64 @@ def test_samples_after_the_launch_shape_was_tuned(xyl, dtype):
         for a, b in zip(want, got):
             np.testing.assert_array_equal(a, b)
         ens.close()
+
+
+def mixed(xyl, dtype, model, budgets=(1 << 40,)):
+    sizes = [(64, 64), (96, 96), (128, 128), (144, 144), (320, 40), (192, 192)] if dtype == "f32" else \
+        [(64, 64), (128, 60), (20, 200)]
+    specs = []
+    for i, (Lx, Ly) in enumerate(sizes):
+        for j in range(8):
+            s = workloads.si_lattice(Lx, Ly, T=1.8 + 0.02 * j, seed=j, replica=10 * i + j) if model == "si" else \
+                workloads.LatticeSpec(Lx, Ly, schedule=((0, 0.4 + 0.1 * j), (40, 0.3)), seed=j, replica=10 * i + j)
+            s.nsteps = budgets[(i + j) % len(budgets)]
+            specs.append(s)
+    return xyl.Ensemble(specs, dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_the_first_chunk_decides_nothing_for_later_ones(xyl, dtype):
+    want = {}
+    for first in (0, 1, 2, 5, 200):
+        ens = mixed(xyl, dtype, "si")
+        if first:
+            ens.step(first)
+            ens.step(3)
+            assert "tiles" not in ens.paths() and "two_step" not in ens.paths()
+        for n in (200, 12, 5):
+            ens.step(n)
+            got = ens.paths()
+            assert want.setdefault(n, got) == got, (first, n)
+        assert "tiles" in want[200]
+        ens.close()
+    say("ensemble paths", dtype, want[200])
+
+
+@pytest.mark.parametrize("graphs", [0, 1, 2])
+@pytest.mark.parametrize("dtype,model", [("f32", "xy"), ("f32", "si"), ("f64", "xy")])
+def test_chunks_of_every_length_equal_single_steps(xyl, dtype, model, graphs):
+    """Chunks of one to two hundred steps in turn, with and without samples, and
+    replicas that end in between: the samples and states of single steps, bit
+    for bit."""
+    say("chunk lengths", dtype, model, graphs)
+    res = []
+    for fusion in (1, 2):
+        ens = mixed(xyl, dtype, model, budgets=(1 << 40, 97, 1 << 40, 240))
+        ens.set_fusion(fusion)
+        ens.set_graphs(graphs)
+        out = []
+        for n, every in ((2, 0), (60, 20), (3, 1), (5, 5), (30, 6), (1, 0), (12, 0), (24, 12), (40, 2), (8, 0), (90, 30),
+                         (7, 0), (60, 20), (60, 20)):
+            got = ens.step(n, every=every)
+            if every:
+                out.append(got)
+        out.append(ens.step(0, every=1))
+        res.append((out, [ens.get_state(r) for r in range(ens.n)]))
+        ens.close()
+    for a, b in zip(res[0][0], res[1][0]):
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
+    for (ta, wa, ka), (tb, wb, kb) in zip(res[0][1], res[1][1]):
+        assert ka == kb
+        np.testing.assert_array_equal(ta, tb)
+        np.testing.assert_array_equal(wa, wb)
