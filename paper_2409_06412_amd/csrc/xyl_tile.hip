@@ -235,11 +235,11 @@ static const TileCost kCost64[] = {{2, 3.0, 0.5, 1.20, 0.90, 16}, {1, 3.0, 0.3, 
 // the fraction `alive` of the steps.
 static double tile_cost(const TileCost& c, uint64_t n, uint64_t nl, int waves, size_t lds, int wgs, double alive) {
     const int fit = std::max(1, std::min((int)(160 * 1024 / lds), c.max_waves / waves));
-    double step = 0.0;
-    for (int left = wgs; left > 0; left -= fit) {
-        const double x = 0.25 * waves * std::min(left, fit) * alive;
-        step += std::sqrt(c.lat * c.lat + c.issue * c.issue * x * x);
-    }
+    auto round = [&](int held) {
+        const double x = 0.25 * waves * held * alive;
+        return std::sqrt(c.lat * c.lat + c.issue * c.issue * x * x);
+    };
+    const double step = (wgs / fit) * round(fit) + (wgs % fit ? round(wgs % fit) : 0.0);
     return ((double)nl * (c.fixed + c.prologue * 0.25 * waves * wgs) + (double)n * step) / (double)n;
 }
 static double tile_alive(int H, int Ly, int t) {
