@@ -317,6 +317,9 @@ int xyl_set_step2_shape(xyl_lattice* h, int32_t rows, int32_t tile_waves);
 int xyl_get_step2_shape(const xyl_lattice* h, int32_t* rows, int32_t* tile_waves, int32_t* tiles);
 
 /* -------------------------------------------------------------- test hooks */
+/* Goes on as if xyl_autotune had found the path (XYL_PATH_SINGLE to
+ * XYL_PATH_TILES) the fastest; runs that it cannot take go as they would then. */
+int xyl_choose_path(xyl_lattice* h, int32_t path);
 /* Goes on as if the lattice's second velocity buffer did not fit: single steps
  * from now on. */
 int xyl_deny_second_buffer(xyl_lattice* h);

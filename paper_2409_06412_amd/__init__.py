@@ -82,6 +82,7 @@ _SIGS = {
     "xyl_set_fusion": (_i32, [_vp, _i32]),
     "xyl_get_fusion": (_i32, [_vp, P(_i32), P(_i32)]),
     "xyl_deny_second_buffer": (_i32, [_vp]),
+    "xyl_choose_path": (_i32, [_vp, _i32]),
     "xyl_stepping_path": (_i32, [_vp, _u64, P(_i32), P(_i32)]),
     "xyl_set_step2_shape": (_i32, [_vp, _i32, _i32]),
     "xyl_get_step2_shape": (_i32, [_vp, P(_i32), P(_i32), P(_i32)]),

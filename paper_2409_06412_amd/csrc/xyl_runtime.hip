@@ -2140,6 +2140,20 @@ int xyl_set_graph_steps(xyl_lattice* h, int32_t steps) {
     });
 }
 
+int xyl_choose_path(xyl_lattice* h, int32_t path) {
+    return guarded([&] {
+        require(h != nullptr, XYL_EINVAL, "NULL handle");
+        require(path >= XYL_PATH_SINGLE && path <= XYL_PATH_TILES, XYL_EINVAL, "not a path of a lattice");
+        h->fusion = path == XYL_PATH_SINGLE ? 1 : 2;
+        h->march = path == XYL_PATH_MARCH ? kChosen : kSlower;
+        h->tiles = path == XYL_PATH_TILES ? kChosen : kSlower;
+        h->shaped = false;
+        h->own_path = true;
+        h->tile_plans.clear();
+        h->touch();
+    });
+}
+
 int xyl_deny_second_buffer(xyl_lattice* h) {
     return guarded([&] {
         require(h != nullptr, XYL_EINVAL, "NULL handle");
