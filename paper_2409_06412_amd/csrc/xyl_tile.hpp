@@ -28,9 +28,6 @@ inline int tile_max_w(int Lx, int ntx) { return (Lx / kLaneSites + ntx - 1) / nt
 inline int tile_max_h(int Ly, int nty) { return (Ly + nty - 1) / nty; }
 inline int tile_region_w(int Lx, int w, int T) { return w == Lx ? w : w + 2 * ((T + 3) / 4 * 4); }
 inline int tile_region_h(int Ly, int h, int T) { return h == Ly ? h : h + 2 * T; }
-// LDS bytes: two tables of (sin, cos) per site of the region.
-template <typename R>
-inline size_t tile_lds(int W, int H) { return sizeof(R) * 4 * (size_t)W * (size_t)H; }
 
 // The cheapest way (by the measured cost model in xyl_tile.hip) to take n
 // steps, n even, in an even number of launches on `cus` CUs; false if no tile
