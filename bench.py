@@ -341,6 +341,22 @@ def bench_si_4096(torch, xyl, workloads, nlaunch=500, launch=None):
     return {"L": 4096, "model": "si", "p": spec.p, "T": spec.schedule[0][1], **out}
 
 
+def bench_tiles(torch, xyl, workloads, nsteps=640):
+    """Stepping of lattices that take several steps per launch on tiles: 512^2
+    (XY) and 1024^2 (Si) in FP32, 64^2 in FP64."""
+    out = {}
+    for name, dtype, L, model in (("xy_512_f32", "f32", 512, "xy"), ("si_1024_f32", "f32", 1024, "si"),
+                                  ("xy_64_f64", "f64", 64, "xy")):
+        spec = workloads.si_lattice(L, L) if model == "si" else workloads.LatticeSpec(L, L, schedule=((0, 0.6),))
+        lat = xyl.Lattice(L, L, dtype=dtype, schedule=spec.schedule, seed=1,
+                          stream=torch.cuda.current_stream().cuda_stream, **spec.params())
+        lat.init_random()
+        path, steps = lat.stepping_path(nsteps)
+        out[name] = {"path": path, "steps_per_launch": steps, "us_per_step": 1e3 * time_steps(torch, lat, nsteps)}
+        lat.close()
+    return out
+
+
 def bench_c1_temperatures(torch, xyl, workloads, nsteps=20000, every=500):
     """The single-lattice configuration at all eight of its temperatures
     (T = 0.3 .. 1.2), batched: eight 4096^2 FP32 replicas advanced together,
@@ -697,7 +713,7 @@ def main():
                     help="steps over which each stepping kernel is timed alone")
     ap.add_argument("--only", type=str, default="",
                     help="comma list of extras to run alone (copy, ensemble, quench, adjoint, domains, control, "
-                         "si, si_fss, structure); "
+                         "si, si_fss, structure, tiles); "
                          "prints their JSON and skips the headline measurement")
     ap.add_argument("--no-autotune", action="store_true",
                     help="keep the built-in launch rules instead of autotuning (for profiler runs, whose "
@@ -709,7 +725,7 @@ def main():
     ap.add_argument("--summarize-traffic", nargs=6,
                     metavar=("FETCH_DIR", "WRITE_DIR", "OUT_JSON", "OUT_MD", "FETCH_CMD", "WRITE_CMD"))
     ap.add_argument("--summarize-valu", nargs=4, metavar=("DIR", "OUT_JSON", "OUT_MD", "COMMAND"))
-    ap.add_argument("--steps-per-launch", type=int, default=0,
+    ap.add_argument("--steps-per-launch", type=float, default=0,
                     help="with --summarize-valu of a tile kernel: the steps of its launches")
     ap.add_argument("--kernel", type=str, default=STEP2_KERNEL,
                     help="kernel name the counter summaries select (default: the two-step pass)")
@@ -746,6 +762,7 @@ def main():
                 "si": lambda: bench_si_4096(torch, xyl, workloads, launch=fixed),
                 "structure": lambda: bench_structure_factor(torch, xyl, workloads),
                 "si_fss": lambda: bench_si_fss(torch, xyl, workloads),
+                "tiles": lambda: bench_tiles(torch, xyl, workloads),
                 "fp64": lambda: bench_fp64_4096(torch, xyl, workloads),
                 "c1": lambda: bench_c1_temperatures(torch, xyl, workloads)}
         print(json.dumps({k: runs[k]() for k in args.only.split(",")}), flush=True)
