@@ -74,27 +74,48 @@ static void launch_row_sum(const double* part, int nrows, int rmax, double N, do
     check_hip(hipGetLastError(), "row sum launch");
 }
 
+// Sums carried as an FP64 number and what its roundings left out.
+__device__ __forceinline__ void two_add(double2& a, double b) {
+    const double s = a.x + b, t = s - a.x;
+    a.y += (a.x - (s - t)) + (b - t);
+    a.x = s;
+}
+
 // C(r) from the structure factor of an axis that goes through the transform
 // (App. C: C and S are a Fourier pair along the axis): C(r) = (1/L) sum_{k<L}
 // S(k) cos(2 pi k r / L) with S(L - k) = S(k), i.e. (1/L) [S(0) + (even L)
-// (-1)^r S(L/2) + 2 sum_{0<k<L/2} S(k) cos(2 pi k r / L)].  One workgroup per r sums in a fixed order (strided
-// partial sums, then a fixed tree); cos from the twiddle table tw.
+// (-1)^r S(L/2) + 2 sum_{0<k<L/2} S(k) cos(2 pi k r / L)].  One workgroup per r
+// sums in a fixed order (strided partial sums, then a fixed tree); cos from the
+// twiddle table tw.  Products and sums keep their roundings (the errors of the
+// S(k) average out, those of a plain sum left C(0) an ulp beside 1).
 __global__ __launch_bounds__(256) void k_corr_from_sf(const double* __restrict__ S, const double2* __restrict__ tw,
                                                       int L, double* __restrict__ out) {
-    __shared__ double red[256];
+    __shared__ double2 red[256];
     const int r = blockIdx.x;
     const int h = (L + 1) / 2;
-    double acc = 0.0;
-    for (int k = 1 + (int)threadIdx.x; k < h; k += blockDim.x) acc += S[k] * tw[(unsigned)(k * r) % (unsigned)L].x;
+    double2 acc = make_double2(0.0, 0.0);
+    for (int k = 1 + (int)threadIdx.x; k < h; k += blockDim.x) {
+        const double c = tw[(unsigned)(k * r) % (unsigned)L].x, p = S[k] * c;
+        two_add(acc, p);
+        acc.y += fma(S[k], c, -p);
+    }
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        if ((int)threadIdx.x < w) {
+            double2 a = red[threadIdx.x];
+            const double2 b = red[threadIdx.x + w];
+            two_add(a, b.x);
+            a.y += b.y;
+            red[threadIdx.x] = a;
+        }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const double last = L % 2 == 0 ? ((r & 1) ? -S[h] : S[h]) : 0.0;
-        out[r] = (S[0] + last + 2.0 * red[0]) / (double)L;
+        double2 a = make_double2(2.0 * red[0].x, 2.0 * red[0].y);
+        two_add(a, S[0]);
+        if (L % 2 == 0) two_add(a, (r & 1) ? -S[h] : S[h]);
+        out[r] = (a.x + a.y) / (double)L;
     }
 }
 
