@@ -19,8 +19,7 @@ struct MarchPlan {
 };
 // For widths that are multiples of 4 and at least 3 rows.
 MarchPlan march_plan(int Lx, int Ly, int cus);
-// Loads this file's kernels on the current device (0.5 ms that the first launch
-// would take).
+// Loads this file's kernels on the current device.
 void load_march_kernels();
 // Steps k .. k + 2 of a lattice with the factored kick.
 void launch_march(const Lat<float>& v, const MarchBuffers& b, const MarchPlan& p, uint64_t k, hipStream_t s);

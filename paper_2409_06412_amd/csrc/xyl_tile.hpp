@@ -85,8 +85,7 @@ void launch_ensemble_tile(const Lat<R>* reps, const TileTask* tasks, int ntasks,
                           int model, int T, int flip, uint64_t dk, const R* u_base, R* u2_base, const uint64_t* kdev,
                           uint64_t j, hipStream_t s);
 
-// Loads the kernels of xyl_tile.hip on the current device (2.5 ms that the
-// first launch would take).
+// Loads the kernels of xyl_tile.hip on the current device.
 void load_tile_kernels();
 
 // T steps from step k of the lattice v: angles and velocities read from th_in
