@@ -444,12 +444,13 @@ int xyl_ensemble_set_graphs(xyl_ensemble* e, int32_t enable);
  * choice follows the chunk's length: fewer than 4 steps, fewer than 8, fewer
  * than 16, and longer ones have a plan each. */
 int xyl_ensemble_paths(xyl_ensemble* e, int32_t* path);
-/* Steps per pass for the batched mode (1 or 2; default 2).  With 2 (FP32),
- * runs of 4m steps between samples advance the replicas on the tile path
- * whose width the two-step pass takes (as for xyl_set_fusion) two steps per
- * pass, in one launch
- * per pass for each class of replicas of the same number of waves per row;
- * the other tile-path replicas keep one batched tile launch per step.
+/* Steps per pass for the batched mode (1 or 2; default 2).  With 2, chunks of 4
+ * steps and more advance the replicas by the paths that a plan for the chunk's
+ * length finds fastest: several steps per launch on tiles (either precision,
+ * all such replicas in one launch); in FP32 two steps per pass for widths that
+ * pass takes (as for xyl_set_fusion), in runs of 4m steps, one launch per pass
+ * for each class of replicas of the same number of waves per row; the other
+ * replicas keep one batched launch per step (small FP32 ones go whole in LDS).
  * Results are bitwise identical either way.  The library allocates a second
  * velocity buffer of the ensemble's size on first use. */
 int xyl_ensemble_set_fusion(xyl_ensemble* e, int32_t steps_per_pass);
@@ -501,18 +502,18 @@ int xyl_adjoint_backward(xyl_lattice* h, uint64_t run, double* grad, double* dth
 int xyl_adjoint_backward_device(xyl_lattice* h, uint64_t run, double scale, double* grad, void* dtheta0,
                                 void* domega0, int32_t dtype);
 /* Reverse steps per pass of xyl_adjoint_backward (App. A.1's step, run
- * backwards): 2 (the default) takes several reverse (and recomputed) steps per
- * launch on tiles where those fit and rows was never set, else two reverse
- * steps per pass over the state where a strip of rows fits one workgroup (one site per lane, Lx at most
- * 1024, Ly >= 4, and (32 rows + 80) Lx bytes of FP32 state and draws, twice
- * that in FP64, within a CU's 160 KiB of LDS), and recomputes the checkpointed
- * segments two steps per pass too where the forward's two-step pass takes
- * the lattice; 1 keeps one step per pass for both.  rows: rows per strip of
- * the two-step reverse pass (1, 2 or 4; 0 keeps the current value,
- * initially 2: where that does not fit, single reverse steps unless 1 is
- * set).  dL/dth and dL/dw are bitwise
- * the same either way; the parameter gradients are sums taken in another
- * order.  EINVAL outside the ranges. */
+ * backwards): 2 (the default) takes several reverse, and several recomputed,
+ * steps per launch on tiles where those fit, are the faster by a rule of the
+ * sizes and rows was never set.  Else it takes two reverse steps per pass over
+ * the state where a strip of rows fits one workgroup (one site per lane, Lx at
+ * most 1024, Ly >= 4, and (32 rows + 80) Lx bytes of FP32 state and draws,
+ * twice that in FP64, within a CU's 160 KiB of LDS), and recomputes the
+ * checkpointed segments two steps per pass where the forward's two-step pass
+ * takes the lattice; 1 keeps one step per pass for both.  rows: rows per strip
+ * of the two-step reverse pass (1, 2 or 4; 0 keeps the current value,
+ * initially 2: where that does not fit, single reverse steps unless 1 is set).
+ * dL/dth and dL/dw are bitwise the same either way; the parameter gradients
+ * are sums taken in another order.  EINVAL outside the ranges. */
 int xyl_set_adjoint_fusion(xyl_lattice* h, int32_t steps_per_pass, int32_t rows);
 
 #ifdef __cplusplus

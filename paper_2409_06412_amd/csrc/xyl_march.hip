@@ -16,11 +16,12 @@
 // Two waves per SIMD (200 registers): independent stages keep the VALU busy
 // even with one.  Three waves (168 registers) spill, four stages need 242 and
 // gain nothing (a wave's two ends recompute D - 1 rows each on average).
-// Bound by VALU issue, 0.33 us per quad-row, stage and SIMD, of which the halo
-// takes 10 to 20%.  Measured, us per step, with the paths before (two-step
-// passes, tiles or single steps) and with this one: 4096^2 25.9 -> 22.7, 8192^2
-// 118 -> 89, 3000^2 29.2 -> 14.4, 3584 x 3000 31.1 -> 15.7, 2564 x 2503 15.9 ->
-// 11.4, 2048^2 10.4 -> 8.4, 6144^2 72.8 -> 53.1, 5000 x 2001 20.6 -> 14.8.
+// Bound by VALU issue (83% of the slots at 4096^2), 0.295 us per wave of a
+// SIMD, row and step, two halo rows included; the halo takes 10 to 20%.
+// Measured, us per step, with two steps per pass and with this pass (tiles
+// where those were the next best): 2048^2 9.4 and 8.3, 2564 x 2503 14.3 and
+// 10.8, 3000^2 17.3 and 14.1, 3584 x 3000 17.7 and 15.4, 4096^2 24.6 and 22.5,
+// 5000 x 2001 20.4 and 14.6, 6144^2 70.8 and 52.7, 8192^2 114.9 and 88.6.
 #include "xyl_march.hpp"
 
 #include <algorithm>
@@ -154,10 +155,10 @@ __global__ __launch_bounds__(256, 2) void k_march(Lat<float> v, MarchBuffers B, 
 }
 
 // Two waves per SIMD in one round, or four in two where strips stay taller than
-// 40 rows (8192^2: 93 us per step against 101; 4096^2: 28.5 against 25.1).
-// The time is the fit of the passes measured from 1100^2 (5.5 us per step) over
-// 1604^2 (6.7), 2048^2 (8.4), 3000^2 (14.4) and 4096^2 (22.9) to 8192^2 (90),
-// within 6%.
+// 40 rows (us per step in one round and in two: 16384 x 4096 90.1 and 88.8,
+// 8192^2 89.1 and 88.6; 4096^2, with strips of 18 rows, 22.5 and 23.8).
+// The time is a fit to passes from 1100^2 (5.2 us per step) over 1604^2 (6.6),
+// 2048^2 (8.3), 3000^2 (14.1) and 4096^2 (22.5) to 8192^2 (88.6), within 10%.
 MarchPlan march_plan(int Lx, int Ly, int cus) {
     MarchPlan p;
     const int nq = Lx / kLaneSites, most = kWave - 2;

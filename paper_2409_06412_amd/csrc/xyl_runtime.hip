@@ -745,7 +745,8 @@ static double lattice_single_us(const xyl_lattice* h) {
 }
 static bool march_shape_ok(int dtype, int Ly) { return dtype == XYL_F32 && Ly >= 4; }
 static bool lattice_march_plan(const xyl_lattice* h, MarchPlan* p) {
-    if (h->march == kSlower || step2_shaped(h) || !march_shape_ok(h->dtype, h->Ly) || h->fusion != 2 || !kick_factored(h->p)) return false;
+    if (h->march == kSlower || step2_shaped(h) || h->fusion != 2) return false;
+    if (!march_shape_ok(h->dtype, h->Ly) || !kick_factored(h->p)) return false;
     *p = march_plan(h->Lx, h->Ly, h->cus);
     return h->march == kChosen || p->us < (step2_eligible(h) ? lattice_step2_us(h) : lattice_single_us(h));
 }
@@ -806,7 +807,8 @@ static bool tile_shape_ok(int Lx, int Ly) {
 // Plans are kept per run length (64 steps and more share one) and form of the
 // kick (the three-step pass that tiles are weighed against has one only).
 static const TilePlan* lattice_tile_choice(xyl_lattice* h, uint64_t n) {
-    if (h->tiles == kSlower || step2_shaped(h) || h->fusion != 2 || n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
+    if (h->tiles == kSlower || step2_shaped(h) || h->fusion != 2) return nullptr;
+    if (n < 2 || !tile_shape_ok(h->Lx, h->Ly)) return nullptr;
     n = std::min<uint64_t>(n, 64);
     const auto key = std::make_pair(n, kick_factored(h->p));
     auto it = h->tile_plans.find(key);
@@ -2471,7 +2473,8 @@ struct EnsTilePlan {
     std::map<std::pair<int, int>, std::pair<int, int>> boxes;
     std::vector<char> tiled;
 };
-static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, const std::vector<int>& active, uint64_t n) {
+static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, const std::vector<int>& active,
+                                  uint64_t n) {
     EnsTilePlan out;
     out.tiled.assign(e->n, 0);
     if (e->fusion != 2 || n < 4 || !e->tiles_ok) return out;
@@ -3300,7 +3303,8 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
         e->fusion = 2;
         const int steps4 = (steps + 3) / 4 * 4;
         if (!active.empty()) ens_upload_table<R>(e, e->j, active, (uint64_t)steps4);
-        if (!active.empty() && e->tab->groups()) {
+        const xyl_ensemble::Tables& tab = *e->tab;
+        if (!active.empty() && tab.groups()) {
             const Lat<float>* dreps = reinterpret_cast<const Lat<float>*>(dtab.p);
             const float* ub = reinterpret_cast<const float*>(tmp.p + 2 * bytes);
             float* u2b = reinterpret_cast<float*>(tmp.p + 3 * bytes);
@@ -3331,7 +3335,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
             // streams, pass by pass across the classes, where a chunk with
             // several classes runs direct; one after the other in a graph
             // otherwise
-            const size_t ncls = e->tab->s2cls.size();
+            const size_t ncls = tab.s2cls.size();
             auto classes = [&](hipStream_t main, bool fork) {
                 if (fork) {
                     e->class_streams(ncls);
@@ -3343,7 +3347,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
                 for (int i = 0; i < steps4; i += 4)
                     for (int ph = 0; ph < 2; ++ph)
                         for (size_t c2 = 0; c2 < ncls; ++c2) {
-                            const auto& cl = e->tab->s2cls[c2];
+                            const auto& cl = tab.s2cls[c2];
                             launch_ensemble_step2(dreps, cl.tasks.p, cl.ntasks, cl.waves, cl.partial, cl.max_lx,
                                                   e->model(), ph, ub, u2b, kc.p, (uint64_t)(i + 2 * ph),
                                                   fork && c2 > 0 ? e->cls_streams[c2 - 1] : main);
@@ -3353,18 +3357,18 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
                         check_hip(hipEventRecord(e->cls_events[c2], e->cls_streams[c2 - 1]), "hipEventRecord");
                         check_hip(hipStreamWaitEvent(main, e->cls_events[c2], 0), "hipStreamWaitEvent");
                     }
-                if (e->tab->ntiles) {
-                    const uint64_t nl = tile_launches((uint64_t)steps4, e->tab->tile_shape.T);
+                if (tab.ntiles) {
+                    const uint64_t nl = tile_launches((uint64_t)steps4, tab.tile_shape.T);
                     const uint64_t q = (uint64_t)steps4 / nl, m = (uint64_t)steps4 % nl;
                     for (uint64_t i = 0, off = 0; i < nl; ++i) {
                         const uint64_t t = q + (i < m ? 1 : 0);
-                        launch_ensemble_tile<R>(dreps, e->tab->tiles.p, e->tab->ntiles, e->tab->tile_shape, e->tab->tile_lds, e->model(),
-                                                (int)t, (int)(i & 1), off, ub, u2b, kc.p, off, main);
+                        launch_ensemble_tile<R>(dreps, tab.tiles.p, tab.ntiles, tab.tile_shape, tab.tile_lds,
+                                                e->model(), (int)t, (int)(i & 1), off, ub, u2b, kc.p, off, main);
                         off += t;
                     }
                 }
-                const Task* single = ncls ? e->tab->tasks_rest.p : e->tab->tasks.p;
-                const int nsingle = ncls ? e->tab->ntasks_rest : e->tab->ntasks_flat;
+                const Task* single = ncls ? tab.tasks_rest.p : tab.tasks.p;
+                const int nsingle = ncls ? tab.ntasks_rest : tab.ntasks_flat;
                 if (nsingle)
                     for (int i = 0; i < steps4; ++i)
                         launch_ensemble_step<R>(dreps, single, nsingle, kStore, e->model(), best.rows, best.wpb, kc.p,
@@ -3389,7 +3393,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
             const float t1 = time_graph(
                 [&] {
                     for (int i = 0; i < steps4; ++i)
-                        launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(dtab.p), e->tab->tasks.p, e->tab->ntasks,
+                        launch_ensemble_step<R>(reinterpret_cast<const Lat<R>*>(dtab.p), tab.tasks.p, tab.ntasks,
                                                 kStore, e->model(), best.rows, best.wpb, kc.p, (uint64_t)i, cap);
                 },
                 steps4);

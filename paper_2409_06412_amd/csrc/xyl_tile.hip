@@ -31,7 +31,8 @@
 // 8.1 -> 4.5; 772 x 501 FP32 4.3 -> 1.54; 1024^2 FP32 4.6 -> 2.9; 1448^2 10.8
 // -> 5.4.  With one wave per SIMD a step costs 0.45 to 0.7 us of latency, from
 // about three waves per SIMD on it is bound by VALU issue (0.317 us per wave
-// and SIMD, 190 issue slots), of which the halo takes 20 to 45%; a launch's
+// and SIMD, 190 issue slots), of which the halo takes about half (512^2: 95
+// lane-instructions per site-update, 41 where whole rows step); a launch's
 // dispatch, first loads and stores take another 2.75 us.
 #include <cmath>
 #include <mutex>
