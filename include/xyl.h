@@ -441,8 +441,10 @@ int xyl_ensemble_set_graphs(xyl_ensemble* e, int32_t enable);
 /* The path (XYL_PATH_*) on which each replica took, or would have taken, the
  * last chunk of the batched mode: the steps between two samples or ends.
  * XYL_PATH_LDS: whole in one workgroup's LDS, several steps per launch.  The
- * choice follows the chunk's length: fewer than 4 steps, fewer than 8, fewer
- * than 16, and longer ones have a plan each. */
+ * choice follows the chunk: fewer than 4 steps (these go with the plan of the
+ * chunk before them), fewer than 8, fewer than 16, and longer ones have a plan
+ * each, those below 16 steps another one where they start with samples of
+ * whole-in-LDS replicas or end with a replica's last step. */
 int xyl_ensemble_paths(xyl_ensemble* e, int32_t* path);
 /* Steps per pass for the batched mode (1 or 2; default 2).  With 2, chunks of 4
  * steps and more advance the replicas by the paths that a plan for the chunk's

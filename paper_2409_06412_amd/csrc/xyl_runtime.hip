@@ -2274,11 +2274,12 @@ struct xyl_ensemble {
         DevBuf<Task2> tasks;
         int ntasks = 0;
     };
-    // How the replicas step in chunks of one class of lengths, and the launches'
-    // tables.  They are kept per class, so that a first short chunk decides
-    // nothing for long ones, and alternating lengths rebuild nothing.
+    // How the replicas step in chunks of one class, and the launches' tables.
+    // They are kept per class, so that a first short chunk decides nothing for
+    // long ones, and alternating lengths rebuild nothing.
     struct Tables {
         bool built = false;
+        uint64_t n = 0;                 // the chunk length that the plan was made for
         std::vector<int> planned_for;   // the active replicas that the plan was made for
         std::vector<int> strips;        // those of them in the tables: all but the LDS path's own
         std::vector<int> meas;          // those that the strip kernels measure: not the LDS path's
@@ -2302,14 +2303,18 @@ struct xyl_ensemble {
         std::unique_ptr<TileFits> fits;
         std::vector<TileSize> fit_sizes;
     };
-    static constexpr int kLengths = 4;
-    Tables tables[kLengths];
+    // Classes 0 to 3: fewer than 4, 8, 16 steps, and longer, each planned for the
+    // first length of it that was met.  Below 16 steps also: 4, chunks at whose
+    // end a replica ends (on tiles that replica's end would make new tables after
+    // a few steps: 48 LDS replicas of 32^2 to 64^2 ending 7 steps apart took 2.8
+    // ms with some of them on tiles, 2.4 without), and 5 and 6, chunks that start
+    // with samples of LDS replicas.
+    static constexpr int kClasses = 7;
+    Tables tables[kClasses];
     Tables* tab = &tables[0];       // of the last chunk
-    static int length_class(uint64_t n) { return n < 4 ? 0 : n < 8 ? 1 : n < 16 ? 2 : 3; }
-    // the length that a class' plan is made for
-    static uint64_t plan_length(int cls) {
-        constexpr uint64_t n[kLengths] = {1, 6, 12, 200};
-        return n[cls];
+    static int chunk_class(uint64_t n, bool ending, bool lds_sampled) {
+        if (n < 4 || n >= 16) return n < 4 ? 0 : 3;
+        return ending ? 4 : (n < 8 ? 1 : 2) + (lds_sampled ? 4 : 0);
     }
     bool tiles_ok = true;           // false: no memory for the second velocity buffer
     // the tables serve neither steps nor measurements any more
@@ -2319,6 +2324,7 @@ struct xyl_ensemble {
             t.built = false;
             t.planned_for.clear();
             t.meas.clear();
+            t.n = 0;
         }
     }
     DevBuf<double> part;
@@ -2357,7 +2363,7 @@ struct xyl_ensemble {
     std::vector<hipStream_t> cls_streams;
     std::vector<hipEvent_t> cls_events;   // [0] fork, [1 + i] join of class i + 1
     // Chunks of steps captured as graphs (step index from the device counter
-    // kc): keyed by (first step within the chunk, steps), captured the second
+    // kc): keyed by (tables, first step within the chunk, steps), captured the second
     // time a key is met and replayed after; all dropped when a table, the
     // launch shape or the steps per pass change (graph_version).
     // 0: no graphs; 1: graphs for chunks with at most one class of two-step
@@ -2374,7 +2380,7 @@ struct xyl_ensemble {
         int seen = 0;
         hipGraphExec_t exec = nullptr;
     };
-    std::map<std::pair<uint64_t, uint64_t>, ChunkGraph> graphs;
+    std::map<std::tuple<const Tables*, uint64_t, uint64_t>, ChunkGraph> graphs;
     void drop_graphs() {
         for (auto& g : graphs)
             if (g.second.exec) (void)hipGraphExecDestroy(g.second.exec);
@@ -2465,11 +2471,11 @@ static int class_rows(const xyl_ensemble* e, int waves, const std::vector<int>& 
 //     all of them take about 3.
 //   * Other widths: single tile-table steps, lattice_untiled_us's form.
 //   * Tiles: TileFits::best.
-// For chunks of n steps; another split than none is taken only where it gains
-// 5%, 30% in chunks of fewer than 16 steps: those pay two launches and more for
-// tiles, one whole in LDS, and new tables whenever one of the replicas ends (48
-// replicas of 32^2 to 64^2 that end 7 steps apart: 2.8 ms with a few of them on
-// tiles, 2.4 all in LDS).
+// For chunks of tab.n steps; another split than none is taken only where it
+// gains 5%.  With `ending` the LDS replicas stay whole in LDS; with `lds_sampled`
+// they are measured at the chunk's start, which is part of their launch whole in
+// LDS and a launch and two waits of its own beside tiles, some 10 us (20 replicas
+// of up to 5000 sites sampled every 4 steps: 51 us a chunk on tiles, 37 in LDS).
 struct EnsTilePlan {
     TilePlan shape;                 // T = 0: no tiles
     size_t lds = 0;
@@ -2477,8 +2483,9 @@ struct EnsTilePlan {
     std::vector<char> tiled;
 };
 static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, const std::vector<int>& active,
-                                  uint64_t n) {
+                                  bool ending, bool lds_sampled) {
     EnsTilePlan out;
+    const uint64_t n = tab.n;
     out.tiled.assign(e->n, 0);
     if (e->fusion != 2 || n < 4 || !e->tiles_ok) return out;
     const bool f64 = e->dtype == XYL_F64;
@@ -2491,8 +2498,9 @@ static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, co
         const xyl_replica_desc& d = e->desc[r];
         const bool fact = f64 || replica_factored(d);
         const bool fits = fact && tile_shape_ok(d.Lx, d.Ly);
-        if (!fits && e->lds[r]) lds_fixed_sites += (double)d.Lx * d.Ly;
-        if (!fits) continue;
+        const bool stays = !fits || (ending && e->lds[r]);
+        if (stays && e->lds[r]) lds_fixed_sites += (double)d.Lx * d.Ly;
+        if (stays) continue;
         if (e->lds[r]) unit[0].push_back(r);
         else if (!f64 && step2_shape(d.Lx, d.Ly)) unit[(d.Lx + kWaveSites - 1) / kWaveSites].push_back(r);
         else unit[17].push_back(r);
@@ -2566,7 +2574,6 @@ static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, co
     const TileFits& fits = *tab.fits;
     // (more than 6 units never occur in practice; the first ones are split then)
     const int nu = std::min<int>((int)used.size(), 6);
-    const double gain = n < 16 ? 0.7 : 0.95;
     double best = 1e30;
     unsigned pick = 0;
     std::vector<long> pick_count;
@@ -2596,8 +2603,9 @@ static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, co
         }
         if (groups > 1) main_us *= 0.9;
         main_us += single_us;
+        if (lds_sampled && used[0] == 0 && (m & 1u)) main_us += 10.0 / (double)n;
         const double us = main_us > 0.0 ? std::max(lds_us, main_us + lds_share) : lds_us;
-        if (us < best * (m ? gain : 1.0)) {
+        if (us < best * (m ? 0.95 : 1.0)) {
             best = us;
             pick = m;
             pick_count = count;
@@ -2625,23 +2633,38 @@ static void ens_join_streams(xyl_ensemble* e) {
 }
 
 // Makes e->tab the tables for a chunk of n steps of the `active` replicas (LDS
-// replicas among them).  What the tables hold of the replicas that step on
+// replicas among them), one of which ends with it if `ending`.  A chunk too
+// short for tiles and passes goes with the last chunk's tables where those are
+// the same replicas'.  What the tables hold of the replicas that step on
 // strips and tiles stays while those and their plan do: an LDS replica that
 // ends changes nothing, and an ensemble that only the LDS path steps uploads
 // nothing.
 template <typename R>
-static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<int>& active, uint64_t n) {
+static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<int>& active, uint64_t n,
+                             bool ending, bool lds_sampled) {
     if (e->tables_fusion != e->fusion) e->drop_tables();
     e->tables_fusion = e->fusion;
-    const int cls = xyl_ensemble::length_class(n);
+    const int cls = xyl_ensemble::chunk_class(n, ending, lds_sampled);
     xyl_ensemble::Tables* before = e->tab;
+    if (cls == 0 && before->built && before->planned_for == active) return;
     xyl_ensemble::Tables& t = e->tables[cls];
     e->tab = &t;
+    // (the replicas on tiles before: a replica that ended since changes between
+    // the streams too, as a sample of its last step is taken by the other)
+    const std::vector<char> tiled_before = before->tiled;
+    auto join = [&] {
+        if (t.tiled != tiled_before) ens_join_streams(e);
+    };
     if (t.built && t.planned_for == active) {
-        if (before != &t) ens_join_streams(e);
+        join();
         return;
     }
-    EnsTilePlan plan = ens_plan_tiles(e, t, active, xyl_ensemble::plan_length(cls));
+    if (!t.n) {
+        t.n = n;
+        t.fits.reset();
+        t.fit_sizes.clear();
+    }
+    EnsTilePlan plan = ens_plan_tiles(e, t, active, cls == 4, cls > 4);
     if (plan.shape.T) {
         // where the second velocity buffer does not fit, the other paths do
         // (the classes, which need it too, report that)
@@ -2652,7 +2675,8 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
             (void)hipGetLastError();
             e->tiles_ok = false;
             e->drop_tables();
-            plan = ens_plan_tiles(e, t, active, xyl_ensemble::plan_length(cls));
+            t.n = n;
+            plan = ens_plan_tiles(e, t, active, cls == 4, cls > 4);
         }
     }
     std::vector<int> strips, meas;
@@ -2664,12 +2688,12 @@ static void ens_upload_table(xyl_ensemble* e, uint64_t jbase, const std::vector<
                       t.tile_shape.T == plan.shape.T && t.tile_shape.S == plan.shape.S &&
                       t.tile_shape.threads == plan.shape.threads;
     t.planned_for = active;
-    if (!same || before != &t) ens_join_streams(e);
+    t.tiled = plan.tiled;
+    join();
     if (same) return;
     t.built = false;
     t.strips = strips;
     t.meas = meas;
-    t.tiled = plan.tiled;
     t.boxes = plan.boxes;
     t.tile_shape = plan.shape;
     t.tile_lds = plan.lds;
@@ -2924,7 +2948,12 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
             chunk = any_active ? std::min(chunk, c) : c;
             any_active = true;
         }
-        if (!active.empty()) ens_upload_table<R>(e, e->j, active, chunk);
+        bool ending = false, lds_sampled = false;
+        for (int r : active) {
+            ending = ending || e->k[r] + chunk == e->desc[r].nsteps;
+            lds_sampled = lds_sampled || (meas[r] && e->lds[r]);
+        }
+        if (!active.empty()) ens_upload_table<R>(e, e->j, active, chunk, ending, lds_sampled);
         xyl_ensemble::Tables& t = *e->tab;
         bool step_g = false;   // replicas that step on the ensemble's stream and its class streams
         for (int r : active) step_g = step_g || !e->lds[r] || t.tiled[r];
@@ -3140,14 +3169,14 @@ static void ens_step_batched(xyl_ensemble* e, uint64_t nsteps, EnsSamples& smp) 
                 // at most kMaxChunkGraphs chunk shapes hold a graph at a time
                 // (adaptive sampling can meet many)
                 constexpr size_t kMaxChunkGraphs = 32;
-                if (!e->graphs.count({c, n}) && e->graphs.size() >= 4 * kMaxChunkGraphs) e->drop_graphs();
-                cg = &e->graphs[{c, n}];
+                if (!e->graphs.count({&t, c, n}) && e->graphs.size() >= 4 * kMaxChunkGraphs) e->drop_graphs();
+                cg = &e->graphs[{&t, c, n}];
                 if (!cg->exec && cg->seen + 1 >= 2) {
                     size_t held = 0;
                     for (auto& g : e->graphs) held += g.second.exec != nullptr;
                     if (held >= kMaxChunkGraphs) {
                         e->drop_graphs();
-                        cg = &e->graphs[{c, n}];
+                        cg = &e->graphs[{&t, c, n}];
                         cg->seen = 1;
                     }
                 }
@@ -3305,7 +3334,7 @@ static Launch ensemble_autotune_impl(xyl_ensemble* e) {
         e->launch = best;
         e->fusion = 2;
         const int steps4 = (steps + 3) / 4 * 4;
-        if (!active.empty()) ens_upload_table<R>(e, e->j, active, (uint64_t)steps4);
+        if (!active.empty()) ens_upload_table<R>(e, e->j, active, (uint64_t)steps4, false, false);
         const xyl_ensemble::Tables& tab = *e->tab;
         if (!active.empty() && tab.groups()) {
             const Lat<float>* dreps = reinterpret_cast<const Lat<float>*>(dtab.p);
