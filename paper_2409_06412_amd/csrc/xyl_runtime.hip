@@ -2595,6 +2595,8 @@ static EnsTilePlan ens_plan_tiles(xyl_ensemble* e, xyl_ensemble::Tables& tab, co
                 single_us += flat_us[q];
             }
         }
+        // (what is left to the other paths may cost more already)
+        if (std::max(lds_us, 0.9 * main_us + single_us + lds_share) >= 0.95 * best) continue;
         if (m) {
             const double t = fits.best(count, nullptr, nullptr, nullptr);
             if (t >= 1e30) continue;
