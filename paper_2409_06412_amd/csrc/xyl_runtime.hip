@@ -3822,26 +3822,26 @@ static void adjoint_forward_impl(xyl_lattice* h, uint64_t N, uint64_t K, uint64_
 // where it does not (FP64 rows above 568 sites), single reverse steps.
 static int adjoint2_rows(const xyl_lattice* h) { return h->adj2_rows ? h->adj2_rows : 2; }
 
-// Times per step (us) of the sweep without tiles, for choosing: reverse steps
-// one by one or two per pass (a pass in FP64 by the rounds of its strips: their
-// LDS leaves one workgroup per CU from 288 sites a row on), and recomputed
-// steps one by one or two per pass (storing twice the state, a seventh more
-// than stepping).  Sweeps measured, us per step, tiles for both and neither:
-// FP32 512^2 3.8 and 6.3, 1024^2 9.9 and 15.2, 2048^2 32.4 and 43.2, 4096^2 124
-// and 154 (121 with the recompute two steps per pass); FP64 256^2 5.8 and 11.0,
-// 560^2 13.7 and 22.1, 320 x 1000 13.8 and 17.1, 1024^2 35.6 and 51.9, 1448^2
-// 69.8 and 79.5, but 512^2 12.1 and 11.4 with the reverse two steps per pass,
-// 2048 x 1024 86 and 73, 2048^2 134 and 121, 4096 x 2048 276 and 212.
-static double adjoint_untiled_us(const xyl_lattice* h, bool fuse) {
-    const double N = (double)h->N;
-    if (h->dtype == XYL_F32) return (fuse ? 3.3 : 6.0) + N / 1.5e5;
-    if (!fuse) return 18.0 + N / 7.6e4;
-    const int rows = adjoint2_rows(h), strips = (h->Ly + rows - 1) / rows;
-    const int slots = h->cus * std::max(1, (int)(160 * 1024 / adjoint2_lds<double>(h->Lx, rows)));
-    return 0.95 * ((strips + slots - 1) / slots) * (4.2 + 0.0055 * h->Lx);
+// Times per step (us) of the sweep without tiles, for choosing.  The reverse
+// steps go on tiles, but for single ones in FP64 (rows too long for two per pass)
+// where those are faster.  Sweeps measured, us per step, tiles for both and
+// neither: FP32 512^2 3.8 and 6.3, 1024^2 9.9 and 15.2, 2048^2 32.4 and 43.2,
+// 4096^2 124 and 154 (121 with the recompute two steps per pass); FP64 1024^2
+// 35.6 and 51.9, 1448^2 69.8 and 79.5, but 2048 x 1024 86 and 73, 2048^2 134 and
+// 121, 4096 x 2048 276 and 212.  Reverse on tiles and two steps per pass, the
+// recompute on tiles both times, over 60 shapes of up to 2^20 sites in FP64 and 2^24
+// in FP32, 4 to 200 steps a segment: FP64 512^2 10.3 and 10.9, 68 x 2400 8.3 and
+// 10.8, 200 x 1400 11.1 and 14.4, 512 x 1400 25.6 and 28.0; 128 x 1400 alone 9.7
+// and 9.4.
+static double adjoint_single_us(const xyl_lattice* h) {
+    return h->dtype == XYL_F64 ? 18.0 + (double)h->N / 7.6e4 : 1e30;
 }
-static double adjoint_recompute_us(const xyl_lattice* h, bool two_step) {
-    return two_step ? 1.15 * step2_us(h->Lx, h->Ly, h->cus, step2_rows(h)) : lattice_single_us(h);
+// (without tiles a segment of K steps, K - 1 of them recomputed, also starts
+// with two copies of the checkpoint)
+static double adjoint_recompute_us(const xyl_lattice* h, bool two_step, uint64_t K) {
+    const double elem = h->dtype == XYL_F64 ? 8.0 : 4.0;
+    return (two_step ? 1.15 * step2_us(h->Lx, h->Ly, h->cus, step2_rows(h)) : lattice_single_us(h)) +
+           (6.0 + 4.0 * elem * (double)h->N / 4.5e6) / (double)(K - 1);
 }
 
 template <typename R>
@@ -3878,8 +3878,8 @@ static void adjoint_backward_impl(xyl_lattice* h, double* grad, void* dth0, void
         if (!tile_plan_reverse(h->Lx, h->Ly, f64, h->cus, a->tile_K, &a->rev, &a->rev_us)) a->rev = TilePlan();
     }
     const TilePlan &rev = a->rev, &rec = a->rec;
-    const bool rev_tiles = may_tile && rev.T > 0 && a->rev_us < adjoint_untiled_us(h, fuse);
-    const bool rec_tiles = may_tile && rec.T > 0 && a->rec_us < adjoint_recompute_us(h, rec2);
+    const bool rev_tiles = may_tile && rev.T > 0 && (fuse || a->rev_us < adjoint_single_us(h));
+    const bool rec_tiles = may_tile && rec.T > 0 && a->rec_us < adjoint_recompute_us(h, rec2, K);
     const int ntasks = rev_tiles ? rev.ntx * rev.nty : adjoint_tasks<R>(v, l.rows, fuse ? rows2 : 0);
     a->gacc.reserve((size_t)ntasks * 4);
     check_hip(hipMemsetAsync(a->gacc.p, 0, sizeof(double) * ntasks * 4, h->stream), "hipMemsetAsync");

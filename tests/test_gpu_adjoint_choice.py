@@ -39,7 +39,8 @@ def backward_us(lat, n):
     ("f32", 4096, 4096, 10), ("f32", 4096, 512, 20), ("f64", 64, 64, 50), ("f64", 256, 256, 50), ("f64", 512, 512, 50),
     ("f64", 1024, 1024, 20), ("f64", 1448, 1448, 20), ("f64", 2048, 1024, 20), ("f64", 2048, 2048, 20),
     ("f64", 4096, 2048, 10), ("f64", 400, 400, 50), ("f64", 560, 560, 50), ("f64", 320, 1000, 50), ("f64", 500, 2000, 20),
-    ("f64", 1024, 2400, 20),
+    ("f64", 1024, 2400, 20), ("f32", 2528, 2528, 3), ("f64", 68, 2337, 3), ("f64", 68, 2337, 50),
+    ("f64", 128, 4000, 20), ("f64", 512, 512, 8),
 ])
 def test_default_sweep_is_not_slower_than_without_tiles(xyl, dtype, Lx, Ly, K):
     import torch
@@ -58,7 +59,7 @@ def test_default_sweep_is_not_slower_than_without_tiles(xyl, dtype, Lx, Ly, K):
 
 
 @pytest.mark.parametrize("dtype,Lx,Ly,K,n", [
-    ("f64", 512, 512, 20, 45),       # reverse two steps per pass, recompute on tiles
+    ("f64", 512, 512, 20, 45),       # both on tiles
     ("f32", 4096, 4096, 5, 11),      # reverse on tiles, recompute two steps per pass, a last segment of one step
     ("f64", 2048, 2048, 6, 12),      # single reverse steps
 ])
